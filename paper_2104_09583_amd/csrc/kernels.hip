@@ -47,9 +47,16 @@ __device__ __forceinline__ double mod_reduce(double v, double q, double qinv) {
 //   r = a b - k q = fma(-k, q, h) + l is an exact integer with |r| < 0.91 q;
 //   reduce_sym: x - q rint(x / q) lies in [-q/2, q/2] for |x| < 8 q;
 //   canon: maps [-q/2, q/2] to [0, q).
-// A radix-8 round grows |x| from q/2 by at most 3 x 0.91 q (forward) or by a
-// factor 8 (inverse sums), so one reduce_sym per element and round keeps every
-// intermediate below 4 q and every product below 2^101 (exact in fp64).
+// In general |mul_lazy(a, b)| <= (0.5 + 3 x 2^-53 |a|) q: the quotient estimate is off by three roundings.
+// Forward, a stage adds one such product to |x|: from |x| <= q six stages reach at most 7.6 q < 2^52 for
+// q = 2^49, every value still an exact integer, so the row pass folds back once, after its second radix-8
+// round; for q < 2^46 (kFwdLazy) its twelve stages stay below 20 q even from 8 q, and it never does.  Inverse, a stage doubles the sums: 2^3 per round, folded back after every round, or for
+// q < 2^44 (kInvLazy) after every second one (64 q <= 2^50).  For q < 2^42 (kInvOpen) the inverse row pass
+// also leaves its output unreduced (32 q): three column stages that follow reach 256 q <= 2^50, where the
+// next product is still within 0.875 q (four: 512 q, within 1.25 q and folded back there).
+constexpr double kFwdLazy = 70368744177664.0;   // 2^46
+constexpr double kInvLazy = 17592186044416.0;   // 2^44
+constexpr double kInvOpen = 4398046511104.0;    // 2^42
 __device__ __forceinline__ double mul_lazy(double a, double b, double q, double qinv) {
   double h = a * b;
   double l = __fma_rn(a, b, -h);
@@ -59,7 +66,7 @@ __device__ __forceinline__ double mul_lazy(double a, double b, double q, double 
 __device__ __forceinline__ double reduce_sym(double x, double q, double qinv) {
   return __fma_rn(-rint(x * qinv), q, x);
 }
-__device__ __forceinline__ double canon(double x, double q) { return x < 0.0 ? x + q : x; }
+__device__ __forceinline__ double canon(double x, double q) { return __fma_rn(x < 0.0 ? 1.0 : 0.0, q, x); }
 
 // A load known to be from global memory (not through a flat address).  Flat loads count on the same
 // wait counter as LDS and scalar loads, so every LDS wait before a barrier would also wait for them;
@@ -101,10 +108,10 @@ __device__ __forceinline__ void lds_wave_sync() { asm volatile("s_waitcnt lgkmcn
 // Slot k holds a(psi^e) with e = 2 bitrev(k) + 1.  sigma_g(a)(psi^e) = a(psi^(g e)), so the
 // output slot k reads the input slot holding exponent g e mod 2N.
 __device__ __forceinline__ uint32_t auto_src(uint32_t k, uint64_t g, int logN) {
+  // g, e < 2 N: only the product's low logN + 1 bits are used, so a 24-bit product (full rate) serves N < 2^23
   uint32_t e = 2 * (__builtin_bitreverse32(k) >> (32 - logN)) + 1;
-  uint64_t ge = (g * e) & ((2ULL << logN) - 1);
-  uint32_t idx = (uint32_t)((ge - 1) >> 1);
-  return __builtin_bitreverse32(idx) >> (32 - logN);
+  uint32_t ge = __umul24((uint32_t)g, e) & (uint32_t)((2ULL << logN) - 1);
+  return __builtin_bitreverse32(ge >> 1) >> (32 - logN);
 }
 
 // ------------------------------------------------------------------ NTT
@@ -497,7 +504,6 @@ __device__ __forceinline__ void row4_fwd_tile(const double* __restrict__ src, si
   for (int k = 0; k < 8; ++k) x[k] = gload(src + jA + 512 * k);
   radix8_ct_w(x, wa, pr);
   const Tw8 wc = tw8_load(pr.fwd, gb0 + jC, 8, mC);
-  red8(x, pr);
 #pragma unroll
   for (int k = 0; k < 8; ++k) sh[lds_idx(jA + 512 * k)] = x[k];
   lds_barrier();
@@ -505,7 +511,7 @@ __device__ __forceinline__ void row4_fwd_tile(const double* __restrict__ src, si
   for (int k = 0; k < 8; ++k) x[k] = sh[lds_idx(jB + 64 * k)];
   radix8_ct_w(x, wb, pr);
   const Tw8 wd = tw8_load(pr.fwd, gb0 + jD, 1, mD);
-  red8(x, pr);
+  if (pr.q >= kFwdLazy) red8(x, pr);   // uniform
 #pragma unroll
   for (int k = 0; k < 8; ++k) sh[lds_idx(jB + 64 * k)] = x[k];
   lds_wave_sync();   // rounds B and C touch the same 512 elements of this wave's block
@@ -516,7 +522,6 @@ __device__ __forceinline__ void row4_fwd_tile(const double* __restrict__ src, si
     for (int k = 0; k < 8; ++k) y[k] = gload(pre + t + 512 * k);
   }
   radix8_ct_w(x, wc, pr);
-  red8(x, pr);
 #pragma unroll
   for (int k = 0; k < 8; ++k) sh[lds_idx(jC + 8 * k)] = x[k];
   lds_wave_sync();   // and so do rounds C and D
@@ -546,7 +551,7 @@ __device__ __forceinline__ void row4_inv_tile(const double* __restrict__ src, si
   for (int k = 0; k < 8; ++k) x[k] = sh[lds_idx(jD + k)];
   radix8_gs_w(x, wd, pr);
   const Tw8 wb = tw8_load(pr.inv, gb0 + jB, 64, mB);
-  red8(x, pr);
+  if (pr.q >= kInvLazy) red8(x, pr);   // uniform
 #pragma unroll
   for (int k = 0; k < 8; ++k) sh[lds_idx(jD + k)] = x[k];
   lds_wave_sync();   // rounds D and C touch the same 512 elements of this wave's block
@@ -561,7 +566,7 @@ __device__ __forceinline__ void row4_inv_tile(const double* __restrict__ src, si
 #pragma unroll
   for (int k = 0; k < 8; ++k) x[k] = sh[lds_idx(jB + 64 * k)];
   radix8_gs_w(x, wb, pr);
-  red8(x, pr);
+  if (pr.q >= kInvLazy) red8(x, pr);
 #pragma unroll
   for (int k = 0; k < 8; ++k) sh[lds_idx(jB + 64 * k)] = x[k];
   lds_barrier();
@@ -591,8 +596,6 @@ __device__ __forceinline__ void row4_fwd_tile2(const double* __restrict__ srcA, 
   radix8_ct_w(x, wa, pr);
   radix8_ct_w(y, wa, pr);
   const Tw8 wc = tw8_load(pr.fwd, gb0 + jC, 8, mC);
-  red8(x, pr);
-  red8(y, pr);
 #pragma unroll
   for (int k = 0; k < 8; ++k) {
     sh[lds_idx(jA + 512 * k)] = x[k];
@@ -607,8 +610,10 @@ __device__ __forceinline__ void row4_fwd_tile2(const double* __restrict__ srcA, 
   radix8_ct_w(x, wb, pr);
   radix8_ct_w(y, wb, pr);
   const Tw8 wd = tw8_load(pr.fwd, gb0 + jD, 1, mD);
-  red8(x, pr);
-  red8(y, pr);
+  if (pr.q >= kFwdLazy) {   // uniform
+    red8(x, pr);
+    red8(y, pr);
+  }
 #pragma unroll
   for (int k = 0; k < 8; ++k) {
     sh[lds_idx(jB + 64 * k)] = x[k];
@@ -622,8 +627,6 @@ __device__ __forceinline__ void row4_fwd_tile2(const double* __restrict__ srcA, 
   }
   radix8_ct_w(x, wc, pr);
   radix8_ct_w(y, wc, pr);
-  red8(x, pr);
-  red8(y, pr);
 #pragma unroll
   for (int k = 0; k < 8; ++k) {
     sh[lds_idx(jC + 8 * k)] = x[k];
@@ -672,8 +675,10 @@ __device__ __forceinline__ void row4_inv_tile2(size_t gb0, int S1, const DevPrim
   radix8_gs_w(x, wd, pr);
   radix8_gs_w(y, wd, pr);
   const Tw8 wb = tw8_load(pr.inv, gb0 + jB, 64, mB);
-  red8(x, pr);
-  red8(y, pr);
+  if (pr.q >= kInvLazy) {   // uniform
+    red8(x, pr);
+    red8(y, pr);
+  }
 #pragma unroll
   for (int k = 0; k < 8; ++k) {
     sh[lds_idx(jD + k)] = x[k];
@@ -703,8 +708,10 @@ __device__ __forceinline__ void row4_inv_tile2(size_t gb0, int S1, const DevPrim
   }
   radix8_gs_w(x, wb, pr);
   radix8_gs_w(y, wb, pr);
-  red8(x, pr);
-  red8(y, pr);
+  if (pr.q >= kInvLazy) {
+    red8(x, pr);
+    red8(y, pr);
+  }
 #pragma unroll
   for (int k = 0; k < 8; ++k) {
     sh[lds_idx(jB + 64 * k)] = x[k];
@@ -737,12 +744,14 @@ __global__ __launch_bounds__(512) void ntt_rowreg4_kernel(double* __restrict__ b
     for (int k = 0; k < 8; ++k) a[t + 512 * k] = canon(reduce_sym(x[k], pr.q, pr.qinv), pr.q);
   } else {
     row4_inv_tile(a, t0, S1, pr, sh, x);
+    if (scale) {
 #pragma unroll
-    for (int k = 0; k < 8; ++k) {
-      double v = x[k];
-      if (scale) v = mul_lazy(v, pr.ninv, pr.q, pr.qinv);
-      v = reduce_sym(v, pr.q, pr.qinv);
-      a[t + 512 * k] = scale ? canon(v, pr.q) : v;
+      for (int k = 0; k < 8; ++k)
+        a[t + 512 * k] = canon(reduce_sym(mul_lazy(x[k], pr.ninv, pr.q, pr.qinv), pr.q, pr.qinv), pr.q);
+    } else {
+      if (pr.q >= kInvOpen || S1 > 4) red8(x, pr);   // uniform
+#pragma unroll
+      for (int k = 0; k < 8; ++k) a[t + 512 * k] = x[k];
     }
   }
 }
@@ -785,8 +794,8 @@ __global__ __launch_bounds__(512) void ntt_rowinv_gather_kernel(double* __restri
 #pragma unroll
     for (int k = 0; k < 8; ++k) {
       const size_t o2 = off + t0 + t + 512 * k;
-      v[k] = mod_mul(gload(a + t + 512 * k), gload(mulp.p[j] + o2), pr.q, pr.qinv);
-      if (poly == 0) v[k] = mod_add(v[k], gload(addp.p[j] + o2), pr.q);
+      v[k] = mul_lazy(gload(a + t + 512 * k), gload(mulp.p[j] + o2), pr.q, pr.qinv);
+      if (poly == 0) v[k] = reduce_sym(v[k] + gload(addp.p[j] + o2), pr.q, pr.qinv);
     }
     row4_inv_tile(a, t0, S1, pr, sh, x, v);
   } else if (mulp.p[j] != nullptr) {
@@ -795,15 +804,16 @@ __global__ __launch_bounds__(512) void ntt_rowinv_gather_kernel(double* __restri
     const int t = threadIdx.x;
     double v[8];
 #pragma unroll
-    for (int k = 0; k < 8; ++k) v[k] = mod_mul(gload(a + t + 512 * k), gload(bs + t + 512 * k), pr.q, pr.qinv);
+    for (int k = 0; k < 8; ++k) v[k] = mul_lazy(gload(a + t + 512 * k), gload(bs + t + 512 * k), pr.q, pr.qinv);
     row4_inv_tile(a, t0, S1, pr, sh, x, v);
   } else {
     row4_inv_tile(a, t0, S1, pr, sh, x);
   }
   double* o = dst + (size_t)r * N + t0;
   const int t = threadIdx.x;
+  if (pr.q >= kInvOpen) red8(x, pr);   // uniform
 #pragma unroll
-  for (int k = 0; k < 8; ++k) o[t + 512 * k] = reduce_sym(x[k], pr.q, pr.qinv);
+  for (int k = 0; k < 8; ++k) o[t + 512 * k] = x[k];
 }
 
 // Forward row pass fused with the end of a ModDown (kMode 1) or of a modulus switch (kMode 2).
@@ -861,15 +871,16 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(6))) void n
 #pragma unroll
     for (int kk = 0; kk < 8; ++kk) {
       const size_t c = (size_t)i * N + t0 + t + 512 * kk;
-      yv[kk] = mod_mul(yv[kk], gload(mulp.p[j] + c), pr.q, pr.qinv);
-      if (k == 0) yv[kk] = mod_add(yv[kk], gload(add.p[j] + c), pr.q);
+      yv[kk] = mul_lazy(yv[kk], gload(mulp.p[j] + c), pr.q, pr.qinv);
+      if (k == 0) yv[kk] += gload(add.p[j] + c);
     }
   }
+  // lazy to the end: |x| < 20 q (below 7.6 q for q >= 2^46) so each product is below 2 q, and with the
+  // addends the sum stays below 8 q
 #pragma unroll
   for (int kk = 0; kk < 8; ++kk) {
     const size_t c = t0 + t + 512 * kk;
-    const double wv = reduce_sym(x[kk], pr.q, pr.qinv);
-    double v = mul_lazy(yv[kk], m1, pr.q, pr.qinv) - mul_lazy(wv, m2, pr.q, pr.qinv);
+    double v = mul_lazy(yv[kk], m1, pr.q, pr.qinv) - mul_lazy(x[kk], m2, pr.q, pr.qinv);
     if (kMode == 3) {
       double av;
       if (mulp.p[j] == nullptr) {
@@ -878,25 +889,19 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(6))) void n
         // the addend is the product of the ciphertexts add and mulp: its polynomial k (uniform)
         const size_t r0 = (size_t)i * N + c, r1 = ((size_t)(nl + 1) + i) * N + c;
         const double a0 = add.p[j][r0], b0 = mulp.p[j][r0];
-        av = k == 0 ? mod_mul(a0, b0, pr.q, pr.qinv)
-                    : mod_add(mod_mul(a0, mulp.p[j][r1], pr.q, pr.qinv),
-                              mod_mul(add.p[j][r1], b0, pr.q, pr.qinv), pr.q);
+        av = k == 0 ? mul_lazy(a0, b0, pr.q, pr.qinv)
+                    : mul_lazy(a0, mulp.p[j][r1], pr.q, pr.qinv) + mul_lazy(add.p[j][r1], b0, pr.q, pr.qinv);
       }
       v += mul_lazy(av, m3, pr.q, pr.qinv);
+      // an optional mask (the `in` pack, l limbs per poly) on the first add_np polys
+      if (k < add_np && in.p[j] != nullptr) v += in.p[j][orow + c];
+    } else if (kMode == 1) {
+      if (add_mode == 1) v += add.p[j][orow + c];
+      if (add_mode == 2 && k == 0) v += add.p[j][(size_t)i * N + (g == 1 ? c : auto_src((uint32_t)c, g, logN))];
+    } else if (kMode == 2) {
+      if (k < add_np && add.p[j] != nullptr) v += add.p[j][orow + c];
     }
-    v = canon(reduce_sym(v, pr.q, pr.qinv), pr.q);
-    // kMode 3: an optional mask (the `in` pack, l limbs per poly) on the first add_np polys
-    if (kMode == 3 && k < add_np && in.p[j] != nullptr) v = mod_add(v, in.p[j][orow + c], pr.q);
-    if (kMode == 1) {
-      if (add_mode == 1) v = mod_add(v, add.p[j][orow + c], pr.q);
-      if (add_mode == 2 && k == 0) {
-        const size_t src = g == 1 ? c : auto_src((uint32_t)c, g, logN);
-        v = mod_add(v, add.p[j][(size_t)i * N + src], pr.q);
-      }
-    } else if (kMode == 2 && k < add_np && add.p[j] != nullptr) {
-      v = mod_add(v, add.p[j][orow + c], pr.q);
-    }
-    out.p[j][orow + c] = v;
+    out.p[j][orow + c] = canon(reduce_sym(v, pr.q, pr.qinv), pr.q);
   }
 }
 
@@ -1174,6 +1179,8 @@ __global__ __launch_bounds__(256) void ntt_bridge_kernel(BridgeSet set, const De
     BridgeOut<S1> nxt;
     if (o + 4 < o1) nxt = bridge_out_load<S1, kMode>(d, P, o + 4);
     const double q = cur.q, qinv = cur.qinv;
+    // below 2^46 the sums (< 8 q) pass unreduced through the column stages and into the row pass
+    const bool lazy = q < kFwdLazy;
     double x[R];
 #pragma unroll
     for (int r = 0; r < R; ++r) {
@@ -1185,10 +1192,14 @@ __global__ __launch_bounds__(256) void ntt_bridge_kernel(BridgeSet set, const De
           if (k < nc) acc += mul_lazy(ys[k][r][lane], cur.m[k], q, qinv);
         // mode 2: |v| <= q_l / 2 < 2 q_o, so the sum stays below 8 q_o
         if (kMode == 2) acc += vt[r];
-        x[r] = reduce_sym(acc, q, qinv);
+        x[r] = acc;
       } else {
         x[r] = reduce_sym(ys[0][r][lane], q, qinv);
       }
+    }
+    if (kMode != 1 && !lazy) {   // uniform
+#pragma unroll
+      for (int r = 0; r < R; ++r) x[r] = reduce_sym(x[r], q, qinv);
     }
 #pragma unroll
     for (int s = 0; s < S1; ++s) {
@@ -1200,9 +1211,13 @@ __global__ __launch_bounds__(256) void ntt_bridge_kernel(BridgeSet set, const De
         for (int oo = 0; oo < half; ++oo) bfly_ct(x[g * 2 * half + oo], x[g * 2 * half + oo + half], w, q, qinv);
       }
     }
+    if (!lazy) {
+#pragma unroll
+      for (int r = 0; r < R; ++r) x[r] = reduce_sym(x[r], q, qinv);
+    }
     double* a = out + (size_t)cur.row.x * N;
 #pragma unroll
-    for (int r = 0; r < R; ++r) a[r * C + c] = reduce_sym(x[r], q, qinv);
+    for (int r = 0; r < R; ++r) a[r * C + c] = x[r];
     cur = nxt;
   }
 }
@@ -1958,11 +1973,12 @@ void launch_ms_finish_multi(Context& c, const std::vector<double*>& out, const s
   }
 }
 
-// (t0, t1) <- polynomials 0 and 1 of the product of ciphertexts (t0, t1) and (b0, b1) at one coefficient
+// (t0, t1) <- polynomials 0 and 1 of the product of ciphertexts (t0, t1) and (b0, b1) at one coefficient (lazy:
+// below 2 q)
 __device__ __forceinline__ void ks_tensor_top(double& t0, double& t1, double b0, double b1, const DevPrime& pr) {
   const double a0 = t0;
-  t0 = mod_mul(a0, b0, pr.q, pr.qinv);
-  t1 = mod_add(mod_mul(a0, b1, pr.q, pr.qinv), mod_mul(t1, b0, pr.q, pr.qinv), pr.q);
+  t0 = mul_lazy(a0, b0, pr.q, pr.qinv);
+  t1 = mul_lazy(a0, b1, pr.q, pr.qinv) + mul_lazy(t1, b0, pr.q, pr.qinv);
 }
 
 // key-switch inner product over jobs; digit rows come straight from the job's input poly (a product's
@@ -1999,14 +2015,14 @@ __global__ void ks_inner2_kernel(KsPack jobs, int D_, int nE, int nl, int L, int
     }
 #pragma unroll
     for (int j = 0; j < kD; ++j) {
-      const double ej = prod && j == own ? mod_mul(e[j], ob, pr.q, pr.qinv) : e[j];
+      const double ej = prod && j == own ? mul_lazy(e[j], ob, pr.q, pr.qinv) : e[j];
       a0 += mul_lazy(ej, kb[j], pr.q, pr.qinv);
       a1 += mul_lazy(ej, ka[j], pr.q, pr.qinv);
     }
   } else {
     for (int j = 0; j < D_; ++j) {
       double e = row(j)[src];
-      if (prod && j == own) e = mod_mul(e, ob, pr.q, pr.qinv);
+      if (prod && j == own) e = mul_lazy(e, ob, pr.q, pr.qinv);
       const size_t ko = (size_t)j * key_ds + (size_t)prime * N + i;
       a0 += mul_lazy(e, jb.kb[ko], pr.q, pr.qinv);
       a1 += mul_lazy(e, jb.ka[ko], pr.q, pr.qinv);
@@ -2103,8 +2119,7 @@ __global__ __launch_bounds__(512, 4) void ks_inner_rows_kernel(KsPack jobs, int 
     double kv[8];
 #pragma unroll
     for (int k = 0; k < 8; ++k) kv[k] = gload(jb.kb + ko + 512 * k);
-#pragma unroll
-    for (int k = 0; k < 8; ++k) x[k] = reduce_sym(x[k], pr.q, pr.qinv);
+    if (pr.q >= kFwdLazy) red8(x, pr);   // uniform; below, |x| < 20 q and the product is within 0.875 q
 #pragma unroll
     for (int k = 0; k < 8; ++k) a0[k] += mul_lazy(x[k], kv[k], pr.q, pr.qinv);
 #pragma unroll
@@ -2153,7 +2168,7 @@ __global__ __launch_bounds__(512, 4) void ks_inner_rows_kernel(KsPack jobs, int 
     if (jb.in_b != nullptr) {
 #pragma unroll
       for (int k = 0; k < 8; ++k)
-        x[k] = mod_mul(x[k], gload(jb.in_b + (size_t)o * N + t0 + t + 512 * k), pr.q, pr.qinv);
+        x[k] = mul_lazy(x[k], gload(jb.in_b + (size_t)o * N + t0 + t + 512 * k), pr.q, pr.qinv);
     }
     mac(own, x);
   }
@@ -2182,23 +2197,24 @@ __global__ __launch_bounds__(512, 4) void ks_inner_rows_kernel(KsPack jobs, int 
       a1[k] += mul_lazy(u1[k], ptop, pr.q, pr.qinv);
     }
   }
-#pragma unroll
-  for (int k = 0; k < 8; ++k) {
-    a0[k] = canon(reduce_sym(a0[k], pr.q, pr.qinv), pr.q);
-    a1[k] = canon(reduce_sym(a1[k], pr.q, pr.qinv), pr.q);
-  }
+  red8(a0, pr);
+  red8(a1, pr);
   if (o >= inv_from) {
     // rows the ModDown transforms back (the special rows, and the top data row of a ModDown merged with
     // the switch): the inverse row pass of both sums' tiles here, as the separate row pass would run it
     double x[8], y[8];
     lds_barrier();   // the tile buffers' previous use is over in every wave
     row4_inv_tile2(t0, S1, pr, sh, sh2, a0, a1, x, y);
+    if (pr.q >= kInvOpen) {   // uniform
+      red8(x, pr);
+      red8(y, pr);
+    }
 #pragma unroll
     for (int k = 0; k < 8; ++k) {
-      a0[k] = reduce_sym(x[k], pr.q, pr.qinv);
-      a1[k] = reduce_sym(y[k], pr.q, pr.qinv);
+      a0[k] = x[k];
+      a1[k] = y[k];
     }
-  }
+  }   // else signed, within q/2: the finish that reads them takes any representative below 2 q
 #pragma unroll
   for (int k = 0; k < 8; ++k) {
     const size_t c = t0 + t + 512 * k;

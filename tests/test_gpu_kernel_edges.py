@@ -1,0 +1,93 @@
+"""GPU kernels at the edges of their dispatch rules: prime sizes, tile and job counts, digit counts and layouts
+at which a kernel takes another branch, against the CPU oracle (residues are whole numbers: every comparison is
+exact)."""
+import math
+import sys
+
+import numpy as np
+import pytest
+
+from oracle import bgv as B
+from oracle import circuit as CI
+from oracle import compiler as OC
+from oracle import forest as F
+from oracle import nt
+from paper_2104_09583_amd import synth
+
+pytestmark = pytest.mark.gpu
+T = 65537
+
+
+def say(*a):
+    print("[gpu-test]", *a, file=sys.stderr, flush=True)
+
+
+@pytest.fixture(scope="module")
+def C():
+    from paper_2104_09583_amd import copse
+    return copse
+
+
+def same(exported, oct_):
+    assert exported["level"] == oct_.level and len(exported["polys"]) == len(oct_.polys)
+    for a, b in zip(exported["polys"], oct_.polys):
+        assert a.shape == b.shape and (a == b).all()
+
+
+def evaluate_groups(C, shape, seed, log_n, bits, alpha, enc, groups, n1=(0, 0), oracle_groups=1):
+    """`groups` query groups in one call on a chain whose data, q_0 and special primes lie just below 2^bits
+    (a triple): the first oracle_groups results equal the oracle's bit for bit, every result its evaluation
+    alone, every label the plain forest's."""
+    text = synth.gen_forest_text(shape, seed)
+    oc = OC.compile_forest(text, shape.n_features, shape.precision)
+    need = CI.seccomp_depth(shape.precision) + 2 + (math.ceil(math.log2(oc.d)) if oc.d > 1 else 0)
+    data, q0, sp = (1 << b for b in bits)
+    ctx = C.Context(log_n, need + 1, q0, data, alpha, sp)
+    sc = B.BGV(nt.make_chain(log_n, T, need + 1, q0, data, alpha, sp))
+    comp, meta = C.forest_compile(text, shape.n_features, shape.precision, log_n, n1_R=n1[0], n1_L=n1[1])
+    kseed = bytes([seed % 251]) * 32
+    keys = ctx.keygen(kseed, C.compiled_rotations(meta))
+    evk = ctx.export_eval(keys)
+    model = ctx.model_encode(comp, keys if enc else None, encrypt=enc, seed=kseed if enc else None)
+    qs = [synth.gen_queries(min(5, meta.queries_per_ct), shape.n_features, shape.precision, 700 + g)
+          for g in range(groups)]
+    cts = [ctx.query_encrypt(keys, meta, q, kseed, group=g) for g, q in enumerate(qs)]
+    say("evaluate", groups, "groups, bits", bits, "alpha", alpha, "enc", enc, "log_n", log_n)
+    res = ctx.evaluate_batch(model, evk, cts)
+    pl = CI.make_plan(oc, sc.N, sc.L, encrypted_model=enc, n1_R=n1[0], n1_L=n1[1])
+    okeys = sc.keygen(kseed, rotations=pl.rotations())
+    omodel = CI.encrypt_model(sc, okeys, pl, kseed) if enc else CI.encode_model(sc, pl)
+    _, trees = F.parse_forest(text)
+    for g in range(groups):
+        got = ctx.export(res[g])[0]
+        if g < oracle_groups:
+            X = CI.encrypt_queries(sc, okeys, pl, qs[g], kseed, g)
+            same(got, CI.Evaluator(sc, okeys, pl).run(X, omodel)["result"])
+        alone = ctx.export(ctx.evaluate(model, evk, cts[g]))[0]
+        assert all((a == b).all() for a, b in zip(got["polys"], alone["polys"])), f"group {g}"
+        labels = ctx.decrypt_labels(keys, meta, res[g], len(qs[g]))
+        assert (labels == np.array([F.evaluate(trees, list(x)) for x in qs[g]])).all()
+
+
+# just below 2^42, 2^44 and 2^46 the transforms leave out reductions that the next size up needs
+@pytest.mark.parametrize("bits", [(42, 42, 44), (43, 44, 44), (44, 46, 46), (46, 47, 48), (48, 49, 49)])
+@pytest.mark.parametrize("enc", [False, True])
+def test_lazy_reductions_by_prime_size(C, bits, enc):
+    evaluate_groups(C, synth.ForestShape(3, 4, 0.7, 3, 4, 3), 71, 13, bits, 3, enc, 2)
+
+
+@pytest.mark.parametrize("log_n,t,bits", [(12, T, 42), (12, T, 44), (13, T, 44), (13, T, 46), (15, T, 42), (15, T, 49),
+                                          (16, 5767169, 44), (16, 5767169, 46), (17, 5767169, 44)])
+def test_transform_extremes(C, log_n, t, bits):
+    """Products of the largest residues (the sums of the inverse transform's first stages as large as they
+    get) and of alternating ones through the two-pass transform."""
+    ctx = C.Context(log_n, 2, 1 << 48, 1 << bits, 1, 1 << 49, t=t)
+    rng = np.random.default_rng(log_n)
+    for i, q in enumerate(ctx.primes()):
+        psi = nt.root_of_unity(2 * ctx.N, q)
+        top = np.full(ctx.N, q - 1, dtype=np.uint64)
+        alt = np.where(np.arange(ctx.N) % 2 == 0, q - 1, q // 2).astype(np.uint64)
+        rnd = rng.integers(0, q, ctx.N, dtype=np.uint64)
+        for a, b in ((top, top), (alt, top), (rnd, alt)):
+            want = B.ntt_inv(B.mulmod_vec(B.ntt_fwd(a, q, psi), B.ntt_fwd(b, q, psi), q), q, psi)
+            assert (ctx.poly_mul(i, a, b) == want).all(), (log_n, i, q)
