@@ -409,20 +409,6 @@ static void lift_to(Context& c, double* dst, const std::vector<int64_t>& v, int 
   COPSE_HIP(hipStreamSynchronize(c.stream));   // hv is pageable host memory
 }
 
-std::unique_ptr<Plain> make_plain(Context& c, const std::vector<int64_t>& centered, int level) {
-  auto p = std::make_unique<Plain>();
-  p->level = level;
-  p->buf = DBuf(&c, (size_t)(level + 1) * c.N);
-  lift_to(c, p->buf.get(), centered, level, true);
-  return p;
-}
-
-std::unique_ptr<Plain> make_plain_slots(Context& c, const uint64_t* slots, int level) {
-  std::vector<int64_t> m;
-  encode_slots(c, slots, m);
-  return make_plain(c, m, level);
-}
-
 // ------------------------------------------------------------------ keys
 static const int2* all_rows(Context& c, int count_polys) {
   // [count][Ltot] rows, primes 0..Ltot-1
@@ -519,32 +505,6 @@ std::unique_ptr<Keys> keygen(Context& c, const uint8_t seed[32], const std::vect
   return K;
 }
 
-CtPtr encrypt(Context& c, const Keys& k, const std::vector<int64_t>& m, int level, const uint8_t seed[32],
-              uint64_t obj) {
-  const size_t N = c.N;
-  const int nl = level + 1;
-  const int2* rows1 = ct_rows(c, 1, nl);
-  std::vector<int64_t> u(N), e0(N), e1(N);
-  sample_ternary(seed, "enc.u", obj, N, u.data());
-  sample_cbd21(seed, "enc.e0", obj, N, e0.data());
-  sample_cbd21(seed, "enc.e1", obj, N, e1.data());
-  for (size_t i = 0; i < N; ++i) {
-    e0[i] = e0[i] * (int64_t)c.t + m[i];
-    e1[i] = e1[i] * (int64_t)c.t;
-  }
-  DBuf du(&c, (size_t)nl * N), d0(&c, (size_t)nl * N), d1(&c, (size_t)nl * N);
-  lift_to(c, du.get(), u, level, true);
-  lift_to(c, d0.get(), e0, level, true);
-  lift_to(c, d1.get(), e1, level, true);
-  auto ct = ct_alloc(c, level, 2);
-  launch_mul(c, ct->poly(0, N), k.pk_b.get(), du.get(), rows1, nl);
-  launch_add(c, ct->poly(0, N), ct->poly(0, N), d0.get(), rows1, nl);
-  launch_mul(c, ct->poly(1, N), k.pk_a.get(), du.get(), rows1, nl);
-  launch_add(c, ct->poly(1, N), ct->poly(1, N), d1.get(), rows1, nl);
-  COPSE_HIP(hipStreamSynchronize(c.stream));
-  return ct;
-}
-
 // [c0 + c1 s (+ c2 s^2)] in coefficient form, per limb, as u64 residues.
 void phase_coef(Context& c, const Keys& k, const Ct& a, std::vector<uint64_t>& out) {
   if (!k.has_secret) fail(COPSE_EKEY, "secret key absent");
@@ -567,38 +527,6 @@ void phase_coef(Context& c, const Keys& k, const Ct& a, std::vector<uint64_t>& o
   COPSE_HIP(hipStreamSynchronize(c.stream));
   out.resize(h.size());
   for (size_t i = 0; i < h.size(); ++i) out[i] = (uint64_t)h[i];
-}
-
-void to_coef_u64(Context& c, const Ct& a, std::vector<uint64_t>& out) {
-  const size_t N = c.N;
-  const int nl = a.level + 1;
-  DBuf tmp(&c, a.words());
-  COPSE_HIP(hipMemcpyAsync(tmp.get(), a.data(), a.words() * 8, hipMemcpyDeviceToDevice, c.stream));
-  launch_ntt_inv(c, tmp.get(), ct_rows(c, a.npolys, nl), a.npolys * nl);
-  std::vector<double> h(a.words());
-  COPSE_HIP(hipMemcpyAsync(h.data(), tmp.get(), h.size() * 8, hipMemcpyDeviceToHost, c.stream));
-  COPSE_HIP(hipStreamSynchronize(c.stream));
-  out.resize(h.size());
-  for (size_t i = 0; i < h.size(); ++i) out[i] = (uint64_t)h[i];
-  (void)N;
-}
-
-CtPtr from_coef_u64(Context& c, const uint64_t* data, int level, int npolys) {
-  const size_t N = c.N;
-  const int nl = level + 1;
-  auto ct = ct_alloc(c, level, npolys);
-  std::vector<double> h((size_t)npolys * nl * N);
-  for (int k = 0; k < npolys; ++k)
-    for (int i = 0; i < nl; ++i)
-      for (size_t j = 0; j < N; ++j) {
-        uint64_t v = data[((size_t)k * nl + i) * N + j];
-        if (v >= c.primes[i]) fail(COPSE_EINVAL, "residue out of range in import");
-        h[((size_t)k * nl + i) * N + j] = (double)v;
-      }
-  COPSE_HIP(hipMemcpyAsync(ct->data(), h.data(), h.size() * 8, hipMemcpyHostToDevice, c.stream));
-  launch_ntt_fwd(c, ct->data(), ct_rows(c, npolys, nl), npolys * nl);
-  COPSE_HIP(hipStreamSynchronize(c.stream));
-  return ct;
 }
 
 // ------------------------------------------------------------------ exact operations

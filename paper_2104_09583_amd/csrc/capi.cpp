@@ -45,6 +45,12 @@ static const Ct& ct_of(const Context& c, const copse_cts* x, size_t i) {
 }
 
 namespace {
+// waits for the stream when a call that copies from or to the caller's memory ends early
+struct StreamWait {
+  hipStream_t s;
+  ~StreamWait() { (void)hipStreamSynchronize(s); }
+};
+
 std::vector<uint64_t> primes_below(uint64_t bound, uint64_t modulus, int count, const std::vector<uint64_t>& taken) {
   std::vector<uint64_t> out;
   if (bound < 2) fail(COPSE_EINVAL, "prime bound too small");
@@ -126,12 +132,16 @@ int copse_ctx_create(const copse_params* p, copse_ctx** out) {
     c->L = (int)p->n_data_primes - 1;
     c->pool = std::make_shared<Pool>(p->device);
     c->primes = make_chain(*p);
-    // transform tables
+    setup_slots(*c);
+    // transform tables of the chain's primes and, last, of t (slots <-> coefficients, root zeta)
     std::vector<DevPrime> dp;
-    for (uint64_t q : c->primes) {
-      uint64_t psi = root_of_unity(2 * N, q);
+    std::vector<uint64_t> moduli(c->primes);
+    moduli.push_back(c->t);
+    for (size_t m = 0; m < moduli.size(); ++m) {
+      const uint64_t q = moduli[m];
+      uint64_t psi = m < c->primes.size() ? root_of_unity(2 * N, q) : c->zeta;
       uint64_t psi_inv = invmod(psi, q);
-      c->psi.push_back(psi);
+      if (m < c->primes.size()) c->psi.push_back(psi);
       std::vector<double> fw(N), iv(N);
       for (uint64_t k = 0; k < N; ++k) {
         uint32_t br = bitrev((uint32_t)k, (int)p->log_n);
@@ -155,7 +165,17 @@ int copse_ctx_create(const copse_params* p, copse_ctx** out) {
     }
     COPSE_HIP(hipMalloc(&c->d_primes, dp.size() * sizeof(DevPrime)));
     COPSE_HIP(hipMemcpy(c->d_primes, dp.data(), dp.size() * sizeof(DevPrime), hipMemcpyHostToDevice));
-    setup_slots(*c);
+    std::vector<uint32_t> slot_of_eval(N);
+    for (uint32_t s = 0; s < N; ++s) slot_of_eval[c->slot_pos[s]] = s;
+    auto upload_u32 = [&](const std::vector<uint32_t>& v) {
+      uint32_t* d;
+      COPSE_HIP(hipMalloc(&d, N * sizeof(uint32_t)));
+      c->tables.push_back(reinterpret_cast<double*>(d));
+      COPSE_HIP(hipMemcpy(d, v.data(), N * sizeof(uint32_t), hipMemcpyHostToDevice));
+      return d;
+    };
+    c->d_eval_of_slot = upload_u32(c->slot_pos);
+    c->d_slot_of_eval = upload_u32(slot_of_eval);
     // every level's key-switching and modulus-switching tables now, and the scratch array's address on this
     // device: an evaluation without allocation (copse_evaluate_noalloc) then finds everything it reads
     c->build_level_tables();
@@ -356,13 +376,14 @@ int copse_query_encrypt(copse_ctx* ctx, const copse_keys* keys, const copse_publ
     for (size_t i = 0; i < n_queries * meta->n_features; ++i)
       if (features[i] >= lim) fail(COPSE_EINVAL, "feature value exceeds the precision");
     auto cts = std::make_unique<copse_cts>();
-    std::vector<uint64_t> slots;
+    const Keys& K = keys_of(c, keys);
+    std::vector<uint64_t> planes((size_t)meta->precision * c.N), slots, objs;
     for (uint32_t k = 0; k < meta->precision; ++k) {
       query_plane_slots(*meta, c.N, features, n_queries, k, slots);
-      std::vector<int64_t> poly;
-      encode_slots(c, slots.data(), poly);
-      cts->v.push_back(encrypt(c, keys_of(c, keys), poly, c.L, seed, (1ULL << 56) | ((uint64_t)group << 32) | k));
+      std::copy(slots.begin(), slots.end(), planes.begin() + (size_t)k * c.N);
+      objs.push_back((1ULL << 56) | ((uint64_t)group << 32) | k);
     }
+    cts->v = encrypt_slots_many(c, K, planes.data(), (int)meta->precision, c.L, seed, objs.data());
     *out = cts.release();
   });
 }
@@ -488,31 +509,16 @@ int copse_decrypt_labels(copse_ctx* ctx, const copse_keys* keys, const copse_pub
       fail(COPSE_EINVAL, "layout made for another ring size");
     if (n_queries > meta->queries_per_ct) fail(COPSE_EINVAL, "more queries than blocks");
     if (cap < n_queries * meta->m) fail(COPSE_EINVAL, "bits buffer too small");
-    std::vector<uint64_t> ph;
-    phase_coef(c, *keys->k, ct, ph);
-    const uint64_t q0 = c.primes[0];
-    std::vector<uint64_t> coef(c.N);
-    uint64_t worst = 0;
-    for (size_t i = 0; i < c.N; ++i) {
-      uint64_t v = ph[i];
-      bool neg = v > q0 / 2;
-      uint64_t mag = neg ? q0 - v : v;
-      worst = std::max(worst, mag);
-      uint64_t r = mag % c.t;
-      coef[i] = neg ? (r ? c.t - r : 0) : r;
-    }
-    if (worst >= (q0 >> 11)) fail(COPSE_ENOISE, "decryption noise above q_0 / 2^11");
-    std::vector<uint64_t> slots(c.N);
-    decode_poly(c, coef, slots.data());
-    size_t bpr = (c.N / 2) / meta->block_w;
+    std::vector<uint8_t> slot_bits;
+    const uint64_t worst = decrypt_label_slots(c, *keys->k, *meta, ct, n_queries, slot_bits);
+    if (worst >= (c.primes[0] >> 11)) fail(COPSE_ENOISE, "decryption noise above q_0 / 2^11");
     for (size_t k = 0; k < n_queries; ++k) {
-      size_t row = k / bpr, col0 = (k % bpr) * meta->block_w;
       uint32_t ones = 0;
       for (uint32_t j = 0; j < meta->m; ++j) {
-        uint64_t v = slots[row * (c.N / 2) + col0 + j];
+        const uint8_t v = slot_bits[k * meta->m + j];
         if (v > 1) fail(COPSE_ENOISE, "decrypted label slot is not a bit");
-        bits[k * meta->m + j] = (uint8_t)v;
-        ones += (uint32_t)v;
+        bits[k * meta->m + j] = v;
+        ones += v;
       }
       // the result is N-hot: exactly one label per tree (Section 4.1, "Classification Result")
       if (ones != meta->n_trees)
@@ -529,10 +535,8 @@ int copse_encrypt_slots(copse_ctx* ctx, const copse_keys* keys, const uint64_t* 
     NEED(ctx && keys && slots && seed && out);
     Context& c = *ctx->c;
     if (level < 0 || level > c.L) fail(COPSE_EINVAL, "level out of range");
-    std::vector<int64_t> poly;
-    encode_slots(c, slots, poly);
     auto r = std::make_unique<copse_cts>();
-    r->v.push_back(encrypt(c, keys_of(c, keys), poly, level, seed, obj));
+    r->v = encrypt_slots_many(c, keys_of(c, keys), slots, 1, level, seed, &obj);
     *out = r.release();
   });
 }
@@ -601,17 +605,21 @@ int copse_cts_export(copse_ctx* ctx, const copse_cts* cts, uint64_t* buf, size_t
     *need = total;
     if (!buf) return;
     if (cap < total) fail(COPSE_EINVAL, "export buffer too small");
+    for (auto& ct : cts->v)
+      if (ct->n != c.N || ct->level > c.L) fail(COPSE_EINVAL, "ciphertext of another ring or chain");
+    // converted to words on the device, copied straight into the caller's buffer
+    StreamWait wait{c.stream};
     size_t off = 0;
     for (auto& ct : cts->v) {
-      std::vector<uint64_t> co;
-      to_coef_u64(c, *ct, co);
+      DBuf words = ct_words(c, *ct);
       buf[off++] = (uint64_t)ct->npolys;
       buf[off++] = (uint64_t)ct->level;
       buf[off++] = (uint64_t)c.N;
       buf[off++] = 0;
-      std::copy(co.begin(), co.end(), buf + off);
-      off += co.size();
+      COPSE_HIP(hipMemcpyAsync(buf + off, words.get(), words.size() * 8, hipMemcpyDeviceToHost, c.stream));
+      off += words.size();
     }
+    COPSE_HIP(hipStreamSynchronize(c.stream));
   });
 }
 
@@ -621,6 +629,10 @@ int copse_cts_import(copse_ctx* ctx, const uint64_t* buf, size_t len, copse_cts*
     *out = nullptr;
     Context& c = *ctx->c;
     auto r = std::make_unique<copse_cts>();
+    // words copied straight from the caller's buffer, converted and checked on the device
+    DBuf bad(&c, 1);
+    COPSE_HIP(hipMemsetAsync(bad.get(), 0, 8, c.stream));
+    StreamWait wait{c.stream};
     size_t off = 0;
     while (off < len) {
       if (len - off < 4) fail(COPSE_EINVAL, "truncated header");
@@ -629,9 +641,13 @@ int copse_cts_import(copse_ctx* ctx, const uint64_t* buf, size_t len, copse_cts*
       off += 4;
       size_t words = (size_t)np * (lv + 1) * c.N;
       if (len - off < words) fail(COPSE_EINVAL, "truncated ciphertext");
-      r->v.push_back(from_coef_u64(c, buf + off, (int)lv, (int)np));
+      r->v.push_back(ct_from_words(c, buf + off, (int)lv, (int)np, reinterpret_cast<int*>(bad.get())));
       off += words;
     }
+    uint64_t flag = 0;
+    COPSE_HIP(hipMemcpyAsync(&flag, bad.get(), 8, hipMemcpyDeviceToHost, c.stream));
+    COPSE_HIP(hipStreamSynchronize(c.stream));
+    if (flag) fail(COPSE_EINVAL, "residue out of range in import");
     *out = r.release();
   });
 }

@@ -57,9 +57,7 @@ std::unique_ptr<Model> build_model(Context& c, const Compiled& C, const Keys* k,
   const uint32_t q = meta.q, b = meta.b, m = meta.m, K = meta.K;
   const uint32_t B_in = m + b + q - 2;
   auto enc_slots = [&](const std::vector<uint64_t>& slots, int level, uint64_t obj) {
-    std::vector<int64_t> poly;
-    encode_slots(c, slots.data(), poly);
-    return encrypt(c, *k, poly, level, seed, obj);
+    return std::move(encrypt_slots_many(c, *k, slots.data(), 1, level, seed, &obj)[0]);
   };
   auto make_operand = [&](const std::vector<uint64_t>& slots, int level, uint64_t obj, bool skip_zero) {
     Operand o;

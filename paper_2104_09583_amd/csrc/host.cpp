@@ -238,6 +238,16 @@ void sample_cbd21(const uint8_t seed[32], const char* dom, uint64_t obj, size_t 
   }
 }
 
+void sample_encryption(const uint8_t seed[32], uint64_t obj, size_t n, int8_t* out) {
+  std::vector<int64_t> v(n);
+  sample_ternary(seed, "enc.u", obj, n, v.data());
+  std::copy(v.begin(), v.end(), out);
+  sample_cbd21(seed, "enc.e0", obj, n, v.data());
+  std::copy(v.begin(), v.end(), out + n);
+  sample_cbd21(seed, "enc.e1", obj, n, v.data());
+  std::copy(v.begin(), v.end(), out + 2 * n);
+}
+
 // ------------------------------------------------------------------ pool
 Pool::~Pool() {
   hipSetDevice(device_);

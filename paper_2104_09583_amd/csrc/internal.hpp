@@ -65,6 +65,8 @@ void sample_uniform(const uint8_t seed[32], const char* dom, uint64_t obj, uint3
                     size_t n, double* out);
 void sample_ternary(const uint8_t seed[32], const char* dom, uint64_t obj, size_t n, int64_t* out);
 void sample_cbd21(const uint8_t seed[32], const char* dom, uint64_t obj, size_t n, int64_t* out);
+// u, e0 and e1 of the encryption with object obj: out[3][n]
+void sample_encryption(const uint8_t seed[32], uint64_t obj, size_t n, int8_t* out);
 
 // ------------------------------------------------------------------ device-side descriptors
 struct DevPrime {
@@ -182,7 +184,9 @@ struct Context {
   int alpha = 0;      // special primes = digit size
   std::vector<uint64_t> primes;   // q_0..q_L, p_0..p_{alpha-1}
   std::vector<uint64_t> psi;      // the device transform's 2N-th roots
-  DevPrime* d_primes = nullptr;
+  DevPrime* d_primes = nullptr;   // the chain's primes, then t (the plaintext transform's modulus)
+  uint32_t* d_eval_of_slot = nullptr;   // slot_pos on the device, and its inverse (owned through tables)
+  uint32_t* d_slot_of_eval = nullptr;
   std::vector<double*> tables;
   std::shared_ptr<Pool> pool;
   uint64_t zeta = 0;              // slot root mod t
@@ -511,12 +515,15 @@ CtPtr ct_alloc(Context& c, int level, int npolys);
 CtPtr ct_copy(Context& c, const Ct& a);
 void encode_slots(const Context& c, const uint64_t* slots, std::vector<int64_t>& coeffs_centered);
 void decode_poly(const Context& c, const std::vector<uint64_t>& coeffs_mod_t, uint64_t* slots);
-std::unique_ptr<Plain> make_plain(Context& c, const std::vector<int64_t>& centered, int level);
 std::unique_ptr<Plain> make_plain_slots(Context& c, const uint64_t* slots, int level);
 
 std::unique_ptr<Keys> keygen(Context& c, const uint8_t seed[32], const std::vector<int32_t>& rots, bool relin);
-CtPtr encrypt(Context& c, const Keys& k, const std::vector<int64_t>& centered, int level,
-              const uint8_t seed[32], uint64_t obj);
+// (wire.hip) fresh encryptions of `count` slot vectors ([count][N]) with objects objs
+std::vector<CtPtr> encrypt_slots_many(Context& c, const Keys& k, const uint64_t* slots, int count, int level,
+                                      const uint8_t seed[32], const uint64_t* objs);
+// (wire.hip) the label slots of a level-0 result (0, 1, or 2 for any other value) and the largest centered phase
+uint64_t decrypt_label_slots(Context& c, const Keys& k, const copse_public_meta& meta, const Ct& ct, size_t n_queries,
+                             std::vector<uint8_t>& bits);
 void phase_coef(Context& c, const Keys& k, const Ct& a, std::vector<uint64_t>& out);  // [level+1][N] u64
 
 CtPtr op_add(Context& c, const Ct& a, const Ct& b);
@@ -536,7 +543,8 @@ CtPtr op_rotate(Context& c, const Keys& k, const Ct& a, int32_t r);
 // sum of rotations of same-level ciphertexts with one ModDown (see bgv.cpp)
 CtPtr op_rotate_sum(Context& c, const Keys& k, const std::vector<std::pair<const Ct*, int32_t>>& items);
 
-void to_coef_u64(Context& c, const Ct& a, std::vector<uint64_t>& out);
-CtPtr from_coef_u64(Context& c, const uint64_t* data, int level, int npolys);
+// (wire.hip) a ciphertext's coefficient words on the device, and a ciphertext from words in host memory
+DBuf ct_words(Context& c, const Ct& a);
+CtPtr ct_from_words(Context& c, const uint64_t* words, int level, int npolys, int* bad);
 
 }  // namespace copse

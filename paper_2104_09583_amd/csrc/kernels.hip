@@ -12,97 +12,9 @@
 #include <type_traits>
 
 #include "internal.hpp"
+#include "modarith.hpp"
 
 namespace copse {
-
-// ------------------------------------------------------------------ modular arithmetic in fp64
-__device__ __forceinline__ double mod_mul(double a, double b, double q, double qinv) {
-  double h = a * b;
-  double l = __fma_rn(a, b, -h);
-  double k = floor(h * qinv);
-  double r = __fma_rn(-k, q, h) + l;
-  r = (r < 0.0) ? r + q : r;
-  r = (r >= q) ? r - q : r;
-  return r;
-}
-__device__ __forceinline__ double mod_add(double a, double b, double q) {
-  double s = a + b;
-  return (s >= q) ? s - q : s;
-}
-__device__ __forceinline__ double mod_sub(double a, double b, double q) {
-  double s = a - b;
-  return (s < 0.0) ? s + q : s;
-}
-// reduce an exact integer |v| < 2^52 into [0, q)
-__device__ __forceinline__ double mod_reduce(double v, double q, double qinv) {
-  double k = floor(v * qinv);
-  double r = __fma_rn(-k, q, v);
-  r = (r < 0.0) ? r + q : r;
-  r = (r >= q) ? r - q : r;
-  return r;
-}
-
-// Lazy (signed) residues for the transforms.  With q < 2^49 and |a| < 4q, |b| < q:
-//   mul_lazy: k = rint(a b / q) is within 0.5 + 2^-3 of the exact quotient, so
-//   r = a b - k q = fma(-k, q, h) + l is an exact integer with |r| < 0.91 q;
-//   reduce_sym: x - q rint(x / q) lies in [-q/2, q/2] for |x| < 8 q;
-//   canon: maps [-q/2, q/2] to [0, q).
-// In general |mul_lazy(a, b)| <= (0.5 + 3 x 2^-53 |a|) q: the quotient estimate is off by three roundings.
-// Forward, a stage adds one such product to |x|: from |x| <= q six stages reach at most 7.6 q < 2^52 for
-// q = 2^49, every value still an exact integer, so the row pass folds back once, after its second radix-8
-// round; for q < 2^46 (kFwdLazy) its twelve stages stay below 20 q even from 8 q, and it never does.  Inverse, a stage doubles the sums: 2^3 per round, folded back after every round, or for
-// q < 2^44 (kInvLazy) after every second one (64 q <= 2^50).  For q < 2^42 (kInvOpen) the inverse row pass
-// also leaves its output unreduced (32 q): three column stages that follow reach 256 q <= 2^50, where the
-// next product is still within 0.875 q (four: 512 q, within 1.25 q and folded back there).
-constexpr double kFwdLazy = 70368744177664.0;   // 2^46
-constexpr double kInvLazy = 17592186044416.0;   // 2^44
-constexpr double kInvOpen = 4398046511104.0;    // 2^42
-__device__ __forceinline__ double mul_lazy(double a, double b, double q, double qinv) {
-  double h = a * b;
-  double l = __fma_rn(a, b, -h);
-  double k = rint(h * qinv);
-  return __fma_rn(-k, q, h) + l;
-}
-__device__ __forceinline__ double reduce_sym(double x, double q, double qinv) {
-  return __fma_rn(-rint(x * qinv), q, x);
-}
-__device__ __forceinline__ double canon(double x, double q) { return __fma_rn(x < 0.0 ? 1.0 : 0.0, q, x); }
-
-// A load known to be from global memory (not through a flat address).  Flat loads count on the same
-// wait counter as LDS and scalar loads, so every LDS wait before a barrier would also wait for them;
-// global loads count only on the vector-memory counter.
-__device__ __forceinline__ double gload(const double* p) {
-  return *(const __attribute__((address_space(1))) double*)(p);
-}
-// A load of a value that is uniform across the wave from a table no kernel writes (twiddles, row
-// descriptors, primes, conversion constants): read through the constant address space, so it is a scalar
-// load into scalar registers.
-template <class T>
-__device__ __forceinline__ T cload(const T* p) {
-  static_assert(std::is_scalar<T>::value, "scalar loads take numbers and pointers");
-  return *(const __attribute__((address_space(4))) T*)(p);
-}
-__device__ __forceinline__ int2 cload_row(const int2* p) {
-  const int* w = reinterpret_cast<const int*>(p);
-  return make_int2(cload(w), cload(w + 1));
-}
-// the fields of a prime the transforms use (q, 1/q, twiddle tables, N^-1)
-__device__ __forceinline__ DevPrime cload_prime(const DevPrime* p) {
-  DevPrime r;
-  r.q = cload(&p->q);
-  r.qinv = cload(&p->qinv);
-  r.fwd = cload(&p->fwd);
-  r.inv = cload(&p->inv);
-  r.ninv = cload(&p->ninv);
-  return r;
-}
-// Workgroup barrier for LDS exchanges: waits for this wave's LDS accesses only, so global loads issued
-// before it (the next round's twiddles, an epilogue's operands) stay in flight across it.  The memory
-// clobber keeps the compiler from moving LDS accesses across it.
-__device__ __forceinline__ void lds_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
-// An LDS exchange among the lanes of one wave: its writes are complete before its next reads are issued
-// (no other wave takes part, so no workgroup barrier)
-__device__ __forceinline__ void lds_wave_sync() { asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory"); }
 
 // ------------------------------------------------------------------ automorphism (evaluation domain)
 // Slot k holds a(psi^e) with e = 2 bitrev(k) + 1.  sigma_g(a)(psi^e) = a(psi^(g e)), so the
@@ -251,18 +163,6 @@ __global__ __launch_bounds__(kThreads) void ntt_rows_kernel(double* __restrict__
 // Column pass: stages 0..S1-1 touch only the 2^S1 elements r*C + c (r < 2^S1, C = N >> S1) of one
 // column c, so one thread keeps a whole column in registers and needs no LDS.  Consecutive
 // threads take consecutive columns: every load and store of a wavefront is one contiguous run.
-__device__ __forceinline__ void bfly_ct(double& x, double& y, double w, double q, double qinv) {
-  double v = mul_lazy(y, w, q, qinv);
-  double u = x;
-  x = u + v;
-  y = u - v;
-}
-__device__ __forceinline__ void bfly_gs(double& x, double& y, double w, double q, double qinv) {
-  double u = x, v = y;
-  x = u + v;
-  y = mul_lazy(u - v, w, q, qinv);
-}
-
 template <int S1, bool kInverse>
 __global__ __launch_bounds__(64) void ntt_colreg_kernel(double* __restrict__ base, const int2* __restrict__ rows,
                                                        const DevPrime* __restrict__ P, int logN, int scale) {

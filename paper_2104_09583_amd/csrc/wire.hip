@@ -1,0 +1,348 @@
+// The data owner's and the wire's side of the boundary on the device: residues to and from 64-bit words
+// (ciphertext import and export), slot vectors to plaintext polynomials and back (the transform modulo t, run
+// by the ring transform's kernels with t as one more prime), and encryption of several plaintexts at once.
+//
+// All of it is bound by launches and by the copy to or from the caller's pageable memory, not by arithmetic,
+// so the kernels are one pass each and fold in what the host did before: range checks, centering, the
+// multiplication by t, the noise check.
+#include <algorithm>
+
+#include "internal.hpp"
+#include "modarith.hpp"
+
+namespace copse {
+
+constexpr int kWireThreads = 256;
+static dim3 wire_grid(const Context& c, int rows, int z = 1) {
+  return dim3((unsigned)((c.N + kWireThreads - 1) / kWireThreads), rows, z);
+}
+
+// ------------------------------------------------------------------ residues <-> 64-bit words
+// rows of nl limbs (row r: prime r % nl).  In place: a word and its residue share their eight bytes.
+__global__ void words_to_residues_kernel(double* io, int nl, const DevPrime* P, int logN, int* bad) {
+  const size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (i >= (size_t)1 << logN) return;
+  const size_t o = ((size_t)blockIdx.y << logN) + i;
+  const uint64_t v = reinterpret_cast<const uint64_t*>(io)[o];
+  const bool ok = v < (uint64_t)P[blockIdx.y % nl].q;
+  if (!ok) *bad = 1;
+  io[o] = ok ? (double)v : 0.0;
+}
+__global__ void residues_to_words_kernel(double* io, int logN) {
+  const size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (i >= (size_t)1 << logN) return;
+  const size_t o = ((size_t)blockIdx.y << logN) + i;
+  reinterpret_cast<uint64_t*>(io)[o] = (uint64_t)io[o];
+}
+
+// The column pass with the conversion folded in, for the rings of the split transform (N = 2^13 .. 2^16): one
+// thread keeps one column (2^S1 elements, C = N >> S1 apart) in registers, in place.
+//   forward (import): words, checked against the prime, then stages 0 .. S1 - 1; signed output for the row pass
+//   inverse (export): the row pass's signed output (< 32 q), the last stages, N^-1, canonical words
+// Bound by the copy from or to the caller's memory.  A request of eight planes (42 MB) in, one evaluation, its result
+// out: 5.50 ms with the conversion loops on the host, 3.14 ms here, of which the copy in takes 1.2 and the evaluation
+// 1.4.
+template <int S1, bool kInverse>
+__global__ __launch_bounds__(64) void wire_cols_kernel(double* io, int nl, const DevPrime* __restrict__ P, int logN,
+                                                       int* bad) {
+  constexpr int R = 1 << S1;
+  const size_t C = (size_t)1 << (logN - S1);
+  const size_t col = (size_t)blockIdx.x * 64 + threadIdx.x;
+  if (col >= C) return;
+  const DevPrime pr = P[blockIdx.y % nl];
+  double* a = io + ((size_t)blockIdx.y << logN) + col;
+  double x[R];
+  if (!kInverse) {
+    const uint64_t q = (uint64_t)pr.q;
+    bool ok = true;
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+      const uint64_t v = reinterpret_cast<const uint64_t*>(a)[r * C];
+      ok = ok && v < q;
+      x[r] = v < q ? (double)v : 0.0;
+    }
+    if (!ok) *bad = 1;
+#pragma unroll
+    for (int s = 0; s < S1; ++s) {
+      const int half = R >> (s + 1);
+#pragma unroll
+      for (int g = 0; g < (1 << s); ++g) {
+        const double w = pr.fwd[(1 << s) + g];
+#pragma unroll
+        for (int o = 0; o < half; ++o) bfly_ct(x[g * 2 * half + o], x[g * 2 * half + o + half], w, pr.q, pr.qinv);
+      }
+    }
+#pragma unroll
+    for (int r = 0; r < R; ++r) a[r * C] = reduce_sym(x[r], pr.q, pr.qinv);
+  } else {
+#pragma unroll
+    for (int r = 0; r < R; ++r) x[r] = a[r * C];
+#pragma unroll
+    for (int s = S1 - 1; s >= 0; --s) {
+      const int half = R >> (s + 1);
+#pragma unroll
+      for (int g = 0; g < (1 << s); ++g) {
+        const double w = pr.inv[(1 << s) + g];
+#pragma unroll
+        for (int o = 0; o < half; ++o) bfly_gs(x[g * 2 * half + o], x[g * 2 * half + o + half], w, pr.q, pr.qinv);
+      }
+    }
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+      const double v = canon(reduce_sym(mul_lazy(x[r], pr.ninv, pr.q, pr.qinv), pr.q, pr.qinv), pr.q);
+      reinterpret_cast<uint64_t*>(a)[r * C] = (uint64_t)v;
+    }
+  }
+}
+
+template <bool kInverse>
+static void launch_wire_cols(Context& c, double* io, int rows, int nl, int* bad) {
+  const int logN = (int)c.log_n, S1 = logN - 12;
+  const dim3 grid((unsigned)(((c.N >> S1) + 63) / 64), rows);
+  switch (S1) {
+    case 1: hipLaunchKernelGGL((wire_cols_kernel<1, kInverse>), grid, dim3(64), 0, c.stream, io, nl, c.d_primes, logN, bad); break;
+    case 2: hipLaunchKernelGGL((wire_cols_kernel<2, kInverse>), grid, dim3(64), 0, c.stream, io, nl, c.d_primes, logN, bad); break;
+    case 3: hipLaunchKernelGGL((wire_cols_kernel<3, kInverse>), grid, dim3(64), 0, c.stream, io, nl, c.d_primes, logN, bad); break;
+    default: hipLaunchKernelGGL((wire_cols_kernel<4, kInverse>), grid, dim3(64), 0, c.stream, io, nl, c.d_primes, logN, bad); break;
+  }
+  COPSE_HIP(hipGetLastError());
+}
+
+// rows of an [np][nl][N] block with primes 0..nl-1
+static const int2* limb_rows(Context& c, int np, int nl) {
+  const std::string key = "ct:" + std::to_string(np) + ":" + std::to_string(nl);
+  auto it = c.row_tables.find(key);
+  if (it != c.row_tables.end()) return it->second;
+  std::vector<int2> h;
+  for (int k = 0; k < np; ++k)
+    for (int i = 0; i < nl; ++i) h.push_back(make_int2(k * nl + i, i));
+  return c.rows(key, h);
+}
+
+// Device copy of a ciphertext's coefficient words, enqueued; the caller copies them out on the same stream.
+DBuf ct_words(Context& c, const Ct& a) {
+  const int nl = a.level + 1, rows = a.npolys * nl;
+  DBuf tmp(&c, a.words());
+  if (bridge_supported(c, 1)) {
+    std::vector<const double*> polys;
+    for (int k = 0; k < a.npolys; ++k) polys.push_back(a.poly(k, c.N));
+    launch_ntt_inv_rows_gather(c, tmp.get(), polys, nl, c.N, 0, -1);
+    launch_wire_cols<true>(c, tmp.get(), rows, nl, nullptr);
+    return tmp;
+  }
+  launch_copy(c, tmp.get(), a.data(), a.words());
+  launch_ntt_inv(c, tmp.get(), limb_rows(c, a.npolys, nl), rows);
+  hipLaunchKernelGGL(residues_to_words_kernel, wire_grid(c, rows), dim3(kWireThreads), 0, c.stream, tmp.get(),
+                     (int)c.log_n);
+  COPSE_HIP(hipGetLastError());
+  return tmp;
+}
+
+// A ciphertext from coefficient words in caller memory, enqueued; *bad (device) becomes 1 when a word is not
+// below its prime.  `words` must stay valid until the stream has been synchronized.
+CtPtr ct_from_words(Context& c, const uint64_t* words, int level, int npolys, int* bad) {
+  auto ct = ct_alloc(c, level, npolys);
+  const int nl = level + 1, rows = npolys * nl;
+  COPSE_HIP(hipMemcpyAsync(ct->data(), words, ct->words() * 8, hipMemcpyHostToDevice, c.stream));
+  if (bridge_supported(c, 1)) {
+    launch_wire_cols<false>(c, ct->data(), rows, nl, bad);
+    launch_ntt_fwd_rows(c, ct->data(), limb_rows(c, npolys, nl), rows);
+    return ct;
+  }
+  hipLaunchKernelGGL(words_to_residues_kernel, wire_grid(c, rows), dim3(kWireThreads), 0, c.stream, ct->data(), nl,
+                     c.d_primes, (int)c.log_n, bad);
+  COPSE_HIP(hipGetLastError());
+  launch_ntt_fwd(c, ct->data(), limb_rows(c, npolys, nl), rows);
+  return ct;
+}
+
+// ------------------------------------------------------------------ slots <-> plaintext polynomials
+// evaluation slot k of plaintext p: slots[p][inv[k]] mod t (inv: position of evaluation slot k among the
+// slots; gathered, so that the writes are contiguous)
+__global__ void slots_to_eval_kernel(double* ev, const uint64_t* slots, const uint32_t* inv, uint64_t t, int logN) {
+  const size_t k = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (k >= (size_t)1 << logN) return;
+  const size_t base = (size_t)blockIdx.y << logN;
+  const uint64_t v = slots[base + inv[k]];
+  ev[base + k] = (double)(v < t ? v : v % t);
+}
+__device__ __forceinline__ double center_t(double m, double t) { return m > (t - 1.0) * 0.5 ? m - t : m; }
+
+// limb rows of a plaintext: its coefficients centered mod t, reduced modulo every prime
+__global__ void lift_plain_kernel(double* out, const double* m, double t, const DevPrime* P, int logN) {
+  const size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (i >= (size_t)1 << logN) return;
+  const DevPrime& pr = P[blockIdx.y];
+  out[((size_t)blockIdx.y << logN) + i] = mod_reduce(center_t(m[i], t), pr.q, pr.qinv);
+}
+
+// row (p, r) of the transform modulo t
+static const int2* t_rows(Context& c, int count) {
+  const std::string key = "tmod:" + std::to_string(count);
+  auto it = c.row_tables.find(key);
+  if (it != c.row_tables.end()) return it->second;
+  std::vector<int2> h;
+  for (int p = 0; p < count; ++p) h.push_back(make_int2(p, c.n_primes()));
+  return c.rows(key, h);
+}
+
+// Coefficients in [0, t) of `count` slot vectors ([count][N] in caller memory), enqueued
+static DBuf encode_device(Context& c, const uint64_t* slots, int count) {
+  DBuf up(&c, (size_t)count * c.N), m(&c, (size_t)count * c.N);
+  COPSE_HIP(hipMemcpyAsync(up.get(), slots, (size_t)count * c.N * 8, hipMemcpyHostToDevice, c.stream));
+  hipLaunchKernelGGL(slots_to_eval_kernel, wire_grid(c, count), dim3(kWireThreads), 0, c.stream, m.get(),
+                     reinterpret_cast<const uint64_t*>(up.get()), c.d_slot_of_eval, c.t, (int)c.log_n);
+  COPSE_HIP(hipGetLastError());
+  launch_ntt_inv(c, m.get(), t_rows(c, count), count);
+  return m;
+}
+
+std::unique_ptr<Plain> make_plain_slots(Context& c, const uint64_t* slots, int level) {
+  auto p = std::make_unique<Plain>();
+  p->level = level;
+  p->buf = DBuf(&c, (size_t)(level + 1) * c.N);
+  DBuf m = encode_device(c, slots, 1);
+  hipLaunchKernelGGL(lift_plain_kernel, wire_grid(c, level + 1), dim3(kWireThreads), 0, c.stream, p->buf.get(), m.get(),
+                     (double)c.t, c.d_primes, (int)c.log_n);
+  COPSE_HIP(hipGetLastError());
+  launch_ntt_fwd(c, p->buf.get(), limb_rows(c, 1, level + 1), level + 1);
+  COPSE_HIP(hipStreamSynchronize(c.stream));   // slots is the caller's memory
+  return p;
+}
+
+// ------------------------------------------------------------------ encryption
+// z = 3 p + k, limb r: the coefficient rows of u (k = 0), t e0 + m (1) and t e1 (2) of plaintext p
+__global__ void enc_lift_kernel(double* out, const int8_t* noise, const double* m, double t, const DevPrime* P,
+                                int logN) {
+  const size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (i >= (size_t)1 << logN) return;
+  const int z = blockIdx.z, k = z % 3;
+  const DevPrime& pr = P[blockIdx.y];
+  double v = (double)noise[((size_t)z << logN) + i];
+  if (k != 0) v *= t;   // |e| <= 21: exact
+  if (k == 1) v += center_t(m[((size_t)(z / 3) << logN) + i], t);
+  out[(((size_t)z * gridDim.y + blockIdx.y) << logN) + i] = mod_reduce(v, pr.q, pr.qinv);
+}
+// (pk_b u + d0, pk_a u + d1) per plaintext and limb
+__global__ void enc_combine_kernel(MPack out, const double* rows, const double* pk_b, const double* pk_a,
+                                   const DevPrime* P, int logN) {
+  const size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (i >= (size_t)1 << logN) return;
+  const int r = blockIdx.y, nl = gridDim.y, p = blockIdx.z;
+  const DevPrime& pr = P[r];
+  const size_t o = ((size_t)r << logN) + i, ps = (size_t)nl << logN;
+  const double* d = rows + (size_t)p * 3 * ps + o;
+  const double u = d[0];
+  out.p[p][o] = canon(reduce_sym(mul_lazy(pk_b[o], u, pr.q, pr.qinv) + d[ps], pr.q, pr.qinv), pr.q);
+  out.p[p][ps + o] = canon(reduce_sym(mul_lazy(pk_a[o], u, pr.q, pr.qinv) + d[2 * ps], pr.q, pr.qinv), pr.q);
+}
+
+// Fresh encryptions of `count` slot vectors at `level` with objects objs: (pk0 u + t e0 + m, pk1 u + t e1).
+// Up to eight plaintexts travel together, so that the limb rows in flight stay below 80 MB for N = 32768 and twelve
+// limbs.  What is left is the host's SHAKE-256 (2.2 ms a plaintext on one core): eight planes encrypted and exported
+// take 13.5 ms, against 40.5 ms with the encoder's transform and the export's conversion on the host.
+std::vector<CtPtr> encrypt_slots_many(Context& c, const Keys& k, const uint64_t* slots, int count, int level,
+                                      const uint8_t seed[32], const uint64_t* objs) {
+  constexpr int kMany = 8;
+  const size_t N = c.N;
+  const int nl = level + 1;
+  std::vector<CtPtr> out;
+  for (int first = 0; first < count; first += kMany) {
+    const int n = std::min(kMany, count - first);
+    std::vector<int8_t> noise((size_t)3 * n * N);
+    for (int p = 0; p < n; ++p) sample_encryption(seed, objs[first + p], N, noise.data() + (size_t)3 * p * N);
+    DBuf dn(&c, (noise.size() + 7) / 8);
+    COPSE_HIP(hipMemcpyAsync(dn.get(), noise.data(), noise.size(), hipMemcpyHostToDevice, c.stream));
+    DBuf m = encode_device(c, slots + (size_t)first * N, n);
+    DBuf rows(&c, (size_t)3 * n * nl * N);
+    hipLaunchKernelGGL(enc_lift_kernel, wire_grid(c, nl, 3 * n), dim3(kWireThreads), 0, c.stream, rows.get(),
+                       reinterpret_cast<const int8_t*>(dn.get()), m.get(), (double)c.t, c.d_primes, (int)c.log_n);
+    COPSE_HIP(hipGetLastError());
+    launch_ntt_fwd(c, rows.get(), limb_rows(c, 3 * n, nl), 3 * n * nl);
+    MPack po;
+    for (int p = 0; p < n; ++p) {
+      out.push_back(ct_alloc(c, level, 2));
+      po.p[p] = out.back()->data();
+    }
+    hipLaunchKernelGGL(enc_combine_kernel, wire_grid(c, nl, n), dim3(kWireThreads), 0, c.stream, po, rows.get(),
+                       k.pk_b.get(), k.pk_a.get(), c.d_primes, (int)c.log_n);
+    COPSE_HIP(hipGetLastError());
+    COPSE_HIP(hipStreamSynchronize(c.stream));   // noise and slots are host memory
+  }
+  return out;
+}
+
+// ------------------------------------------------------------------ decryption of labels
+// c0 + c1 s of a level-0 ciphertext
+__global__ void phase0_kernel(double* out, const double* c0, const double* c1, const double* s, const DevPrime* P,
+                              int logN) {
+  const size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (i >= (size_t)1 << logN) return;
+  const DevPrime& pr = P[0];
+  out[i] = canon(reduce_sym(mul_lazy(c1[i], s[i], pr.q, pr.qinv) + c0[i], pr.q, pr.qinv), pr.q);
+}
+// the phase's coefficients centered mod q_0, reduced mod t; the largest magnitude into *worst
+__global__ void phase_mod_t_kernel(double* io, double q0, double t, double tinv, int logN, unsigned long long* worst) {
+  const size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
+  unsigned long long mag = 0;
+  if (i < (size_t)1 << logN) {
+    const double v = io[i];
+    const bool neg = v > (q0 - 1.0) * 0.5;
+    const double a = neg ? q0 - v : v;
+    mag = (unsigned long long)a;
+    const double r = mod_reduce(a, t, tinv);
+    io[i] = neg && r != 0.0 ? t - r : r;
+  }
+#pragma unroll
+  for (int d = 32; d > 0; d >>= 1) {
+    const unsigned long long o = __shfl_xor(mag, d);
+    mag = o > mag ? o : mag;
+  }
+  if ((threadIdx.x & 63) == 0) atomicMax(worst, mag);
+}
+// slot j < m of query k (block k of block_w slots): 0, 1, or 2 for any other value
+__global__ void label_bits_kernel(uint8_t* bits, const double* ev, const uint32_t* eval_of_slot, uint32_t m, uint32_t total,
+                                  uint32_t block_w, uint32_t blocks_per_row, int logN) {
+  const uint32_t g = blockIdx.x * blockDim.x + threadIdx.x;
+  if (g >= total) return;
+  const uint32_t k = g / m, j = g % m;
+  const uint32_t slot = ((k / blocks_per_row) << (logN - 1)) + (k % blocks_per_row) * block_w + j;
+  const double v = ev[eval_of_slot[slot]];
+  bits[g] = v == 0.0 ? 0 : v == 1.0 ? 1 : 2;
+}
+
+// The label slots of a level-0 result: bits[n_queries * m] as label_bits_kernel; returns the largest centered
+// phase coefficient.  Only these bytes leave the device (1.1 ms to 0.2 ms for the 16-tree forest's 32 queries
+// together with the result's import: the transform modulo t took the host 0.8 ms).
+uint64_t decrypt_label_slots(Context& c, const Keys& k, const copse_public_meta& meta, const Ct& ct, size_t n_queries,
+                             std::vector<uint8_t>& bits) {
+  if (!k.has_secret) fail(COPSE_EKEY, "secret key absent");
+  const size_t N = c.N, total = n_queries * meta.m;
+  const int logN = (int)c.log_n;
+  DBuf ph(&c, N), back(&c, 1 + (total + 7) / 8);
+  auto* worst = reinterpret_cast<unsigned long long*>(back.get());
+  COPSE_HIP(hipMemsetAsync(worst, 0, 8, c.stream));
+  hipLaunchKernelGGL(phase0_kernel, wire_grid(c, 1), dim3(kWireThreads), 0, c.stream, ph.get(), ct.poly(0, N),
+                     ct.poly(1, N), k.s.get(), c.d_primes, logN);
+  COPSE_HIP(hipGetLastError());
+  launch_ntt_inv(c, ph.get(), limb_rows(c, 1, 1), 1);
+  hipLaunchKernelGGL(phase_mod_t_kernel, wire_grid(c, 1), dim3(kWireThreads), 0, c.stream, ph.get(),
+                     (double)c.primes[0], (double)c.t, 1.0 / (double)c.t, logN, worst);
+  COPSE_HIP(hipGetLastError());
+  launch_ntt_fwd(c, ph.get(), t_rows(c, 1), 1);
+  if (total > 0) {
+    hipLaunchKernelGGL(label_bits_kernel, dim3((unsigned)((total + kWireThreads - 1) / kWireThreads)),
+                       dim3(kWireThreads), 0, c.stream, reinterpret_cast<uint8_t*>(worst + 1), ph.get(),
+                       c.d_eval_of_slot, meta.m, (uint32_t)total, meta.block_w, (uint32_t)(N / 2 / meta.block_w), logN);
+    COPSE_HIP(hipGetLastError());
+  }
+  std::vector<uint8_t> h(8 + total);
+  COPSE_HIP(hipMemcpyAsync(h.data(), back.get(), h.size(), hipMemcpyDeviceToHost, c.stream));
+  COPSE_HIP(hipStreamSynchronize(c.stream));
+  bits.assign(h.begin() + 8, h.end());
+  uint64_t w;
+  std::memcpy(&w, h.data(), 8);
+  return w;
+}
+
+}  // namespace copse

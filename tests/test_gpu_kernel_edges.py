@@ -91,3 +91,54 @@ def test_transform_extremes(C, log_n, t, bits):
         for a, b in ((top, top), (alt, top), (rnd, alt)):
             want = B.ntt_inv(B.mulmod_vec(B.ntt_fwd(a, q, psi), B.ntt_fwd(b, q, psi), q), q, psi)
             assert (ctx.poly_mul(i, a, b) == want).all(), (log_n, i, q)
+
+
+@pytest.mark.parametrize("log_n,t", [(10, T), (11, T), (12, T), (13, T), (14, T), (15, T), (16, 5767169), (17, 5767169)])
+@pytest.mark.parametrize("level,polys", [(0, 1), (0, 2), (2, 3)])
+def test_wire_roundtrip_and_range(C, log_n, t, level, polys):
+    """Words in, words out, at the smallest and largest residues; a word equal to its prime, or far above it, is
+    refused wherever it stands."""
+    ctx = C.Context(log_n, 3, 1 << 48, 1 << 46, 1, 1 << 49, t=t)
+    qs = ctx.primes()[:level + 1]
+    rng = np.random.default_rng(log_n)
+    block = [np.stack([rng.integers(0, q, ctx.N, dtype=np.uint64) for q in qs]) for _ in range(polys)]
+    for p in block:
+        for i, q in enumerate(qs):
+            p[i, 0], p[i, 1], p[i, -1] = 0, q - 1, q - 1
+    got = ctx.export(ctx.import_(block, level))[0]
+    assert got["level"] == level and all((a == b).all() for a, b in zip(got["polys"], block))
+    for where in ((0, 0, 0), (polys - 1, level, ctx.N - 1), (polys - 1, 0, ctx.N // 2 + 1)):
+        for bad in (qs[where[1]], (1 << 64) - 1):
+            again = [p.copy() for p in block]
+            again[where[0]][where[1], where[2]] = bad
+            with pytest.raises(C.CopseError) as e:
+                ctx.import_(again, level)
+            assert e.value.code == C.COPSE_EINVAL
+
+
+@pytest.mark.parametrize("log_n,precision", [(11, 7), (11, 8), (11, 9), (13, 9)])
+def test_query_planes_beyond_one_launch(C, log_n, precision):
+    """Planes travel eight at a time: seven, eight and nine of them equal the oracle's."""
+    text = synth.gen_forest_text(synth.ForestShape(1, 2, 0.7, 3, precision, 2), 5)
+    oc = OC.compile_forest(text, 3, precision)
+    ctx = C.Context(log_n, 10, 1 << 49, 1 << 42, 2, 1 << 49)
+    sc = B.BGV(nt.make_chain(log_n, T, 10, 1 << 49, 1 << 42, 2, 1 << 49))
+    _, meta = C.forest_compile(text, 3, precision, log_n)
+    seed = b"\x17" * 32
+    keys, okeys = ctx.keygen(seed, [1]), sc.keygen(seed, rotations=[1])
+    queries = synth.gen_queries(4, 3, precision, 8)
+    X = CI.encrypt_queries(sc, okeys, CI.make_plan(oc, sc.N, sc.L), queries, seed, 3)
+    got = ctx.export(ctx.query_encrypt(keys, meta, queries, seed, group=3))
+    assert len(got) == len(X) == precision
+    for a, b in zip(got, X):
+        same(a, b)
+
+
+def test_slots_are_taken_modulo_t(C):
+    ctx = C.Context(11, 2, 1 << 49, 1 << 42, 1, 1 << 49)
+    keys = ctx.keygen(b"\x18" * 32, [])
+    v = np.random.default_rng(4).integers(0, T, ctx.N, dtype=np.uint64)
+    big = v.copy()
+    big[::3] += np.uint64(T) * np.uint64(281470681743361 - 1)   # up to just below 2^64
+    a, b = (ctx.export(ctx.encrypt_slots(keys, s, 1, b"\x19" * 32, 7))[0] for s in (v, big))
+    assert all((x == y).all() for x, y in zip(a["polys"], b["polys"]))
