@@ -433,7 +433,7 @@ std::unique_ptr<Keys> keygen(Context& c, const uint8_t seed[32], const std::vect
   K->pk_b = DBuf(&c, (size_t)nd * N);
   {
     std::vector<double> ha((size_t)nd * N);
-    for (int i = 0; i < nd; ++i) sample_uniform(seed, "pk.a", 0, (uint32_t)i, c.primes[i], N, ha.data() + (size_t)i * N);
+    sample_uniform_limbs(seed, "pk.a", 0, 0, {c.primes.begin(), c.primes.begin() + nd}, N, ha.data());
     COPSE_HIP(hipMemcpyAsync(K->pk_a.get(), ha.data(), ha.size() * 8, hipMemcpyHostToDevice, c.stream));
     launch_ntt_fwd(c, K->pk_a.get(), drows, nd);
     std::vector<int64_t> e(N);
@@ -457,8 +457,7 @@ std::unique_ptr<Keys> keygen(Context& c, const uint8_t seed[32], const std::vect
     DBuf te(&c, (size_t)Lt * N), as(&c, (size_t)Lt * N);
     for (int j = 0; j < D; ++j) {
       uint64_t obj = key_id * 256 + (uint64_t)j;
-      for (int i = 0; i < Lt; ++i)
-        sample_uniform(seed, "ksk.a", obj, (uint32_t)i, c.primes[i], N, ha.data() + (size_t)i * N);
+      sample_uniform_limbs(seed, "ksk.a", obj, 0, c.primes, N, ha.data());
       double* aj = k->a.get() + (size_t)j * Lt * N;
       double* bj = k->b.get() + (size_t)j * Lt * N;
       COPSE_HIP(hipMemcpyAsync(aj, ha.data(), ha.size() * 8, hipMemcpyHostToDevice, c.stream));

@@ -376,14 +376,7 @@ int copse_query_encrypt(copse_ctx* ctx, const copse_keys* keys, const copse_publ
     for (size_t i = 0; i < n_queries * meta->n_features; ++i)
       if (features[i] >= lim) fail(COPSE_EINVAL, "feature value exceeds the precision");
     auto cts = std::make_unique<copse_cts>();
-    const Keys& K = keys_of(c, keys);
-    std::vector<uint64_t> planes((size_t)meta->precision * c.N), slots, objs;
-    for (uint32_t k = 0; k < meta->precision; ++k) {
-      query_plane_slots(*meta, c.N, features, n_queries, k, slots);
-      std::copy(slots.begin(), slots.end(), planes.begin() + (size_t)k * c.N);
-      objs.push_back((1ULL << 56) | ((uint64_t)group << 32) | k);
-    }
-    cts->v = encrypt_slots_many(c, K, planes.data(), (int)meta->precision, c.L, seed, objs.data());
+    cts->v = encrypt_query(c, keys_of(c, keys), *meta, features, n_queries, seed, group);
     *out = cts.release();
   });
 }

@@ -309,25 +309,6 @@ void replicate_blocks(const copse_public_meta& M, size_t N, const std::vector<in
     }
 }
 
-void query_plane_slots(const copse_public_meta& M, size_t N, const uint32_t* feats, size_t nq, uint32_t plane,
-                       std::vector<uint64_t>& slots) {
-  slots.assign(N, 0);
-  uint32_t B_in = M.m + M.b + M.q - 2;
-  for (size_t k = 0; k < nq; ++k) {
-    if (M.server_rep) {
-      // each feature once, extended with period F over B_in + F - 1 slots
-      for (uint32_t s = 0; s < B_in + M.n_features - 1; ++s)
-        slots[slot_index(M, N, (uint32_t)k, s)] = (feats[k * M.n_features + s % M.n_features] >> plane) & 1u;
-      continue;
-    }
-    for (uint32_t s = 0; s < B_in; ++s) {
-      uint32_t pos = s % M.q;
-      uint32_t f = pos / M.K;
-      slots[slot_index(M, N, (uint32_t)k, s)] = (feats[k * M.n_features + f] >> plane) & 1u;
-    }
-  }
-}
-
 // Generalized diagonal k of A (rows x n), pre-rotated to block offset g*n1, replicated per block.
 void diagonal_slots(const copse_public_meta& M, size_t N, const std::vector<std::vector<int64_t>>& A, uint32_t k,
                     uint32_t n1, std::vector<uint64_t>& slots, uint64_t t, bool* nonzero) {

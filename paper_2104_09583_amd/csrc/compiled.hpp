@@ -59,8 +59,6 @@ SeccompPlan seccomp_plan(int n);
 int seccomp_depth(uint32_t p);
 void replicate_blocks(const copse_public_meta& M, size_t N, const std::vector<int64_t>& vec,
                       std::vector<uint64_t>& slots, uint64_t t);
-void query_plane_slots(const copse_public_meta& M, size_t N, const uint32_t* feats, size_t nq, uint32_t plane,
-                       std::vector<uint64_t>& slots);
 void diagonal_slots(const copse_public_meta& M, size_t N, const std::vector<std::vector<int64_t>>& A, uint32_t k,
                     uint32_t n1, std::vector<uint64_t>& slots, uint64_t t, bool* nonzero);
 

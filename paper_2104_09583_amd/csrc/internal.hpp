@@ -65,8 +65,13 @@ void sample_uniform(const uint8_t seed[32], const char* dom, uint64_t obj, uint3
                     size_t n, double* out);
 void sample_ternary(const uint8_t seed[32], const char* dom, uint64_t obj, size_t n, int64_t* out);
 void sample_cbd21(const uint8_t seed[32], const char* dom, uint64_t obj, size_t n, int64_t* out);
-// u, e0 and e1 of the encryption with object obj: out[3][n]
-void sample_encryption(const uint8_t seed[32], uint64_t obj, size_t n, int8_t* out);
+// sample_uniform of limbs first_limb, first_limb + 1, ... modulo q[0], q[1], ...: out[q.size()][n]
+void sample_uniform_limbs(const uint8_t seed[32], const char* dom, uint64_t obj, uint32_t first_limb,
+                          const std::vector<uint64_t>& q, size_t n, double* out);
+// The randomness of `count` encryptions, per encryption encryption_noise_bytes(n): u (n bytes, ternary), then the raw
+// streams of e0 and e1 (6 n bytes used of each, sample_cbd21's input).
+size_t encryption_noise_bytes(size_t n);
+void sample_encryption_many(const uint8_t seed[32], const uint64_t* objs, int count, size_t n, uint8_t* out);
 
 // ------------------------------------------------------------------ device-side descriptors
 struct DevPrime {
@@ -521,6 +526,9 @@ std::unique_ptr<Keys> keygen(Context& c, const uint8_t seed[32], const std::vect
 // (wire.hip) fresh encryptions of `count` slot vectors ([count][N]) with objects objs
 std::vector<CtPtr> encrypt_slots_many(Context& c, const Keys& k, const uint64_t* slots, int count, int level,
                                       const uint8_t seed[32], const uint64_t* objs);
+// (wire.hip) one query group's bit planes encrypted at the top level
+std::vector<CtPtr> encrypt_query(Context& c, const Keys& k, const copse_public_meta& M, const uint32_t* features,
+                                 size_t n_queries, const uint8_t seed[32], uint32_t group);
 // (wire.hip) the label slots of a level-0 result (0, 1, or 2 for any other value) and the largest centered phase
 uint64_t decrypt_label_slots(Context& c, const Keys& k, const copse_public_meta& meta, const Ct& ct, size_t n_queries,
                              std::vector<uint8_t>& bits);

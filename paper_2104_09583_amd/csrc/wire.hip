@@ -211,15 +211,25 @@ std::unique_ptr<Plain> make_plain_slots(Context& c, const uint64_t* slots, int l
 }
 
 // ------------------------------------------------------------------ encryption
-// z = 3 p + k, limb r: the coefficient rows of u (k = 0), t e0 + m (1) and t e1 (2) of plaintext p
-__global__ void enc_lift_kernel(double* out, const int8_t* noise, const double* m, double t, const DevPrime* P,
-                                int logN) {
-  const size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= (size_t)1 << logN) return;
+// z = 3 p + k, limb r: the coefficient rows of u (k = 0), t e0 + m (1) and t e1 (2) of plaintext p.  noise: per
+// plaintext `stride` bytes, u as bytes, then the two error streams of which every six bytes are one centered binomial
+// value (bits 0..20 against bits 21..41).
+__global__ void enc_lift_kernel(double* out, const uint8_t* noise, size_t stride, const double* m, double t,
+                                const DevPrime* P, int logN) {
+  const size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x, N = (size_t)1 << logN;
+  if (i >= N) return;
   const int z = blockIdx.z, k = z % 3;
   const DevPrime& pr = P[blockIdx.y];
-  double v = (double)noise[((size_t)z << logN) + i];
-  if (k != 0) v *= t;   // |e| <= 21: exact
+  const uint8_t* u = noise + (size_t)(z / 3) * stride;
+  double v;
+  if (k == 0) {
+    v = (double)(int8_t)u[i];
+  } else {
+    // N and the streams' length are even, so every value starts on an even address
+    const uint16_t* e = reinterpret_cast<const uint16_t*>(u + N + (size_t)(k - 1) * ((stride - N) / 2)) + 3 * i;
+    const uint64_t w = (uint64_t)e[0] | (uint64_t)e[1] << 16 | (uint64_t)e[2] << 32;
+    v = (double)((int)__popc((uint32_t)w & 0x1fffffu) - (int)__popc((uint32_t)(w >> 21) & 0x1fffffu)) * t;   // exact
+  }
   if (k == 1) v += center_t(m[((size_t)(z / 3) << logN) + i], t);
   out[(((size_t)z * gridDim.y + blockIdx.y) << logN) + i] = mod_reduce(v, pr.q, pr.qinv);
 }
@@ -237,37 +247,90 @@ __global__ void enc_combine_kernel(MPack out, const double* rows, const double* 
   out.p[p][ps + o] = canon(reduce_sym(mul_lazy(pk_a[o], u, pr.q, pr.qinv) + d[2 * ps], pr.q, pr.qinv), pr.q);
 }
 
-// Fresh encryptions of `count` slot vectors at `level` with objects objs: (pk0 u + t e0 + m, pk1 u + t e1).
-// Up to eight plaintexts travel together, so that the limb rows in flight stay below 80 MB for N = 32768 and twelve
-// limbs.  What is left is the host's SHAKE-256 (2.2 ms a plaintext on one core): eight planes encrypted and exported
-// take 13.5 ms, against 40.5 ms with the encoder's transform and the export's conversion on the host.
+// Fresh encryptions at `level` of n plaintexts given by their coefficients in [0, t): (pk0 u + t e0 + m, pk1 u + t e1)
+// A full group of eight planes encrypted and exported takes 5.4 ms (40.5 ms with encoding, sampling and layout on one
+// host core): 1.8 the host's SHAKE-256, 0.4 the device, the rest the 42 MB copied out to fresh pages.
+static void encrypt_many(Context& c, const Keys& k, const DBuf& m, int n, int level, const uint8_t seed[32],
+                         const uint64_t* objs, std::vector<CtPtr>& out) {
+  const size_t N = c.N, stride = encryption_noise_bytes(N);
+  const int nl = level + 1;
+  std::vector<uint8_t> noise(n * stride);
+  sample_encryption_many(seed, objs, n, N, noise.data());
+  DBuf dn(&c, (noise.size() + 7) / 8);
+  COPSE_HIP(hipMemcpyAsync(dn.get(), noise.data(), noise.size(), hipMemcpyHostToDevice, c.stream));
+  DBuf rows(&c, (size_t)3 * n * nl * N);
+  hipLaunchKernelGGL(enc_lift_kernel, wire_grid(c, nl, 3 * n), dim3(kWireThreads), 0, c.stream, rows.get(),
+                     reinterpret_cast<const uint8_t*>(dn.get()), stride, m.get(), (double)c.t, c.d_primes,
+                     (int)c.log_n);
+  COPSE_HIP(hipGetLastError());
+  launch_ntt_fwd(c, rows.get(), limb_rows(c, 3 * n, nl), 3 * n * nl);
+  MPack po;
+  for (int p = 0; p < n; ++p) {
+    out.push_back(ct_alloc(c, level, 2));
+    po.p[p] = out.back()->data();
+  }
+  hipLaunchKernelGGL(enc_combine_kernel, wire_grid(c, nl, n), dim3(kWireThreads), 0, c.stream, po, rows.get(),
+                     k.pk_b.get(), k.pk_a.get(), c.d_primes, (int)c.log_n);
+  COPSE_HIP(hipGetLastError());
+  COPSE_HIP(hipStreamSynchronize(c.stream));   // the noise is host memory
+}
+
+// Plaintexts travel eight at a time: the limb rows in flight stay below 80 MB (N = 32768, twelve limbs), and eight
+// streams of randomness fill the host's vectors.
+constexpr int kEncryptMany = 8;
+
 std::vector<CtPtr> encrypt_slots_many(Context& c, const Keys& k, const uint64_t* slots, int count, int level,
                                       const uint8_t seed[32], const uint64_t* objs) {
-  constexpr int kMany = 8;
-  const size_t N = c.N;
-  const int nl = level + 1;
   std::vector<CtPtr> out;
-  for (int first = 0; first < count; first += kMany) {
-    const int n = std::min(kMany, count - first);
-    std::vector<int8_t> noise((size_t)3 * n * N);
-    for (int p = 0; p < n; ++p) sample_encryption(seed, objs[first + p], N, noise.data() + (size_t)3 * p * N);
-    DBuf dn(&c, (noise.size() + 7) / 8);
-    COPSE_HIP(hipMemcpyAsync(dn.get(), noise.data(), noise.size(), hipMemcpyHostToDevice, c.stream));
-    DBuf m = encode_device(c, slots + (size_t)first * N, n);
-    DBuf rows(&c, (size_t)3 * n * nl * N);
-    hipLaunchKernelGGL(enc_lift_kernel, wire_grid(c, nl, 3 * n), dim3(kWireThreads), 0, c.stream, rows.get(),
-                       reinterpret_cast<const int8_t*>(dn.get()), m.get(), (double)c.t, c.d_primes, (int)c.log_n);
+  for (int first = 0; first < count; first += kEncryptMany) {
+    const int n = std::min(kEncryptMany, count - first);
+    encrypt_many(c, k, encode_device(c, slots + (size_t)first * c.N, n), n, level, seed, objs + first, out);
+  }
+  return out;
+}
+
+// Evaluation slot k of bit plane first + y: the query layout (compile.cpp) read backwards, from the slot to the
+// feature it holds, so that the features (n_queries x F words) are all that is copied to the device.
+__global__ void query_eval_kernel(double* ev, const uint32_t* feats, const uint32_t* slot_of_eval, uint32_t n_queries,
+                                  uint32_t n_features, uint32_t B, uint32_t q, uint32_t K, uint32_t block_w,
+                                  uint32_t first, int server_rep, int logN) {
+  const uint32_t k = blockIdx.x * blockDim.x + threadIdx.x;
+  if (k >= 1u << logN) return;
+  const uint32_t half = 1u << (logN - 1), slot = slot_of_eval[k], col = slot & (half - 1);
+  const uint32_t per_row = half / block_w, in_row = col / block_w, s = col % block_w;
+  const uint32_t query = (slot >> (logN - 1)) * per_row + in_row;
+  double v = 0.0;
+  if (in_row < per_row && query < n_queries && s < B) {
+    const uint32_t f = server_rep ? s % n_features : s % q / K;
+    v = (double)((feats[query * n_features + f] >> (first + blockIdx.y)) & 1u);
+  }
+  ev[((size_t)blockIdx.y << logN) + k] = v;
+}
+
+// One query group: every bit plane encrypted at the top level (objects as copse_query_encrypt)
+std::vector<CtPtr> encrypt_query(Context& c, const Keys& k, const copse_public_meta& M, const uint32_t* features,
+                                 size_t n_queries, const uint8_t seed[32], uint32_t group) {
+  // what the kernel divides by and indexes with (a compiled layout has it so)
+  if (M.block_w == 0 || M.block_w > c.N / 2 || M.n_features == 0 || M.K == 0 || M.q == 0 ||
+      (uint64_t)M.q > (uint64_t)M.K * M.n_features || n_queries > c.N / 2 / M.block_w * 2 || M.precision > 32)
+    fail(COPSE_EINVAL, "layout made for another ring size");
+  std::vector<CtPtr> out;
+  if (M.precision == 0) return out;
+  const size_t words = n_queries * M.n_features;
+  DBuf feats(&c, (words + 1) / 2);
+  COPSE_HIP(hipMemcpyAsync(feats.get(), features, words * sizeof(uint32_t), hipMemcpyHostToDevice, c.stream));
+  const uint32_t B = M.m + M.b + M.q - 2 + (M.server_rep ? M.n_features - 1 : 0);
+  for (uint32_t first = 0; first < M.precision; first += kEncryptMany) {
+    const int n = (int)std::min<uint32_t>(kEncryptMany, M.precision - first);
+    DBuf m(&c, n * c.N);
+    hipLaunchKernelGGL(query_eval_kernel, wire_grid(c, n), dim3(kWireThreads), 0, c.stream, m.get(),
+                       reinterpret_cast<const uint32_t*>(feats.get()), c.d_slot_of_eval, (uint32_t)n_queries,
+                       M.n_features, B, M.q, M.K, M.block_w, first, M.server_rep ? 1 : 0, (int)c.log_n);
     COPSE_HIP(hipGetLastError());
-    launch_ntt_fwd(c, rows.get(), limb_rows(c, 3 * n, nl), 3 * n * nl);
-    MPack po;
-    for (int p = 0; p < n; ++p) {
-      out.push_back(ct_alloc(c, level, 2));
-      po.p[p] = out.back()->data();
-    }
-    hipLaunchKernelGGL(enc_combine_kernel, wire_grid(c, nl, n), dim3(kWireThreads), 0, c.stream, po, rows.get(),
-                       k.pk_b.get(), k.pk_a.get(), c.d_primes, (int)c.log_n);
-    COPSE_HIP(hipGetLastError());
-    COPSE_HIP(hipStreamSynchronize(c.stream));   // noise and slots are host memory
+    launch_ntt_inv(c, m.get(), t_rows(c, n), n);
+    uint64_t objs[kEncryptMany];
+    for (int p = 0; p < n; ++p) objs[p] = (1ULL << 56) | ((uint64_t)group << 32) | (first + (uint32_t)p);
+    encrypt_many(c, k, m, n, c.L, seed, objs, out);
   }
   return out;
 }
