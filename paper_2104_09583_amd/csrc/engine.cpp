@@ -357,16 +357,33 @@ static void ks_batch(Context& c, int level, const std::vector<const double*>& in
   const int R = (int)reqs.size();
   const int Lt = c.n_primes();
   KSTables& T = c.kstab(level);
-  const bool fused = bridge_supported(c, c.alpha);
+  // rotations with more than eight digits take the separate passes
+  const bool fused = bridge_supported(c, c.alpha) && !(add_mode == 2 && D > 8);
   if (merge && !(fused && add_mode == 1 && level >= 1 && T.mm_ok))
     fail(COPSE_EINVAL, "internal: merged switch not available here");
   if (inputs_b && (!merge || inputs_b->size() != inputs.size()))
     fail(COPSE_EINVAL, "internal: product inputs only for the merged relinearization");
   // relinearizations (no automorphism) fold the ModUp's forward row pass and the ModDown's inverse row
   // pass into the inner products (two launches fewer, the extended rows never written in NTT form)
-  bool no_auto = fused;
-  for (const KsReq& rq : reqs) no_auto = no_auto && rq.g == 1;
+  const bool no_auto = fused && add_mode == 1;
   DBuf ext = modup_batch(c, level, inputs, !no_auto, inputs_b);
+  if (fused && add_mode == 2) {
+    // rotations: the inner products only where their result is used (keyswitch.hip)
+    DBuf acc(&c, (size_t)R * 2 * c.alpha * N), w(&c, (size_t)R * 2 * nl * N);
+    std::vector<KsRot> rots;
+    for (const KsReq& rq : reqs)
+      rots.push_back(KsRot{inputs[rq.input], ext.get() + (size_t)rq.input * D * nE * N, rq.key->b.get(),
+                           rq.key->a.get(), rq.add, rq.out, rq.g});
+    launch_ks_rot_special(c, rots, acc.get(), D, nE, level, (size_t)Lt * N);
+    std::vector<int2> inr, outr;
+    for (int s = 0; s < c.alpha; ++s) inr.push_back(make_int2(s, c.L + 1 + s));
+    for (int i = 0; i < nl; ++i) outr.push_back(make_int2(i, i));
+    launch_bridge(c, 0, w.get(), rows_cached(c, "mdout:" + std::to_string(level), outr), nl, acc.get(),
+                  rows_cached(c, "rotin:" + std::to_string(c.alpha), inr), c.alpha, T.d_md_mult, T.d_md_mat, 2 * R,
+                  (size_t)c.alpha * N, (size_t)nl * N);
+    launch_ks_rot_finish(c, rots, w.get(), T.d_md_pinv, D, nE, level, (size_t)Lt * N);
+    return;
+  }
   // inner products
   DBuf acc(&c, (size_t)R * 2 * nE * N);
   std::vector<KsJob2> jobs;
@@ -449,8 +466,7 @@ static void ks_batch(Context& c, int level, const std::vector<const double*>& in
     launch_bridge(c, 0, zh.get(), rows_cached(c, "mdout:" + std::to_string(level), outr), nl, acc.get(),
                   rows_cached(c, "mdin:" + std::to_string(level), inr), c.alpha, T.d_md_mult, T.d_md_mat, 2 * R,
                   (size_t)nE * N, (size_t)nl * N);
-    launch_ntt_fwd_rows_md_finish(c, outs, adds, gal, acc.get(), zh.get(), nE, nl, T.d_md_pinv, T.d_md_tpinv,
-                                  add_mode);
+    launch_ntt_fwd_rows_md_finish(c, outs, adds, acc.get(), zh.get(), nE, nl, T.d_md_pinv, T.d_md_tpinv);
     return;
   } else {
     launch_bconv(c, zh.get(), rows_cached(c, "mdout:" + std::to_string(level), outr), nl, acc.get(),

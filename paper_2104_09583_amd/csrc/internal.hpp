@@ -287,10 +287,10 @@ void launch_ntt_inv_rows_gather(Context& c, double* dst, const std::vector<const
                                 const std::vector<int>* levels = nullptr,
                                 const std::vector<const double*>* mulp = nullptr,
                                 const std::vector<const double*>* addp = nullptr);
-// forward row pass of the ModDown rows w fused with the ModDown finish (as launch_md_finish2)
+// forward row pass of the ModDown rows w fused with the ModDown finish (as launch_md_finish2 with add_mode 1)
 void launch_ntt_fwd_rows_md_finish(Context& c, const std::vector<double*>& out, const std::vector<const double*>& add,
-                                   const std::vector<uint64_t>& gal, const double* acc, const double* w, int nE,
-                                   int nl, const double* pinv, const double* tpinv, int add_mode);
+                                   const double* acc, const double* w, int nE, int nl, const double* pinv,
+                                   const double* tpinv);
 // forward row pass of the merged ModDown + switch rows w (l = level of the inputs, l output limbs) fused
 // with its finish: out_j[k][i] = acc[2j+k][i] m1_i + add_j[k][i] m3_i - w[2j+k][i] m2_i  (i < l)
 // masks (optional): masks[j] (l limbs per poly) is added to the first mask_np polys of out[j]
@@ -427,6 +427,22 @@ void launch_ks_inner2(Context& c, const std::vector<KsJob2>& jobs, int D, int nE
 // are written after the inverse row pass (the rows the ModDown transforms back; nE: none)
 void launch_ks_inner_rows(Context& c, const std::vector<KsJob2>& jobs, int D, int nE, int level, size_t key_ds,
                           double ptop, int inv_from);
+// Hoisted rotations on the rings of the split transform (keyswitch.hip), jobs of one level and digit count D <= 8:
+// the special rows of the inner products with their inverse row pass, to acc [jobs][2][alpha][N], and, from the
+// converted rows w [jobs][2][nl][N], the ModDown's finish with the data rows' inner products inside.
+struct KsRot {
+  const double* in;      // input poly (NTT form, nl limbs): the digits' own limbs
+  const double* ext;     // [D][nE][N] ModUp output (target rows only)
+  const double* kb;
+  const double* ka;
+  const double* c0;      // added after sigma_g to polynomial 0
+  double* out;           // 2 polys of nl limbs
+  uint64_t g;
+};
+void launch_ks_rot_special(Context& c, const std::vector<KsRot>& jobs, double* acc, int D, int nE, int level,
+                           size_t key_ds);
+void launch_ks_rot_finish(Context& c, const std::vector<KsRot>& jobs, const double* w, const double* pinv, int D,
+                          int nE, int level, size_t key_ds);
 // Key-switch inner products summed per output (giant steps of a product, one ModDown for their sum).
 // Product p has G outputs (batch elements) that share its key sequence: output (p, b) accumulates, over the
 // product's steps s, sum_j digit_j(sigma_{g_s}(in_{s,b})) key_{s,j} in the extended basis, plus P times the

@@ -12,19 +12,9 @@
 #include <type_traits>
 
 #include "internal.hpp"
-#include "modarith.hpp"
+#include "rowtile.hpp"
 
 namespace copse {
-
-// ------------------------------------------------------------------ automorphism (evaluation domain)
-// Slot k holds a(psi^e) with e = 2 bitrev(k) + 1.  sigma_g(a)(psi^e) = a(psi^(g e)), so the
-// output slot k reads the input slot holding exponent g e mod 2N.
-__device__ __forceinline__ uint32_t auto_src(uint32_t k, uint64_t g, int logN) {
-  // g, e < 2 N: only the product's low logN + 1 bits are used, so a 24-bit product (full rate) serves N < 2^23
-  uint32_t e = 2 * (__builtin_bitreverse32(k) >> (32 - logN)) + 1;
-  uint32_t ge = __umul24((uint32_t)g, e) & (uint32_t)((2ULL << logN) - 1);
-  return __builtin_bitreverse32(ge >> 1) >> (32 - logN);
-}
 
 // ------------------------------------------------------------------ NTT
 // Forward transform: Cooley-Tukey butterflies, natural-order input,
@@ -244,11 +234,6 @@ __device__ __forceinline__ void radix8_gs(double* x, size_t gb, size_t d, size_t
   for (int k = 0; k < 4; ++k) bfly_gs(x[k], x[k + 4], w0, pr.q, pr.qinv);
 }
 
-__device__ __forceinline__ void red8(double* x, const DevPrime& pr) {
-#pragma unroll
-  for (int k = 0; k < 8; ++k) x[k] = reduce_sym(x[k], pr.q, pr.qinv);
-}
-
 template <bool kInverse>
 __global__ __launch_bounds__(256) void ntt_rowreg_kernel(double* __restrict__ base, const int2* __restrict__ rows,
                                                         const DevPrime* __restrict__ P, int logN, int S1, int scale) {
@@ -344,289 +329,6 @@ __global__ __launch_bounds__(256) void ntt_rowreg_kernel(double* __restrict__ ba
   }
 }
 
-// Twiddles of one radix-8 round of a thread whose 8 elements gb + d k (k < 8) lie in one aligned block of
-// 8 d at stage offset m (the round's three stages use 1, 2 and 4 of them).
-struct Tw8 {
-  double w0, w1a, w1b, w2[4];
-};
-__device__ __forceinline__ Tw8 tw8_load(const double* tab, size_t gb, size_t d, size_t m) {
-  const size_t g0 = gb / (8 * d);
-  Tw8 w;
-  w.w0 = gload(tab + m + g0);
-  w.w1a = gload(tab + 2 * m + 2 * g0);
-  w.w1b = gload(tab + 2 * m + 2 * g0 + 1);
-#pragma unroll
-  for (int k = 0; k < 4; ++k) w.w2[k] = gload(tab + 4 * m + 4 * g0 + k);
-  return w;
-}
-__device__ __forceinline__ void radix8_ct_w(double* x, const Tw8& w, const DevPrime& pr) {
-#pragma unroll
-  for (int k = 0; k < 4; ++k) bfly_ct(x[k], x[k + 4], w.w0, pr.q, pr.qinv);
-  bfly_ct(x[0], x[2], w.w1a, pr.q, pr.qinv);
-  bfly_ct(x[1], x[3], w.w1a, pr.q, pr.qinv);
-  bfly_ct(x[4], x[6], w.w1b, pr.q, pr.qinv);
-  bfly_ct(x[5], x[7], w.w1b, pr.q, pr.qinv);
-#pragma unroll
-  for (int k = 0; k < 4; ++k) bfly_ct(x[2 * k], x[2 * k + 1], w.w2[k], pr.q, pr.qinv);
-}
-__device__ __forceinline__ void radix8_gs_w(double* x, const Tw8& w, const DevPrime& pr) {
-#pragma unroll
-  for (int k = 0; k < 4; ++k) bfly_gs(x[2 * k], x[2 * k + 1], w.w2[k], pr.q, pr.qinv);
-  bfly_gs(x[0], x[2], w.w1a, pr.q, pr.qinv);
-  bfly_gs(x[1], x[3], w.w1a, pr.q, pr.qinv);
-  bfly_gs(x[4], x[6], w.w1b, pr.q, pr.qinv);
-  bfly_gs(x[5], x[7], w.w1b, pr.q, pr.qinv);
-#pragma unroll
-  for (int k = 0; k < 4; ++k) bfly_gs(x[k], x[k + 4], w.w0, pr.q, pr.qinv);
-}
-
-// Row pass over a tile of 4096 contiguous elements (stages S1..S1+11): 512 threads x 8 registers,
-// four radix-8 rounds (distances 2048/1024/512, 256/128/64, 32/16/8, 4/2/1) with three LDS exchanges.
-constexpr int kLdsTile4 = 4096 + 4096 / 16;
-
-// One 4096-element tile of the row pass, 512 threads x 8 registers, four radix-8 rounds with LDS
-// exchanges between them and one more so that global memory is always touched at t + 512 k (each
-// load or store instruction covers 512 consecutive bytes per wave).  Both directions read src[t + 512 k]
-// of the tile and leave the values of tile positions t + 512 k in x[k] (signed, not reduced).  gb0 is the
-// tile's first index in the row (twiddle groups).  The twiddles of the first two rounds are loaded with
-// the data and those of every later round one round ahead, so a small launch waits on memory once.
-// With pre given, the forward tile also loads pre[t + 512 k] into y[k] during its third round (an
-// epilogue's operand, so that its latency overlaps the transform).
-__device__ __forceinline__ void row4_fwd_tile(const double* __restrict__ src, size_t gb0, int S1, const DevPrime& pr,
-                                              double* sh, double x[8], const double* pre = nullptr,
-                                              double* y = nullptr) {
-  const int t = threadIdx.x;
-  const size_t mA = (size_t)1 << S1, mB = mA << 3, mC = mA << 6, mD = mA << 9;
-  const int jA = t, jB = (t >> 6) * 512 + (t & 63), jC = (t >> 3) * 64 + (t & 7), jD = 8 * t;
-  const Tw8 wa = tw8_load(pr.fwd, gb0 + jA, 512, mA);
-  const Tw8 wb = tw8_load(pr.fwd, gb0 + jB, 64, mB);
-#pragma unroll
-  for (int k = 0; k < 8; ++k) x[k] = gload(src + jA + 512 * k);
-  radix8_ct_w(x, wa, pr);
-  const Tw8 wc = tw8_load(pr.fwd, gb0 + jC, 8, mC);
-#pragma unroll
-  for (int k = 0; k < 8; ++k) sh[lds_idx(jA + 512 * k)] = x[k];
-  lds_barrier();
-#pragma unroll
-  for (int k = 0; k < 8; ++k) x[k] = sh[lds_idx(jB + 64 * k)];
-  radix8_ct_w(x, wb, pr);
-  const Tw8 wd = tw8_load(pr.fwd, gb0 + jD, 1, mD);
-  if (pr.q >= kFwdLazy) red8(x, pr);   // uniform
-#pragma unroll
-  for (int k = 0; k < 8; ++k) sh[lds_idx(jB + 64 * k)] = x[k];
-  lds_wave_sync();   // rounds B and C touch the same 512 elements of this wave's block
-#pragma unroll
-  for (int k = 0; k < 8; ++k) x[k] = sh[lds_idx(jC + 8 * k)];
-  if (pre != nullptr) {
-#pragma unroll
-    for (int k = 0; k < 8; ++k) y[k] = gload(pre + t + 512 * k);
-  }
-  radix8_ct_w(x, wc, pr);
-#pragma unroll
-  for (int k = 0; k < 8; ++k) sh[lds_idx(jC + 8 * k)] = x[k];
-  lds_wave_sync();   // and so do rounds C and D
-#pragma unroll
-  for (int k = 0; k < 8; ++k) x[k] = sh[lds_idx(jD + k)];
-  radix8_ct_w(x, wd, pr);
-  // each thread overwrites only the LDS words it just read
-#pragma unroll
-  for (int k = 0; k < 8; ++k) sh[lds_idx(jD + k)] = x[k];
-  lds_barrier();
-#pragma unroll
-  for (int k = 0; k < 8; ++k) x[k] = sh[lds_idx(jA + 512 * k)];
-}
-
-// With vals given, the tile's values at t + 512 k are vals[k] instead of src[t + 512 k].
-__device__ __forceinline__ void row4_inv_tile(const double* __restrict__ src, size_t gb0, int S1, const DevPrime& pr,
-                                              double* sh, double x[8], const double* vals = nullptr) {
-  const int t = threadIdx.x;
-  const size_t mA = (size_t)1 << S1, mB = mA << 3, mC = mA << 6, mD = mA << 9;
-  const int jA = t, jB = (t >> 6) * 512 + (t & 63), jC = (t >> 3) * 64 + (t & 7), jD = 8 * t;
-  const Tw8 wd = tw8_load(pr.inv, gb0 + jD, 1, mD);
-  const Tw8 wc = tw8_load(pr.inv, gb0 + jC, 8, mC);
-#pragma unroll
-  for (int k = 0; k < 8; ++k) sh[lds_idx(jA + 512 * k)] = vals != nullptr ? vals[k] : gload(src + jA + 512 * k);
-  lds_barrier();
-#pragma unroll
-  for (int k = 0; k < 8; ++k) x[k] = sh[lds_idx(jD + k)];
-  radix8_gs_w(x, wd, pr);
-  const Tw8 wb = tw8_load(pr.inv, gb0 + jB, 64, mB);
-  if (pr.q >= kInvLazy) red8(x, pr);   // uniform
-#pragma unroll
-  for (int k = 0; k < 8; ++k) sh[lds_idx(jD + k)] = x[k];
-  lds_wave_sync();   // rounds D and C touch the same 512 elements of this wave's block
-#pragma unroll
-  for (int k = 0; k < 8; ++k) x[k] = sh[lds_idx(jC + 8 * k)];
-  radix8_gs_w(x, wc, pr);
-  const Tw8 wa = tw8_load(pr.inv, gb0 + jA, 512, mA);
-  red8(x, pr);
-#pragma unroll
-  for (int k = 0; k < 8; ++k) sh[lds_idx(jC + 8 * k)] = x[k];
-  lds_wave_sync();   // and so do rounds C and B
-#pragma unroll
-  for (int k = 0; k < 8; ++k) x[k] = sh[lds_idx(jB + 64 * k)];
-  radix8_gs_w(x, wb, pr);
-  if (pr.q >= kInvLazy) red8(x, pr);
-#pragma unroll
-  for (int k = 0; k < 8; ++k) sh[lds_idx(jB + 64 * k)] = x[k];
-  lds_barrier();
-#pragma unroll
-  for (int k = 0; k < 8; ++k) x[k] = sh[lds_idx(jA + 512 * k)];
-  radix8_gs_w(x, wa, pr);
-}
-
-// Two tiles of one row pass at once (the same prime and tile position, so the same twiddles): the rounds of
-// both run between the same exchanges, so a workgroup waits at half the barriers per tile and has twice the
-// independent work between them.  sh and sh2: one tile buffer each.  The forward pair reads srcA[t + 512 k]
-// and srcB[t + 512 k]; the inverse pair takes the tiles' values at t + 512 k in va and vb.  Results as for
-// one tile, in x and y.
-__device__ __forceinline__ void row4_fwd_tile2(const double* __restrict__ srcA, const double* __restrict__ srcB,
-                                               size_t gb0, int S1, const DevPrime& pr, double* sh, double* sh2,
-                                               double x[8], double y[8]) {
-  const int t = threadIdx.x;
-  const size_t mA = (size_t)1 << S1, mB = mA << 3, mC = mA << 6, mD = mA << 9;
-  const int jA = t, jB = (t >> 6) * 512 + (t & 63), jC = (t >> 3) * 64 + (t & 7), jD = 8 * t;
-  const Tw8 wa = tw8_load(pr.fwd, gb0 + jA, 512, mA);
-  const Tw8 wb = tw8_load(pr.fwd, gb0 + jB, 64, mB);
-#pragma unroll
-  for (int k = 0; k < 8; ++k) {
-    x[k] = gload(srcA + jA + 512 * k);
-    y[k] = gload(srcB + jA + 512 * k);
-  }
-  radix8_ct_w(x, wa, pr);
-  radix8_ct_w(y, wa, pr);
-  const Tw8 wc = tw8_load(pr.fwd, gb0 + jC, 8, mC);
-#pragma unroll
-  for (int k = 0; k < 8; ++k) {
-    sh[lds_idx(jA + 512 * k)] = x[k];
-    sh2[lds_idx(jA + 512 * k)] = y[k];
-  }
-  lds_barrier();
-#pragma unroll
-  for (int k = 0; k < 8; ++k) {
-    x[k] = sh[lds_idx(jB + 64 * k)];
-    y[k] = sh2[lds_idx(jB + 64 * k)];
-  }
-  radix8_ct_w(x, wb, pr);
-  radix8_ct_w(y, wb, pr);
-  const Tw8 wd = tw8_load(pr.fwd, gb0 + jD, 1, mD);
-  if (pr.q >= kFwdLazy) {   // uniform
-    red8(x, pr);
-    red8(y, pr);
-  }
-#pragma unroll
-  for (int k = 0; k < 8; ++k) {
-    sh[lds_idx(jB + 64 * k)] = x[k];
-    sh2[lds_idx(jB + 64 * k)] = y[k];
-  }
-  lds_wave_sync();   // rounds B and C touch the same 512 elements of this wave's block
-#pragma unroll
-  for (int k = 0; k < 8; ++k) {
-    x[k] = sh[lds_idx(jC + 8 * k)];
-    y[k] = sh2[lds_idx(jC + 8 * k)];
-  }
-  radix8_ct_w(x, wc, pr);
-  radix8_ct_w(y, wc, pr);
-#pragma unroll
-  for (int k = 0; k < 8; ++k) {
-    sh[lds_idx(jC + 8 * k)] = x[k];
-    sh2[lds_idx(jC + 8 * k)] = y[k];
-  }
-  lds_wave_sync();   // and so do rounds C and D
-#pragma unroll
-  for (int k = 0; k < 8; ++k) {
-    x[k] = sh[lds_idx(jD + k)];
-    y[k] = sh2[lds_idx(jD + k)];
-  }
-  radix8_ct_w(x, wd, pr);
-  radix8_ct_w(y, wd, pr);
-  // each thread overwrites only the LDS words it just read
-#pragma unroll
-  for (int k = 0; k < 8; ++k) {
-    sh[lds_idx(jD + k)] = x[k];
-    sh2[lds_idx(jD + k)] = y[k];
-  }
-  lds_barrier();
-#pragma unroll
-  for (int k = 0; k < 8; ++k) {
-    x[k] = sh[lds_idx(jA + 512 * k)];
-    y[k] = sh2[lds_idx(jA + 512 * k)];
-  }
-}
-
-__device__ __forceinline__ void row4_inv_tile2(size_t gb0, int S1, const DevPrime& pr, double* sh, double* sh2,
-                                               const double va[8], const double vb[8], double x[8], double y[8]) {
-  const int t = threadIdx.x;
-  const size_t mA = (size_t)1 << S1, mB = mA << 3, mC = mA << 6, mD = mA << 9;
-  const int jA = t, jB = (t >> 6) * 512 + (t & 63), jC = (t >> 3) * 64 + (t & 7), jD = 8 * t;
-  const Tw8 wd = tw8_load(pr.inv, gb0 + jD, 1, mD);
-  const Tw8 wc = tw8_load(pr.inv, gb0 + jC, 8, mC);
-#pragma unroll
-  for (int k = 0; k < 8; ++k) {
-    sh[lds_idx(jA + 512 * k)] = va[k];
-    sh2[lds_idx(jA + 512 * k)] = vb[k];
-  }
-  lds_barrier();
-#pragma unroll
-  for (int k = 0; k < 8; ++k) {
-    x[k] = sh[lds_idx(jD + k)];
-    y[k] = sh2[lds_idx(jD + k)];
-  }
-  radix8_gs_w(x, wd, pr);
-  radix8_gs_w(y, wd, pr);
-  const Tw8 wb = tw8_load(pr.inv, gb0 + jB, 64, mB);
-  if (pr.q >= kInvLazy) {   // uniform
-    red8(x, pr);
-    red8(y, pr);
-  }
-#pragma unroll
-  for (int k = 0; k < 8; ++k) {
-    sh[lds_idx(jD + k)] = x[k];
-    sh2[lds_idx(jD + k)] = y[k];
-  }
-  lds_wave_sync();   // rounds D and C touch the same 512 elements of this wave's block
-#pragma unroll
-  for (int k = 0; k < 8; ++k) {
-    x[k] = sh[lds_idx(jC + 8 * k)];
-    y[k] = sh2[lds_idx(jC + 8 * k)];
-  }
-  radix8_gs_w(x, wc, pr);
-  radix8_gs_w(y, wc, pr);
-  const Tw8 wa = tw8_load(pr.inv, gb0 + jA, 512, mA);
-  red8(x, pr);
-  red8(y, pr);
-#pragma unroll
-  for (int k = 0; k < 8; ++k) {
-    sh[lds_idx(jC + 8 * k)] = x[k];
-    sh2[lds_idx(jC + 8 * k)] = y[k];
-  }
-  lds_wave_sync();   // and so do rounds C and B
-#pragma unroll
-  for (int k = 0; k < 8; ++k) {
-    x[k] = sh[lds_idx(jB + 64 * k)];
-    y[k] = sh2[lds_idx(jB + 64 * k)];
-  }
-  radix8_gs_w(x, wb, pr);
-  radix8_gs_w(y, wb, pr);
-  if (pr.q >= kInvLazy) {
-    red8(x, pr);
-    red8(y, pr);
-  }
-#pragma unroll
-  for (int k = 0; k < 8; ++k) {
-    sh[lds_idx(jB + 64 * k)] = x[k];
-    sh2[lds_idx(jB + 64 * k)] = y[k];
-  }
-  lds_barrier();
-#pragma unroll
-  for (int k = 0; k < 8; ++k) {
-    x[k] = sh[lds_idx(jA + 512 * k)];
-    y[k] = sh2[lds_idx(jA + 512 * k)];
-  }
-  radix8_gs_w(x, wa, pr);
-  radix8_gs_w(y, wa, pr);
-}
-
 template <bool kInverse>
 __global__ __launch_bounds__(512) void ntt_rowreg4_kernel(double* __restrict__ base, const int2* __restrict__ rows,
                                                          const DevPrime* __restrict__ P, int logN, int S1, int scale) {
@@ -636,22 +338,21 @@ __global__ __launch_bounds__(512) void ntt_rowreg4_kernel(double* __restrict__ b
   const size_t N = (size_t)1 << logN;
   const size_t t0 = (size_t)blockIdx.x * 4096;
   double* a = base + (size_t)row.x * N + t0;
-  const int t = threadIdx.x;
   double x[8];
   if (!kInverse) {
     row4_fwd_tile(a, t0, S1, pr, sh, x);
 #pragma unroll
-    for (int k = 0; k < 8; ++k) a[t + 512 * k] = canon(reduce_sym(x[k], pr.q, pr.qinv), pr.q);
+    for (int k = 0; k < 8; ++k) tile_store(a, k, canon(reduce_sym(x[k], pr.q, pr.qinv), pr.q));
   } else {
     row4_inv_tile(a, t0, S1, pr, sh, x);
     if (scale) {
 #pragma unroll
       for (int k = 0; k < 8; ++k)
-        a[t + 512 * k] = canon(reduce_sym(mul_lazy(x[k], pr.ninv, pr.q, pr.qinv), pr.q, pr.qinv), pr.q);
+        tile_store(a, k, canon(reduce_sym(mul_lazy(x[k], pr.ninv, pr.q, pr.qinv), pr.q, pr.qinv), pr.q));
     } else {
       if (pr.q >= kInvOpen || S1 > 4) red8(x, pr);   // uniform
 #pragma unroll
-      for (int k = 0; k < 8; ++k) a[t + 512 * k] = x[k];
+      for (int k = 0; k < 8; ++k) tile_store(a, k, x[k]);
     }
   }
 }
@@ -689,37 +390,35 @@ __global__ __launch_bounds__(512) void ntt_rowinv_gather_kernel(double* __restri
   const double* a = src.p[j] + (size_t)poly * stride + off + t0;
   double x[8];
   if (prime_fixed == -4) {
-    const int t = threadIdx.x;
+    const double* mp = mulp.p[j] + off + t0;
+    const double* ap = addp.p[j] + off + t0;
     double v[8];
 #pragma unroll
-    for (int k = 0; k < 8; ++k) {
-      const size_t o2 = off + t0 + t + 512 * k;
-      v[k] = mul_lazy(gload(a + t + 512 * k), gload(mulp.p[j] + o2), pr.q, pr.qinv);
-      if (poly == 0) v[k] = reduce_sym(v[k] + gload(addp.p[j] + o2), pr.q, pr.qinv);
+    for (int k = 0; k < 8; ++k) v[k] = mul_lazy(tile_load(a, k), tile_load(mp, k), pr.q, pr.qinv);
+    if (poly == 0) {
+#pragma unroll
+      for (int k = 0; k < 8; ++k) v[k] = reduce_sym(v[k] + tile_load(ap, k), pr.q, pr.qinv);
     }
     row4_inv_tile(a, t0, S1, pr, sh, x, v);
   } else if (mulp.p[j] != nullptr) {
     // a product's third polynomial src (.) mulp, computed here (mulp in the layout of src)
     const double* bs = mulp.p[j] + (size_t)poly * stride + off + t0;
-    const int t = threadIdx.x;
     double v[8];
 #pragma unroll
-    for (int k = 0; k < 8; ++k) v[k] = mul_lazy(gload(a + t + 512 * k), gload(bs + t + 512 * k), pr.q, pr.qinv);
+    for (int k = 0; k < 8; ++k) v[k] = mul_lazy(tile_load(a, k), tile_load(bs, k), pr.q, pr.qinv);
     row4_inv_tile(a, t0, S1, pr, sh, x, v);
   } else {
     row4_inv_tile(a, t0, S1, pr, sh, x);
   }
   double* o = dst + (size_t)r * N + t0;
-  const int t = threadIdx.x;
   if (pr.q >= kInvOpen) red8(x, pr);   // uniform
 #pragma unroll
-  for (int k = 0; k < 8; ++k) o[t + 512 * k] = x[k];
+  for (int k = 0; k < 8; ++k) tile_store(o, k, x[k]);
 }
 
 // Forward row pass fused with the end of a ModDown (kMode 1) or of a modulus switch (kMode 2).
 //   kMode 1: block (tile, i, z = job * 2 + k) transforms w row z * nl + i and writes
-//            out_job[k][i] = acc[z][i] P^-1 - w t P^-1  (+ add_job[k][i] when add_mode 1,
-//            + add_job[0][i] at the automorphism's source index when add_mode 2 and k = 0)
+//            out_job[k][i] = acc[z][i] P^-1 - w t P^-1  (+ add_job[k][i] when add_mode 1)
 //   kMode 2: block (tile, i, z = job * np + k) transforms w row z * l + i and writes
 //            out_job[k][i] = in_job[k][i] q_l^-1 - w t q_l^-1  (+ add_job[k][i] for k < add_np)
 //   kMode 4: as kMode 2 for the switch of a plaintext layer: in_job[k] stands for in_job[k] * mulp_job
@@ -732,7 +431,7 @@ __global__ __launch_bounds__(512) void ntt_rowinv_gather_kernel(double* __restri
 // t q_l^-1 at 3 + 2 i).  Outputs are canonical.
 // at most 80 VGPRs: three workgroups per CU, as for the plain row pass
 template <int kMode>
-__global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(6))) void ntt_rowfwd_finish_kernel(MPack out, Pack in, Pack add, GPack gal, Pack ws,
+__global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(6))) void ntt_rowfwd_finish_kernel(MPack out, Pack in, Pack add, Pack ws,
                                                                Pack tabs, IPack lvs,
                                                                const double* __restrict__ acc,
                                                                const double* __restrict__ w, int nE, int nl_,
@@ -753,7 +452,6 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(6))) void n
   const DevPrime pr = P[i];
   const size_t N = (size_t)1 << logN;
   const size_t t0 = (size_t)blockIdx.x * 4096;
-  const int t = threadIdx.x;
   double x[8];
   const double* wrow = kMd ? w + ((size_t)z * nl + i) * N : ws.p[j] + ((size_t)k * nl + i) * N;
   const double* tab = kMd ? nullptr : tabs.p[j];
@@ -762,47 +460,66 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(6))) void n
   const double m3 = kMode == 3 ? amul[i] : 0.0;
   const size_t orow = ((size_t)k * nl + i) * N;
   const double* yrow = kMd ? acc + ((size_t)z * nE + i) * N : in.p[j] + ((size_t)k * nin + i) * N;
-  const uint64_t g = kMode == 1 ? gal.g[j] : 1;
   // the epilogue's main operand is loaded during the transform, so its latency overlaps it
   double yv[8];
   row4_fwd_tile(wrow + t0, t0, S1, pr, sh, x, yrow + t0, yv);
   if (kMode == 4) {
     // the plaintext layer's value of this limb (the input's limb i, the plaintexts' limb i)
+    const double* mp = mulp.p[j] + (size_t)i * N + t0;
+    const double* ap = add.p[j] + (size_t)i * N + t0;
 #pragma unroll
-    for (int kk = 0; kk < 8; ++kk) {
-      const size_t c = (size_t)i * N + t0 + t + 512 * kk;
-      yv[kk] = mul_lazy(yv[kk], gload(mulp.p[j] + c), pr.q, pr.qinv);
-      if (k == 0) yv[kk] += gload(add.p[j] + c);
+    for (int kk = 0; kk < 8; ++kk) yv[kk] = mul_lazy(yv[kk], tile_load(mp, kk), pr.q, pr.qinv);
+    if (k == 0) {
+#pragma unroll
+      for (int kk = 0; kk < 8; ++kk) yv[kk] += tile_load(ap, kk);
     }
   }
   // lazy to the end: |x| < 20 q (below 7.6 q for q >= 2^46) so each product is below 2 q, and with the
   // addends the sum stays below 8 q
 #pragma unroll
-  for (int kk = 0; kk < 8; ++kk) {
-    const size_t c = t0 + t + 512 * kk;
-    double v = mul_lazy(yv[kk], m1, pr.q, pr.qinv) - mul_lazy(x[kk], m2, pr.q, pr.qinv);
-    if (kMode == 3) {
-      double av;
-      if (mulp.p[j] == nullptr) {
-        av = add.p[j][((size_t)k * (nl + 1) + i) * N + c];
+  for (int kk = 0; kk < 8; ++kk) x[kk] = mul_lazy(yv[kk], m1, pr.q, pr.qinv) - mul_lazy(x[kk], m2, pr.q, pr.qinv);
+  // adds a row to x, all its loads issued first
+  auto add_row = [&](const double* row) {
+    double v[8];
+#pragma unroll
+    for (int kk = 0; kk < 8; ++kk) v[kk] = tile_load(row, kk);
+#pragma unroll
+    for (int kk = 0; kk < 8; ++kk) x[kk] += v[kk];
+  };
+  if (kMode == 3) {
+    const double* d0 = add.p[j] + (size_t)i * N + t0;             // the addend's polynomials at limb i
+    const double* d1 = d0 + (size_t)(nl + 1) * N;
+    double av[8];
+    if (mulp.p[j] == nullptr) {
+      const double* d = k == 0 ? d0 : d1;
+#pragma unroll
+      for (int kk = 0; kk < 8; ++kk) av[kk] = tile_load(d, kk);
+    } else {
+      // the addend is the product of the ciphertexts add and mulp: its polynomial k (uniform)
+      const double* e0 = mulp.p[j] + (size_t)i * N + t0;
+      const double* e1 = e0 + (size_t)(nl + 1) * N;
+      if (k == 0) {
+#pragma unroll
+        for (int kk = 0; kk < 8; ++kk) av[kk] = mul_lazy(tile_load(d0, kk), tile_load(e0, kk), pr.q, pr.qinv);
       } else {
-        // the addend is the product of the ciphertexts add and mulp: its polynomial k (uniform)
-        const size_t r0 = (size_t)i * N + c, r1 = ((size_t)(nl + 1) + i) * N + c;
-        const double a0 = add.p[j][r0], b0 = mulp.p[j][r0];
-        av = k == 0 ? mul_lazy(a0, b0, pr.q, pr.qinv)
-                    : mul_lazy(a0, mulp.p[j][r1], pr.q, pr.qinv) + mul_lazy(add.p[j][r1], b0, pr.q, pr.qinv);
+#pragma unroll
+        for (int kk = 0; kk < 8; ++kk)
+          av[kk] = mul_lazy(tile_load(d0, kk), tile_load(e1, kk), pr.q, pr.qinv) +
+                   mul_lazy(tile_load(d1, kk), tile_load(e0, kk), pr.q, pr.qinv);
       }
-      v += mul_lazy(av, m3, pr.q, pr.qinv);
-      // an optional mask (the `in` pack, l limbs per poly) on the first add_np polys
-      if (k < add_np && in.p[j] != nullptr) v += in.p[j][orow + c];
-    } else if (kMode == 1) {
-      if (add_mode == 1) v += add.p[j][orow + c];
-      if (add_mode == 2 && k == 0) v += add.p[j][(size_t)i * N + (g == 1 ? c : auto_src((uint32_t)c, g, logN))];
-    } else if (kMode == 2) {
-      if (k < add_np && add.p[j] != nullptr) v += add.p[j][orow + c];
     }
-    out.p[j][orow + c] = canon(reduce_sym(v, pr.q, pr.qinv), pr.q);
+#pragma unroll
+    for (int kk = 0; kk < 8; ++kk) x[kk] += mul_lazy(av[kk], m3, pr.q, pr.qinv);
+    // an optional mask (the `in` pack, l limbs per poly) on the first add_np polys
+    if (k < add_np && in.p[j] != nullptr) add_row(in.p[j] + orow + t0);
+  } else if (kMode == 1) {
+    if (add_mode == 1) add_row(add.p[j] + orow + t0);
+  } else if (kMode == 2) {
+    if (k < add_np && add.p[j] != nullptr) add_row(add.p[j] + orow + t0);
   }
+  double* op = out.p[j] + orow + t0;
+#pragma unroll
+  for (int kk = 0; kk < 8; ++kk) tile_store(op, kk, canon(reduce_sym(x[kk], pr.q, pr.qinv), pr.q));
 }
 
 template <bool kInverse>
@@ -1280,30 +997,27 @@ void launch_ntt_inv_rows_gather(Context& c, double* dst, const std::vector<const
 }
 
 void launch_ntt_fwd_rows_md_finish(Context& c, const std::vector<double*>& out, const std::vector<const double*>& add,
-                                   const std::vector<uint64_t>& gal, const double* acc, const double* w, int nE,
-                                   int nl, const double* pinv, const double* tpinv, int add_mode) {
+                                   const double* acc, const double* w, int nE, int nl, const double* pinv,
+                                   const double* tpinv) {
   if (c.log_n < 13) fail(COPSE_EINVAL, "internal: split transform needs N >= 8192");
   for (size_t first = 0; first < out.size(); first += kPack) {
     const int cnt = (int)std::min<size_t>(kPack, out.size() - first);
     MPack po;
-    Pack pa, pin;
-    GPack pg;
+    Pack pa;
     for (int k = 0; k < cnt; ++k) {
       po.p[k] = out[first + k];
-      pa.p[k] = add.empty() ? nullptr : add[first + k];
-      pg.g[k] = gal.empty() ? 1 : gal[first + k];
-      pin.p[k] = nullptr;
+      pa.p[k] = add[first + k];
     }
     hipEvent_t ev;
     prof_begin(c, 7, &ev);
     Pack none{};
     IPack nolv{};
     hipLaunchKernelGGL(ntt_rowfwd_finish_kernel<1>, dim3((unsigned)(c.N / 4096), nl, 2 * cnt), dim3(512), 0,
-                       c.stream, po, pin, pa, pg, none, none, nolv, acc + first * 2 * nE * c.N,
-                       w + first * 2 * nl * c.N, nE, nl, 2, add_mode, 0, pinv, tpinv, c.d_primes, (int)c.log_n,
+                       c.stream, po, none, pa, none, none, nolv, acc + first * 2 * nE * c.N,
+                       w + first * 2 * nl * c.N, nE, nl, 2, 1, 0, pinv, tpinv, c.d_primes, (int)c.log_n,
                        (int)c.log_n - 12, nullptr, none);
     COPSE_HIP(hipGetLastError());
-    prof_end(c, 7, ev, (6.0 + (add_mode == 1 ? 2.0 : add_mode == 2 ? 1.0 : 0.0)) * nl * cnt * (double)c.N * 8.0);
+    prof_end(c, 7, ev, 8.0 * nl * cnt * (double)c.N * 8.0);
   }
 }
 
@@ -1331,7 +1045,7 @@ void launch_ntt_fwd_rows_mdms_finish(Context& c, const std::vector<double*>& out
     hipEvent_t ev;
     prof_begin(c, 7, &ev);
     hipLaunchKernelGGL(ntt_rowfwd_finish_kernel<3>, dim3((unsigned)(c.N / 4096), l, 2 * cnt), dim3(512), 0,
-                       c.stream, po, pm, pa, pg, none, none, nolv, acc + first * 2 * nE * c.N,
+                       c.stream, po, pm, pa, none, none, nolv, acc + first * 2 * nE * c.N,
                        w + first * 2 * l * c.N, nE, l, 2, 0, masks ? mask_np : 0, m1, m2, c.d_primes,
                        (int)c.log_n, (int)c.log_n - 12, m3, pb);
     COPSE_HIP(hipGetLastError());
@@ -1373,11 +1087,11 @@ void launch_ntt_fwd_rows_ms_finish(Context& c, const std::vector<double*>& out, 
     prof_begin(c, 8, &ev);
     if (mulp)   // the plaintext layer (`add` holds its addends, no post-switch add)
       hipLaunchKernelGGL(ntt_rowfwd_finish_kernel<4>, dim3((unsigned)(c.N / 4096), lmax, np * cnt), dim3(512), 0,
-                         c.stream, po, pi, pa, pg, pw, pt, lv, nullptr, nullptr, 0, 0, np, 0, 0, nullptr, nullptr,
+                         c.stream, po, pi, pa, pw, pt, lv, nullptr, nullptr, 0, 0, np, 0, 0, nullptr, nullptr,
                          c.d_primes, (int)c.log_n, (int)c.log_n - 12, nullptr, pm);
     else
       hipLaunchKernelGGL(ntt_rowfwd_finish_kernel<2>, dim3((unsigned)(c.N / 4096), lmax, np * cnt), dim3(512), 0,
-                         c.stream, po, pi, pa, pg, pw, pt, lv, nullptr, nullptr, 0, 0, np, 0, add ? add_np : 0,
+                         c.stream, po, pi, pa, pw, pt, lv, nullptr, nullptr, 0, 0, np, 0, add ? add_np : 0,
                          nullptr, nullptr, c.d_primes, (int)c.log_n, (int)c.log_n - 12, nullptr, pm);
     COPSE_HIP(hipGetLastError());
     prof_end(c, 8, ev, bytes);
@@ -2009,21 +1723,20 @@ __global__ __launch_bounds__(512, 4) void ks_inner_rows_kernel(KsPack jobs, int 
   const int prime = o < nl ? o : L + 1 + (o - nl);
   const DevPrime pr = P[prime];
   const size_t t0 = (size_t)(lin % gridDim.x) * 4096;
-  const int t = threadIdx.x;
   const int own = o < nl ? o / alpha : -1;   // digit whose own limb this row is
   double a0[8], a1[8];
   // digit j's tile x times its key values, added to the sums (the keys read after x is ready, one
   // polynomial at a time)
   auto mac = [&](int j, double(&x)[8]) {
-    const size_t ko = (size_t)j * key_ds + (size_t)prime * N + t0 + t;
+    const size_t ko = (size_t)j * key_ds + (size_t)prime * N + t0;
     double kv[8];
 #pragma unroll
-    for (int k = 0; k < 8; ++k) kv[k] = gload(jb.kb + ko + 512 * k);
+    for (int k = 0; k < 8; ++k) kv[k] = tile_load(jb.kb + ko, k);
     if (pr.q >= kFwdLazy) red8(x, pr);   // uniform; below, |x| < 20 q and the product is within 0.875 q
 #pragma unroll
     for (int k = 0; k < 8; ++k) a0[k] += mul_lazy(x[k], kv[k], pr.q, pr.qinv);
 #pragma unroll
-    for (int k = 0; k < 8; ++k) kv[k] = gload(jb.ka + ko + 512 * k);
+    for (int k = 0; k < 8; ++k) kv[k] = tile_load(jb.ka + ko, k);
 #pragma unroll
     for (int k = 0; k < 8; ++k) a1[k] += mul_lazy(x[k], kv[k], pr.q, pr.qinv);
   };
@@ -2064,11 +1777,11 @@ __global__ __launch_bounds__(512, 4) void ks_inner_rows_kernel(KsPack jobs, int 
   if (own >= 0) {
     double x[8];
 #pragma unroll
-    for (int k = 0; k < 8; ++k) x[k] = gload(jb.in + (size_t)o * N + t0 + t + 512 * k);
+    for (int k = 0; k < 8; ++k) x[k] = tile_load(jb.in + (size_t)o * N + t0, k);
     if (jb.in_b != nullptr) {
 #pragma unroll
       for (int k = 0; k < 8; ++k)
-        x[k] = mul_lazy(x[k], gload(jb.in_b + (size_t)o * N + t0 + t + 512 * k), pr.q, pr.qinv);
+        x[k] = mul_lazy(x[k], tile_load(jb.in_b + (size_t)o * N + t0, k), pr.q, pr.qinv);
     }
     mac(own, x);
   }
@@ -2076,17 +1789,15 @@ __global__ __launch_bounds__(512, 4) void ks_inner_rows_kernel(KsPack jobs, int 
     double u0[8], u1[8];
 #pragma unroll
     for (int k = 0; k < 8; ++k) {
-      const size_t c = t0 + t + 512 * k;
-      u0[k] = gload(jb.top + (size_t)o * N + c);
-      u1[k] = gload(jb.top + ((size_t)nl + o) * N + c);
+      u0[k] = tile_load(jb.top + (size_t)o * N + t0, k);
+      u1[k] = tile_load(jb.top + ((size_t)nl + o) * N + t0, k);
     }
     if (jb.top_b != nullptr) {
       double b0[8], b1[8];
 #pragma unroll
       for (int k = 0; k < 8; ++k) {
-        const size_t c = t0 + t + 512 * k;
-        b0[k] = gload(jb.top_b + (size_t)o * N + c);
-        b1[k] = gload(jb.top_b + ((size_t)nl + o) * N + c);
+        b0[k] = tile_load(jb.top_b + (size_t)o * N + t0, k);
+        b1[k] = tile_load(jb.top_b + ((size_t)nl + o) * N + t0, k);
       }
 #pragma unroll
       for (int k = 0; k < 8; ++k) ks_tensor_top(u0[k], u1[k], b0[k], b1[k], pr);
@@ -2117,9 +1828,8 @@ __global__ __launch_bounds__(512, 4) void ks_inner_rows_kernel(KsPack jobs, int 
   }   // else signed, within q/2: the finish that reads them takes any representative below 2 q
 #pragma unroll
   for (int k = 0; k < 8; ++k) {
-    const size_t c = t0 + t + 512 * k;
-    jb.acc[(size_t)o * N + c] = a0[k];
-    jb.acc[((size_t)nE + o) * N + c] = a1[k];
+    tile_store(jb.acc + (size_t)o * N + t0, k, a0[k]);
+    tile_store(jb.acc + ((size_t)nE + o) * N + t0, k, a1[k]);
   }
 }
 

@@ -67,6 +67,17 @@ __device__ __forceinline__ double canon(double x, double q) { return __fma_rn(x 
 __device__ __forceinline__ double gload(const double* p) {
   return *(const __attribute__((address_space(1))) double*)(p);
 }
+// A pointer that is the same for the whole wave, kept in scalar registers: without this the compiler adds constant
+// offsets beyond the instruction's range to a 64-bit address in every lane.
+template <class T>
+__device__ __forceinline__ T* uniform(T* p) {
+  asm("" : "+s"(p));
+  return p;
+}
+// global load from a uniform base and a 32-bit byte offset per lane
+__device__ __forceinline__ double gload_off(const double* p, uint32_t bytes) {
+  return *(const __attribute__((address_space(1))) double*)((const char*)p + (size_t)bytes);
+}
 // A load of a value that is uniform across the wave from a table no kernel writes (twiddles, row
 // descriptors, primes, conversion constants): read through the constant address space, so it is a scalar
 // load into scalar registers.

@@ -34,13 +34,14 @@ def same(exported, oct_):
         assert a.shape == b.shape and (a == b).all()
 
 
-def evaluate_groups(C, shape, seed, log_n, bits, alpha, enc, groups, n1=(0, 0), oracle_groups=1):
+def evaluate_groups(C, shape, seed, log_n, bits, alpha, enc, groups, n1=(0, 0), oracle_groups=1, spare=0):
     """`groups` query groups in one call on a chain whose data, q_0 and special primes lie just below 2^bits
-    (a triple): the first oracle_groups results equal the oracle's bit for bit, every result its evaluation
+    (a triple), with `spare` levels that the circuit leaves over: the first oracle_groups results equal the oracle's bit for bit, every result its evaluation
     alone, every label the plain forest's."""
     text = synth.gen_forest_text(shape, seed)
     oc = OC.compile_forest(text, shape.n_features, shape.precision)
     need = CI.seccomp_depth(shape.precision) + 2 + (math.ceil(math.log2(oc.d)) if oc.d > 1 else 0)
+    need += spare
     data, q0, sp = (1 << b for b in bits)
     ctx = C.Context(log_n, need + 1, q0, data, alpha, sp)
     sc = B.BGV(nt.make_chain(log_n, T, need + 1, q0, data, alpha, sp))
@@ -142,3 +143,18 @@ def test_slots_are_taken_modulo_t(C):
     big[::3] += np.uint64(T) * np.uint64(281470681743361 - 1)   # up to just below 2^64
     a, b = (ctx.export(ctx.encrypt_slots(keys, s, 1, b"\x19" * 32, 7))[0] for s in (v, big))
     assert all((x == y).all() for x, y in zip(a["polys"], b["polys"]))
+
+
+# one to eight digits per key switch (alpha 1: one prime each)
+@pytest.mark.parametrize("log_n,alpha,precision,depth,spare",
+                         [(13, 1, 3, 2, 0), (13, 2, 4, 3, 0), (13, 4, 4, 3, 1), (14, 3, 3, 2, 0), (15, 4, 3, 2, 0)])
+@pytest.mark.parametrize("groups", [1, 3])
+def test_rotations_by_digit_count(C, log_n, alpha, precision, depth, spare, groups):
+    evaluate_groups(C, synth.ForestShape(3, depth, 1.0, 3, precision, 3), 73, log_n, (42, 48, 48), alpha, False, groups,
+                    spare=spare)
+
+
+def test_rotations_with_nine_digits(C):
+    """More digits than the fused rotation takes (a chain whose switches are not merged, so that only rotations
+    remain): the separate passes."""
+    evaluate_groups(C, synth.ForestShape(1, 1, 1.0, 3, 1, 3), 73, 13, (48, 44, 48), 1, False, 2, spare=7)
