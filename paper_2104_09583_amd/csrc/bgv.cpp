@@ -79,6 +79,10 @@ Context::~Context() {
   for (auto& kv : row_tables) (void)hipFree(kv.second);
   for (double* p : tables) (void)hipFree(p);
   if (d_primes) (void)hipFree(d_primes);
+  for (int k = 0; k < 2; ++k) {
+    if (export_done[k]) (void)hipEventDestroy(export_done[k]);
+    if (export_slot[k]) (void)hipHostFree(export_slot[k]);
+  }
   pool.reset();
   if (own_stream) (void)hipStreamDestroy(own_stream);
 }

@@ -600,19 +600,10 @@ int copse_cts_export(copse_ctx* ctx, const copse_cts* cts, uint64_t* buf, size_t
     if (cap < total) fail(COPSE_EINVAL, "export buffer too small");
     for (auto& ct : cts->v)
       if (ct->n != c.N || ct->level > c.L) fail(COPSE_EINVAL, "ciphertext of another ring or chain");
-    // converted to words on the device, copied straight into the caller's buffer
+    std::vector<const Ct*> list;
+    for (auto& ct : cts->v) list.push_back(ct.get());
     StreamWait wait{c.stream};
-    size_t off = 0;
-    for (auto& ct : cts->v) {
-      DBuf words = ct_words(c, *ct);
-      buf[off++] = (uint64_t)ct->npolys;
-      buf[off++] = (uint64_t)ct->level;
-      buf[off++] = (uint64_t)c.N;
-      buf[off++] = 0;
-      COPSE_HIP(hipMemcpyAsync(buf + off, words.get(), words.size() * 8, hipMemcpyDeviceToHost, c.stream));
-      off += words.size();
-    }
-    COPSE_HIP(hipStreamSynchronize(c.stream));
+    export_cts(c, list, buf);
   });
 }
 

@@ -205,6 +205,11 @@ struct Context {
   std::map<std::string, int2*> call_rows;
   std::vector<std::vector<int2>> call_rows_host;
   std::vector<DBuf> call_row_bufs;
+  // pinned staging of copse_cts_export, allocated by the first export and kept: two slots of at most
+  // kExportSlotMax bytes
+  char* export_slot[2] = {nullptr, nullptr};
+  size_t export_slot_bytes = 0;
+  hipEvent_t export_done[2] = {nullptr, nullptr};
   Tuning tune;                    // active for the evaluation being issued
   std::vector<TuneEntry> tune_table;
   // the table's entry for an evaluation of `batch` query groups of a plaintext or encrypted model (defaults
@@ -567,8 +572,8 @@ CtPtr op_rotate(Context& c, const Keys& k, const Ct& a, int32_t r);
 // sum of rotations of same-level ciphertexts with one ModDown (see bgv.cpp)
 CtPtr op_rotate_sum(Context& c, const Keys& k, const std::vector<std::pair<const Ct*, int32_t>>& items);
 
-// (wire.hip) a ciphertext's coefficient words on the device, and a ciphertext from words in host memory
-DBuf ct_words(Context& c, const Ct& a);
+// (wire.hip) ciphertexts in the export format to caller memory, and a ciphertext from words in host memory
+void export_cts(Context& c, const std::vector<const Ct*>& cts, uint64_t* buf);
 CtPtr ct_from_words(Context& c, const uint64_t* words, int level, int npolys, int* bad);
 
 }  // namespace copse
