@@ -167,7 +167,7 @@ KSTables& Context::kstab(int level) {
     T->digits.push_back(std::move(dg));
   }
   // ModDown constants
-  std::vector<double> mdm, mdmat, pinv, tpinv;
+  std::vector<double> mdm, mdmat, pinv, tpinv, pmod, tpmod;
   for (int r = 0; r < alpha; ++r) {
     uint64_t p = primes[L + 1 + r];
     uint64_t hat = 1;
@@ -190,11 +190,15 @@ KSTables& Context::kstab(int level) {
     uint64_t pi = invmod(P, q);
     pinv.push_back((double)pi);
     tpinv.push_back((double)mulmod(t % q, pi, q));
+    pmod.push_back((double)P);
+    tpmod.push_back((double)mulmod(t % q, P, q));
   }
   T->d_md_mult = upload(T->owned, mdm);
   T->d_md_mat = upload(T->owned, mdmat);
   T->d_md_pinv = upload(T->owned, pinv);
   T->d_md_tpinv = upload(T->owned, tpinv);
+  T->d_md_p = upload(T->owned, pmod);
+  T->d_md_tp = upload(T->owned, tpmod);
   if (level >= 1) {
     uint64_t ql = primes[level];
     std::vector<double> ms = {(double)level, (double)invmod(t % ql, ql)};

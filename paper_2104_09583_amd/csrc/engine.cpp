@@ -394,7 +394,16 @@ static void ks_batch(Context& c, int level, const std::vector<const double*>& in
                           inputs_b ? (*inputs_b)[rq.input] : nullptr, inputs_b ? rq.add_b : nullptr});
   }
   // the fused inner product also runs the ModDown's inverse row pass on the rows that need it
-  if (no_auto) launch_ks_inner_rows(c, jobs, D, nE, level, (size_t)Lt * N, merge ? T.mm_ptop : 0.0, merge ? nl - 1 : nl);
+  const int back = merge ? nl - 1 : nl;   // first row that the ModDown transforms back
+  // The data rows' inner products inside the finish: 9 instead of 15 rows move per product and limb, but their
+  // transforms then stand between the column pass and the finish instead of beside the special rows' ones.  Where the
+  // finish fills the chip twice (two workgroups of it on each of 256 units) the bytes count: 16 groups of the encrypted
+  // 8-tree forest 20.7 to 19.6 ms, of the 32-tree forest 16.6 to 16.2, five 16-bit groups 6.19 to 5.88; near it (800
+  // and 960 workgroups: one 16-bit query, three groups of the 16-tree forest) both are even; below it the longer chain
+  // does (320: one query of the 16-tree forest 1.34 to 1.36 ms; the one-tree forest 0.526 to 0.568).
+  const bool inline_data = no_auto && (size_t)(N / 4096) * back * R >= 1024;
+  if (no_auto)
+    launch_ks_inner_rows(c, jobs, D, nE, level, (size_t)Lt * N, merge ? T.mm_ptop : 0.0, back, inline_data ? back : 0);
   else launch_ks_inner2(c, jobs, D, nE, level, (size_t)Lt * N, merge ? T.mm_ptop : 0.0);
   if (merge) {
     // ModDown by P and switch by q_l in one pass: the top data row (now y_l + P a_l) joins the special rows
@@ -418,6 +427,14 @@ static void ks_batch(Context& c, int level, const std::vector<const double*>& in
     launch_bridge(c, 2, w.get(), rows_cached(c, "mdmsout:" + std::to_string(level), outr), l, acc.get(),
                   rows_cached(c, "mdmsin:" + std::to_string(level), inr), c.alpha + 1, T.d_mm_mult, T.d_mm_mat,
                   2 * R, (size_t)nE * N, (size_t)l * N);
+    if (inline_data) {
+      std::vector<KsRelin> rj;
+      for (int q = 0; q < R; ++q)
+        rj.push_back(KsRelin{jobs[q].in, jobs[q].in_b, jobs[q].ext, jobs[q].kb, jobs[q].ka, reqs[q].add, jobs[q].top_b,
+                             reqs[q].out});
+      launch_ks_relin_finish(c, rj, w.get(), T.d_mm_m1, T.d_md_tp, T.d_md_p, l, D, nE, level, (size_t)Lt * N);
+      return;
+    }
     std::vector<double*> outs;
     std::vector<const double*> adds, adds_b;
     for (auto& rq : reqs) {
@@ -466,6 +483,13 @@ static void ks_batch(Context& c, int level, const std::vector<const double*>& in
     launch_bridge(c, 0, zh.get(), rows_cached(c, "mdout:" + std::to_string(level), outr), nl, acc.get(),
                   rows_cached(c, "mdin:" + std::to_string(level), inr), c.alpha, T.d_md_mult, T.d_md_mat, 2 * R,
                   (size_t)nE * N, (size_t)nl * N);
+    if (inline_data) {
+      std::vector<KsRelin> rj;
+      for (int q = 0; q < R; ++q)
+        rj.push_back(KsRelin{jobs[q].in, nullptr, jobs[q].ext, jobs[q].kb, jobs[q].ka, reqs[q].add, nullptr, reqs[q].out});
+      launch_ks_relin_finish(c, rj, zh.get(), T.d_md_pinv, nullptr, T.d_md_p, nl, D, nE, level, (size_t)Lt * N);
+      return;
+    }
     launch_ntt_fwd_rows_md_finish(c, outs, adds, acc.get(), zh.get(), nE, nl, T.d_md_pinv, T.d_md_tpinv);
     return;
   } else {

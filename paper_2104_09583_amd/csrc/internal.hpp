@@ -248,6 +248,8 @@ struct KSTables {
   double* d_md_mat = nullptr;    // [alpha][nl] (P/p_r) mod q_i
   double* d_md_pinv = nullptr;   // [nl] P^-1 mod q_i
   double* d_md_tpinv = nullptr;  // [nl] t P^-1 mod q_i
+  double* d_md_p = nullptr;      // [nl] P mod q_i
+  double* d_md_tp = nullptr;     // [nl] t P mod q_i
   // Modulus switch from this level to level-1
   double* d_ms = nullptr;        // [4 + 2*level]: q_l, t^-1 mod q_l, then per i<l: q_l^-1, t q_l^-1
   // ModDown merged with the switch to level-1 (level >= 1): conversion multipliers of the special rows
@@ -429,9 +431,10 @@ void launch_ks_inner2(Context& c, const std::vector<KsJob2>& jobs, int D, int nE
                       double ptop = 0.0);
 // the same for jobs without automorphism (g = 1) whose ext holds the ModUp rows after the column stages
 // only: the forward row pass is done inside (relinearizations); extended rows inv_from.. nE - 1 of acc
-// are written after the inverse row pass (the rows the ModDown transforms back; nE: none)
+// are written after the inverse row pass (the rows the ModDown transforms back; nE: none), and only rows from
+// first_row on are formed
 void launch_ks_inner_rows(Context& c, const std::vector<KsJob2>& jobs, int D, int nE, int level, size_t key_ds,
-                          double ptop, int inv_from);
+                          double ptop, int inv_from, int first_row = 0);
 // Hoisted rotations on the rings of the split transform (keyswitch.hip), jobs of one level and digit count D <= 8:
 // the special rows of the inner products with their inverse row pass, to acc [jobs][2][alpha][N], and, from the
 // converted rows w [jobs][2][nl][N], the ModDown's finish with the data rows' inner products inside.
@@ -448,6 +451,21 @@ void launch_ks_rot_special(Context& c, const std::vector<KsRot>& jobs, double* a
                            size_t key_ds);
 void launch_ks_rot_finish(Context& c, const std::vector<KsRot>& jobs, const double* w, const double* pinv, int D,
                           int nE, int level, size_t key_ds);
+// Data rows of relinearizations (keyswitch.hip): from the converted rows w [jobs][2][nout][N], the forward row passes
+// of w and of the other digits' ModUp rows (left after the column stages), the inner products, the addend and the
+// finish.  nout: level + 1 limbs (ModDown alone) or level (merged with the switch); m1, cw, ca per limb as there.
+struct KsRelin {
+  const double* in;      // as KsJob2: the relinearized polynomial, or a1 with in_b = b1
+  const double* in_b;
+  const double* ext;
+  const double* kb;
+  const double* ka;
+  const double* add;     // the 2 polys of the addend, or the ciphertext a with add_b = b
+  const double* add_b;
+  double* out;           // 2 polys of nout limbs
+};
+void launch_ks_relin_finish(Context& c, const std::vector<KsRelin>& jobs, const double* w, const double* m1,
+                            const double* cw, const double* ca, int nout, int D, int nE, int level, size_t key_ds);
 // Key-switch inner products summed per output (giant steps of a product, one ModDown for their sum).
 // Product p has G outputs (batch elements) that share its key sequence: output (p, b) accumulates, over the
 // product's steps s, sum_j digit_j(sigma_{g_s}(in_{s,b})) key_{s,j} in the extended basis, plus P times the

@@ -1708,7 +1708,7 @@ void launch_ks_inner2(Context& c, const std::vector<KsJob2>& jobs, int D, int nE
 // run as one pair.
 __global__ __launch_bounds__(512, 4) void ks_inner_rows_kernel(KsPack jobs, int D, int nE, int nl, int L, int alpha,
                                                                int logN, int S1, size_t key_ds, const DevPrime* P,
-                                                               double ptop, int inv_from) {
+                                                               double ptop, int inv_from, int njobs) {
   __shared__ double sh[kLdsTile4], sh2[kLdsTile4];
   const size_t N = (size_t)1 << logN;
   // block order: the hardware deals consecutive workgroups to the eight XCDs in turn, so with the tile
@@ -1718,8 +1718,8 @@ __global__ __launch_bounds__(512, 4) void ks_inner_rows_kernel(KsPack jobs, int 
   // ones against two) start first instead of forming the launch's tail
   const unsigned lin = blockIdx.x + gridDim.x * (blockIdx.y + gridDim.y * blockIdx.z);
   const unsigned rest = lin / gridDim.x;
-  const int o = (int)gridDim.y - 1 - (int)(rest / gridDim.z);
-  const KsJob2 jb = jobs.j[rest % gridDim.z];
+  const int o = nE - 1 - (int)(rest / (unsigned)njobs);
+  const KsJob2 jb = jobs.j[rest % (unsigned)njobs];
   const int prime = o < nl ? o : L + 1 + (o - nl);
   const DevPrime pr = P[prime];
   const size_t t0 = (size_t)(lin % gridDim.x) * 4096;
@@ -1834,7 +1834,7 @@ __global__ __launch_bounds__(512, 4) void ks_inner_rows_kernel(KsPack jobs, int 
 }
 
 void launch_ks_inner_rows(Context& c, const std::vector<KsJob2>& jobs, int D, int nE, int level, size_t key_ds,
-                          double ptop, int inv_from) {
+                          double ptop, int inv_from, int first_row) {
   if (c.log_n < 13) fail(COPSE_EINVAL, "internal: split transform needs N >= 8192");
   if (D > 8) fail(COPSE_EINVAL, "internal: too many digits for the fused inner product");
   const size_t per = c.tune.ks_jobs > 0 ? (size_t)std::min(c.tune.ks_jobs, KsPack::kMax) : KsPack::kMax;
@@ -1847,9 +1847,9 @@ void launch_ks_inner_rows(Context& c, const std::vector<KsJob2>& jobs, int D, in
     }
     hipEvent_t ev;
     prof_begin(c, 15, &ev);
-    hipLaunchKernelGGL(ks_inner_rows_kernel, dim3((unsigned)(c.N / 4096), nE, cnt), dim3(512), 0, c.stream, pk, D, nE,
-                       level + 1, c.L, c.alpha, (int)c.log_n, (int)c.log_n - 12, key_ds, c.d_primes, ptop,
-                       inv_from);
+    hipLaunchKernelGGL(ks_inner_rows_kernel, dim3((unsigned)(c.N / 4096), nE - first_row, cnt), dim3(512), 0, c.stream,
+                       pk, D, nE, level + 1, c.L, c.alpha, (int)c.log_n, (int)c.log_n - 12, key_ds, c.d_primes, ptop,
+                       inv_from, cnt);
     COPSE_HIP(hipGetLastError());
     int keys = 0;
     for (int k = 0; k < cnt; ++k) {

@@ -172,4 +172,139 @@ void launch_ks_rot_finish(Context& c, const std::vector<KsRot>& jobs, const doub
   }
 }
 
+// ------------------------------------------------------------------ relinearizations
+struct RelinPack {
+  static constexpr int kMax = 32;   // 32 x 64 B of kernel arguments
+  KsRelin j[kMax];
+};
+
+// Data row i of both polynomials of one job.  The finish is out_k = (sum_k - cw w_k + ca add_k) m1 (cw = t, ca = P,
+// m1 = P^-1 for a ModDown; t P, P and (P q_l)^-1 merged with the switch), so the sums start from -cw w_k + ca add_k
+// and everything stays in registers: the inner products are never written, and of a product's operands each row is
+// read once for the addend (a0 b0, a0 b1 + a1 b0) and for the row's own digit a1 b1.  Both rows w are transformed as
+// one pair, the other digits' rows one at a time with the sums live (128 registers, two workgroups per compute unit).
+__global__ __launch_bounds__(512, 4) void ks_relin_finish_kernel(RelinPack jobs, int njobs,
+                                                                 const double* __restrict__ w,
+                                                                 const double* __restrict__ m1,
+                                                                 const double* __restrict__ cw,
+                                                                 const double* __restrict__ ca, double t_mod, int nout,
+                                                                 int D, int nE, int nl, int alpha, int logN,
+                                                                 size_t key_ds, const DevPrime* __restrict__ P) {
+  __shared__ double sh[kLdsTile4], sh2[kLdsTile4];
+  const size_t N = (size_t)1 << logN;
+  const unsigned lin = blockIdx.x + gridDim.x * (blockIdx.y + gridDim.y * blockIdx.z);
+  const unsigned rest = lin / gridDim.x;
+  const size_t t0 = (size_t)(lin % gridDim.x) * 4096;
+  const int job = (int)(rest % (unsigned)njobs), i = (int)(rest / (unsigned)njobs);
+  const KsRelin jb = jobs.j[job];
+  const DevPrime pr = cload_prime(P + i);
+  const int S1 = logN - 12, own = i / alpha;
+  const size_t ro = (size_t)i * N + t0, ps = (size_t)nl * N;
+  double a0[8], a1[8];
+  const double* w0 = w + ((size_t)job * 2 * nout + i) * N + t0;
+  row4_fwd_tile2(w0, w0 + (size_t)nout * N, t0, S1, pr, sh, sh2, a0, a1);
+  const double c1 = cw != nullptr ? cload(cw + i) : t_mod, c2 = cload(ca + i);
+#pragma unroll
+  for (int k = 0; k < 8; ++k) {
+    a0[k] = -mul_lazy(a0[k], c1, pr.q, pr.qinv);
+    a1[k] = -mul_lazy(a1[k], c1, pr.q, pr.qinv);
+  }
+  auto mac = [&](int j, double(&x)[8]) {
+    const size_t ko = (size_t)j * key_ds + ro;
+    double kv[8];
+#pragma unroll
+    for (int k = 0; k < 8; ++k) kv[k] = tile_load(jb.kb + ko, k);
+    if (pr.q >= kFwdLazy) red8(x, pr);   // uniform
+#pragma unroll
+    for (int k = 0; k < 8; ++k) a0[k] += mul_lazy(x[k], kv[k], pr.q, pr.qinv);
+#pragma unroll
+    for (int k = 0; k < 8; ++k) kv[k] = tile_load(jb.ka + ko, k);
+#pragma unroll
+    for (int k = 0; k < 8; ++k) a1[k] += mul_lazy(x[k], kv[k], pr.q, pr.qinv);
+  };
+  // the addend, and the row's own digit
+  {
+    double x[8];
+    const double* d0 = jb.add + ro;
+    const double* d1 = d0 + ps;
+    if (jb.add_b != nullptr) {   // uniform
+      const double* e0 = jb.add_b + ro;
+      const double* e1 = e0 + ps;
+      // in an order that keeps three rows live
+      double u[8], v[8], y[8];
+#pragma unroll
+      for (int k = 0; k < 8; ++k) {
+        u[k] = tile_load(d0, k);
+        v[k] = tile_load(e0, k);
+      }
+#pragma unroll
+      for (int k = 0; k < 8; ++k)
+        a0[k] += mul_lazy(mul_lazy(u[k], v[k], pr.q, pr.qinv), c2, pr.q, pr.qinv);
+#pragma unroll
+      for (int k = 0; k < 8; ++k) y[k] = tile_load(e1, k);
+#pragma unroll
+      for (int k = 0; k < 8; ++k) u[k] = mul_lazy(u[k], y[k], pr.q, pr.qinv);
+#pragma unroll
+      for (int k = 0; k < 8; ++k) x[k] = tile_load(d1, k);
+#pragma unroll
+      for (int k = 0; k < 8; ++k) {
+        a1[k] += mul_lazy(u[k] + mul_lazy(x[k], v[k], pr.q, pr.qinv), c2, pr.q, pr.qinv);
+        x[k] = mul_lazy(x[k], y[k], pr.q, pr.qinv);
+      }
+    } else {
+      double u[8], v[8];
+#pragma unroll
+      for (int k = 0; k < 8; ++k) {
+        u[k] = tile_load(d0, k);
+        v[k] = tile_load(d1, k);
+        x[k] = tile_load(jb.in + ro, k);
+      }
+#pragma unroll
+      for (int k = 0; k < 8; ++k) {
+        a0[k] += mul_lazy(u[k], c2, pr.q, pr.qinv);
+        a1[k] += mul_lazy(v[k], c2, pr.q, pr.qinv);
+      }
+    }
+    mac(own, x);
+  }
+  for (int j = 0; j < D; ++j) {   // uniform
+    if (j == own) continue;
+    double x[8];
+    lds_barrier();   // the tile buffer's previous use is over in every wave
+    row4_fwd_tile(jb.ext + ((size_t)j * nE + i) * N + t0, t0, S1, pr, sh, x);
+    mac(j, x);
+  }
+  // at most eight digits: |a| < 10 q, the product below 2.5 q
+  const double m = cload(m1 + i);
+  double* o = jb.out + ro;
+#pragma unroll
+  for (int k = 0; k < 8; ++k) {
+    tile_store(o, k, canon(reduce_sym(mul_lazy(a0[k], m, pr.q, pr.qinv), pr.q, pr.qinv), pr.q));
+    tile_store(o + (size_t)nout * N, k, canon(reduce_sym(mul_lazy(a1[k], m, pr.q, pr.qinv), pr.q, pr.qinv), pr.q));
+  }
+}
+
+void launch_ks_relin_finish(Context& c, const std::vector<KsRelin>& jobs, const double* w, const double* m1,
+                            const double* cw, const double* ca, int nout, int D, int nE, int level, size_t key_ds) {
+  check_rot(c, D);
+  if (nout < 1 || nout > level + 1) fail(COPSE_EINVAL, "internal: relinearization without output limbs");
+  const size_t per = c.tune.ks_jobs > 0 ? (size_t)std::min(c.tune.ks_jobs, RelinPack::kMax) : RelinPack::kMax;
+  for (size_t first = 0; first < jobs.size(); first += per) {
+    const int cnt = (int)std::min<size_t>(per, jobs.size() - first);
+    RelinPack pk;
+    double rows = 0;
+    for (int k = 0; k < cnt; ++k) {
+      pk.j[k] = jobs[first + k];
+      rows += D - 1 + 2 + 2 + (pk.j[k].add_b != nullptr ? 4 : 3);
+    }
+    hipEvent_t ev;
+    prof_begin(c, 7, &ev);
+    hipLaunchKernelGGL(ks_relin_finish_kernel, dim3((unsigned)(c.N / 4096), nout, cnt), dim3(512), 0, c.stream, pk, cnt,
+                       w + first * 2 * nout * c.N, m1, cw, ca, (double)c.t, nout, D, nE, level + 1, c.alpha,
+                       (int)c.log_n, key_ds, c.d_primes);
+    COPSE_HIP(hipGetLastError());
+    prof_end(c, 7, ev, (rows + 2.0 * D) * nout * (double)c.N * 8.0);
+  }
+}
+
 }  // namespace copse

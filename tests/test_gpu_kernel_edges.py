@@ -158,3 +158,11 @@ def test_rotations_with_nine_digits(C):
     """More digits than the fused rotation takes (a chain whose switches are not merged, so that only rotations
     remain): the separate passes."""
     evaluate_groups(C, synth.ForestShape(1, 1, 1.0, 3, 1, 3), 73, 13, (48, 44, 48), 1, False, 2, spare=7)
+
+
+# jobs x limbs x tiles below and above the count from which a relinearization's finish forms its own inner products,
+# merged with the switch (products) and not (the encrypted model's inner sums), with two and three digits
+@pytest.mark.parametrize("log_n,alpha,enc,groups", [(13, 4, False, 24), (13, 4, False, 64), (14, 2, False, 40),
+                                                    (13, 3, True, 8), (13, 4, True, 33), (14, 3, True, 12)])
+def test_relinearizations_by_workgroup_count(C, log_n, alpha, enc, groups):
+    evaluate_groups(C, synth.ForestShape(3, 3, 0.9, 3, 4, 3), 74, log_n, (42, 48, 48), alpha, enc, groups)
