@@ -142,8 +142,8 @@ size_t copse_ctx_device_bytes(const copse_ctx* ctx);
  * groups of a plaintext model, else 12); mm_waves, batch elements per MatMul
  * workgroup when G is a multiple of 8 (4 or 8; built in 8); ks_jobs,
  * key-switch inner products per launch (1..32; built in 32); bridge_wgs, the
- * workgroup count under which the fused column pass of a base change splits
- * its outputs (built in 512); gsum_b, batch elements per thread of the
+ * workgroup count under which the fused column pass of a base change gives
+ * every output a wave of its own (built in 512); gsum_b, batch elements per thread of the
  * giant-step key-switch sums (4 or 8; built in 8). */
 typedef struct {
   uint32_t log_n, top_level, batch_lo, batch_hi;

@@ -79,7 +79,7 @@ std::vector<SCt> b_modswitch(Context& c, const std::vector<const Ct*>& in,
         std::vector<int2> ir{make_int2(0, l)}, orr;
         for (int i = 0; i < l; ++i) orr.push_back(make_int2(i, i));
         BridgeDesc d{rows_cached(c, "msout:" + std::to_string(l), orr), rows_cached(c, "msin:" + std::to_string(l), ir),
-                     T.d_ms + 1, nullptr, l, 1, 0, 0};
+                     T.d_ms + 1, nullptr, l, 1};
         d.in = top.get() + (size_t)j0 * np * N;
         d.out = w.get() + woff * N;
         d.in_bs = N;
@@ -179,7 +179,7 @@ static std::vector<SCt> b_switch_by(Context& c, const std::vector<const Ct*>& in
       const MsMulti& M = c.ms_multi(l, k);
       const int n_out = l - k + 1;
       auto outs = alloc_batch(c, j1 - j0, l - k, np);
-      BridgeDesc d{M.out_rows, M.in_rows, M.mult, M.mat, n_out, k, 0, 0};
+      BridgeDesc d{M.out_rows, M.in_rows, M.mult, M.mat, n_out, k};
       d.in = top.get() + (size_t)j0 * rpj * N;
       d.out = w.get() + woff * N;
       d.in_bs = (size_t)kmax * N;
@@ -228,7 +228,7 @@ static std::vector<SCt> b_ptlayer_switch(Context& c, const std::vector<const dou
   std::vector<int2> ir{make_int2(0, l)}, orr;
   for (int i = 0; i < l; ++i) orr.push_back(make_int2(i, i));
   BridgeDesc d{rows_cached(c, "msout:" + std::to_string(l), orr), rows_cached(c, "msin:" + std::to_string(l), ir),
-               T.d_ms + 1, nullptr, l, 1, 0, 0};
+               T.d_ms + 1, nullptr, l, 1};
   d.in = top.get();
   d.out = w.get();
   d.in_bs = N;
@@ -299,7 +299,7 @@ static DBuf modup_batch(Context& c, int level, const std::vector<const double*>&
     std::vector<BridgeDesc> ds;
     for (int j = 0; j < D; ++j) {
       auto& dg = T.digits[j];
-      ds.push_back(BridgeDesc{dg.d_out_rows, dg.d_in_rows, dg.d_mult, dg.d_mat, (int)dg.targets.size(), dg.count, 0, 0});
+      ds.push_back(BridgeDesc{dg.d_out_rows, dg.d_in_rows, dg.d_mult, dg.d_mat, (int)dg.targets.size(), dg.count});
       if ((int)ds.size() == BridgeSet::kMax || j == D - 1) {
         launch_bridge_set(c, 0, ext.get(), cf.get(), ds, I, (size_t)nl * N, (size_t)D * nE * N);
         ds.clear();

@@ -169,7 +169,7 @@ struct Tuning {
   int mm_cap = 0;       // giant groups per register tile of the MatMul inner sums (4..32)
   int mm_waves = 0;     // batch elements per MatMul workgroup when the batch is a multiple of 8 (4 or 8)
   int ks_jobs = 0;      // key-switch inner products per launch (1..32)
-  int bridge_wgs = 0;   // workgroup count under which the fused column pass splits its outputs (64..8192)
+  int bridge_wgs = 0;   // workgroup count under which the fused column pass gives every output a wave (64..8192)
   int gsum_b = 0;       // batch elements per thread of the giant-step sums (4 or 8)
 };
 struct TuneEntry {
@@ -317,8 +317,7 @@ void launch_ntt_fwd_rows_ms_finish(Context& c, const std::vector<double*>& out, 
                                    const std::vector<const double*>* add, int add_np,
                                    const std::vector<const double*>* mulp = nullptr);
 // One coefficient map of the fused column pass: rows of the input block (index, prime), rows of the
-// output block, per-input multipliers and the [n_in][n_out] matrix (mode 0).  chunk0 / ochunk are set by
-// the launcher.  Several maps over the same input and output blocks (the digits of a ModUp) run as one
+// output block, per-input multipliers and the [n_in][n_out] matrix (mode 0).  Several maps over the same input and output blocks (the digits of a ModUp) run as one
 // launch.
 struct BridgeDesc {
   const int2* out_rows;
@@ -326,7 +325,6 @@ struct BridgeDesc {
   const double* mult;
   const double* mat;
   int n_out, n_in;
-  int chunk0, ochunk;
   // set by launch_bridge_set when left empty: the blocks and batch of this map
   const double* in = nullptr;
   double* out = nullptr;

@@ -655,11 +655,13 @@ void launch_ntt_inv(Context& c, double* base, const int2* rows, int nrows) {
 //            the finish then computes (c - t out) D_k^-1.
 // The values handed to the forward stages are any representatives of the residues (|v| <= q/2), so the
 // transform's canonical output is the same as that of the unfused steps.
-// grid: x over column groups of 64, y over chunks of ochunk outputs (small batches: more blocks, the
-// inputs' stages recomputed per chunk), z over the batch (in_bs / out_bs apart).
+// grid: x over column groups of 64, y over the maps (digits), z over the batch (in_bs / out_bs apart).
 constexpr int kBridgeIn = 4;
-// A workgroup is 64 columns x 4 waves: wave k runs the inverse stages of input row k (k < n_in) and
-// leaves [coef * mult_k] in LDS; then the four waves take the outputs of the block's chunk in turn.
+// A workgroup is 64 columns x W waves: wave k runs the inverse stages of input rows k, k + W, ... and leaves
+// [coef * mult_k] in LDS; then the waves take the outputs in turn.  W is the launcher's: four, or one output per wave
+// where the launch does not fill the chip.  (Five to eight waves for an even share of the outputs ran 15% slower at 16
+// groups: fewer workgroups then cover each other's loads.)  The single-query work is bound by its chain of scalar loads
+// and one wave's output after another, the batched by HBM (5.3 TB/s) and fp64 issue (77%) at once.
 // What a wave needs for one output row besides the LDS values: its place, prime and twiddles and its
 // column of the conversion matrix.  All uniform (scalar registers); loaded one output ahead so that the
 // chain row descriptor -> prime -> twiddles is off the critical path.
@@ -688,7 +690,7 @@ __device__ __forceinline__ BridgeOut<S1> bridge_out_load(const BridgeDesc& d, co
 }
 
 template <int S1, int kMode>
-__global__ __launch_bounds__(256) void ntt_bridge_kernel(BridgeSet set, const DevPrime* __restrict__ P, int logN) {
+__global__ __launch_bounds__(1024) void ntt_bridge_kernel(BridgeSet set, const DevPrime* __restrict__ P, int logN) {
   constexpr int R = 1 << S1;
   // mode 2 has one more input (the top row) than conversion rows
   constexpr int kSlots = kMode == 2 ? kBridgeIn + 1 : kBridgeIn;
@@ -699,24 +701,17 @@ __global__ __launch_bounds__(256) void ntt_bridge_kernel(BridgeSet set, const De
   const int wv = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
   const size_t c = (size_t)blockIdx.x * 64 + lane;
   const bool active = c < C;
-  // the conversion (digit) this block belongs to: set.d[k] owns grid rows [chunk0, next chunk0)
-  int di = 0;
-#pragma unroll
-  for (int k = 1; k < BridgeSet::kMax; ++k)
-    if (k < set.n && (int)blockIdx.y >= set.d[k].chunk0) di = k;
-  const BridgeDesc& d = set.d[di];
+  const BridgeDesc& d = set.d[blockIdx.y];
   if ((int)blockIdx.z >= d.nz) return;   // uniform per workgroup, before the barrier
+  const int nw = (int)(blockDim.x >> 6);
   const int n_in = d.n_in, n_out = d.n_out;
   const double* in = d.in + (size_t)blockIdx.z * d.in_bs;
   double* out = d.out + (size_t)blockIdx.z * d.out_bs;
-  // this wave's outputs: o0 + wv, o0 + wv + 4, ... below o1; the first one's parameters are fetched now
-  const int o0 = ((int)blockIdx.y - d.chunk0) * d.ochunk;
-  const int o1 = min(n_out, o0 + d.ochunk);
-  int o = o0 + wv;
+  // this wave's outputs: wv, wv + nw, ...; the first one's parameters are fetched now
+  int o = wv;
   BridgeOut<S1> cur;
-  if (o < o1) cur = bridge_out_load<S1, kMode>(d, P, o);
-  // input k < n_in is run by wave k % 4
-  for (int ik = wv; ik < n_in && active; ik += 4) {
+  if (o < n_out) cur = bridge_out_load<S1, kMode>(d, P, o);
+  for (int ik = wv; ik < n_in && active; ik += nw) {
     const int2 irow = cload_row(d.in_rows + ik);
     const DevPrime pk = cload_prime(P + irow.y);
     const double* a = in + (size_t)irow.x * N;
@@ -751,8 +746,8 @@ __global__ __launch_bounds__(256) void ntt_bridge_kernel(BridgeSet set, const De
   }
   lds_barrier();
   if (kMode == 3) {
-    // the k lifts of the single switches, one after the other per coefficient; wave w takes rows w, w + 4..
-    for (int r = wv; r < R && active; r += 4) {
+    // the k lifts of the single switches, one after the other per coefficient; the waves share the rows
+    for (int r = wv; r < R && active; r += nw) {
       double z[kBridgeIn];
 #pragma unroll
       for (int m = 0; m < kBridgeIn; ++m) {
@@ -771,30 +766,31 @@ __global__ __launch_bounds__(256) void ntt_bridge_kernel(BridgeSet set, const De
     }
     lds_barrier();
   }
-  if (!active) return;
-  // mode 2: the switch's centered lift v of the top limb, per coefficient of this thread's column
-  double vt[kMode == 2 ? R : 1];
-  if (kMode == 2 && o < o1) {
+  if (kMode == 2) {
+    // the switch's centered lift v of the top limb, once per coefficient (the waves share the rows; each wave for
+    // itself, it was a fifth of the kernel: 645 against 552 us at 16 groups of the 32-tree forest), in place of the top
+    // row
     const int nc = n_in - 1;
     const int2 trow = cload_row(d.in_rows + nc);
     const double ql = cload(&P[trow.y].q), qlinv = cload(&P[trow.y].qinv);
     double mt[kBridgeIn];
 #pragma unroll
     for (int k = 0; k < kBridgeIn; ++k) mt[k] = k < nc ? cload(d.mat + k * (n_out + 1) + n_out) : 0.0;
-#pragma unroll
-    for (int r = 0; r < R; ++r) {
+    for (int r = wv; r < R && active; r += nw) {
       double sl = 0.0;
 #pragma unroll
       for (int k = 0; k < kBridgeIn; ++k)
         if (k < nc) sl += mul_lazy(ys[k][r][lane], mt[k], ql, qlinv);
       // z_r < 2^49, so each lazy product is below 0.6 q_l and |ys_top - sl| < 4 q_l: the symmetric
       // reduction gives the centered representative
-      vt[r] = reduce_sym(ys[nc][r][lane] - sl, ql, qlinv);
+      ys[nc][r][lane] = reduce_sym(ys[nc][r][lane] - sl, ql, qlinv);
     }
+    lds_barrier();
   }
-  for (; o < o1; o += 4) {
+  if (!active) return;
+  for (; o < n_out; o += nw) {
     BridgeOut<S1> nxt;
-    if (o + 4 < o1) nxt = bridge_out_load<S1, kMode>(d, P, o + 4);
+    if (o + nw < n_out) nxt = bridge_out_load<S1, kMode>(d, P, o + nw);
     const double q = cur.q, qinv = cur.qinv;
     // below 2^46 the sums (< 8 q) pass unreduced through the column stages and into the row pass
     const bool lazy = q < kFwdLazy;
@@ -808,7 +804,7 @@ __global__ __launch_bounds__(256) void ntt_bridge_kernel(BridgeSet set, const De
         for (int k = 0; k < kBridgeIn; ++k)
           if (k < nc) acc += mul_lazy(ys[k][r][lane], cur.m[k], q, qinv);
         // mode 2: |v| <= q_l / 2 < 2 q_o, so the sum stays below 8 q_o
-        if (kMode == 2) acc += vt[r];
+        if (kMode == 2) acc += ys[nc][r][lane];
         x[r] = acc;
       } else {
         x[r] = reduce_sym(ys[0][r][lane], q, qinv);
@@ -850,7 +846,7 @@ void launch_bridge_set(Context& c, int mode, double* out_base, const double* in_
   for (size_t first = 0; first < descs.size(); first += BridgeSet::kMax) {
     BridgeSet set{};
     set.n = (int)std::min<size_t>(BridgeSet::kMax, descs.size() - first);
-    int rows_y = 0, zmax = 0;
+    int zmax = 0, omax = 0;
     double bytes = 0;
     for (int k = 0; k < set.n; ++k) {
       BridgeDesc d = descs[first + k];
@@ -868,23 +864,20 @@ void launch_bridge_set(Context& c, int mode, double* out_base, const double* in_
       if (mode == 2 && d.n_in < 2) fail(COPSE_EINVAL, "internal: merged switch needs special rows and the top row");
       if (mode == 3 && d.n_in < 1) fail(COPSE_EINVAL, "internal: switch by no prime");
       if (d.n_out <= 0) fail(COPSE_EINVAL, "internal: conversion without outputs");
-      // at least ~512 workgroups (2048 waves) when the batch is small, by splitting the outputs into chunks
-      // of at least 4 (one per wave)
-      int chunks = 1;
-      const size_t target = c.tune.bridge_wgs > 0 ? (size_t)c.tune.bridge_wgs : 512;
-      while (chunks * 8 <= d.n_out && (size_t)xb * d.nz * chunks * set.n < target) chunks *= 2;
-      d.ochunk = (d.n_out + chunks - 1) / chunks;
-      chunks = (d.n_out + d.ochunk - 1) / d.ochunk;
-      d.chunk0 = rows_y;
-      rows_y += chunks;
       zmax = std::max(zmax, d.nz);
+      omax = std::max(omax, d.n_out);
       set.d[k] = d;
       bytes += (double)(d.n_out + d.n_in) * d.nz * (double)c.N * 8.0;   // inputs counted once
     }
     if (zmax == 0) continue;
     hipEvent_t ev;
     prof_begin(c, 5, &ev);
-    dim3 grid(xb, rows_y, zmax), blk(256);
+    // below two workgroups per compute unit every output gets a wave of its own (at most 16): splitting the outputs over
+    // workgroups instead repeats the inverse stages in each (one query of the one-tree forest 526 to 520 us)
+    const size_t wgs = (size_t)xb * set.n * zmax;
+    const bool small = wgs < (c.tune.bridge_wgs > 0 ? (size_t)c.tune.bridge_wgs : 512);
+    const int waves = small ? std::min(16, std::max(4, omax)) : 4;
+    const dim3 grid(xb, set.n, zmax), blk(64 * waves);
 #define COPSE_BRIDGE(S, M) hipLaunchKernelGGL((ntt_bridge_kernel<S, M>), grid, blk, 0, c.stream, set, c.d_primes, (int)c.log_n)
     if (mode == 0) {
       switch (S1) {
@@ -927,7 +920,7 @@ void launch_bridge(Context& c, int mode, double* out_base, const int2* out_rows,
   if (n_out <= 0 || batch <= 0) return;
   // batches beyond one launch's z range run in slices
   for (int first = 0; first < batch; first += kMaxGridY) {
-    BridgeDesc d{out_rows, in_rows, mult, mat, n_out, n_in, 0, 0};
+    BridgeDesc d{out_rows, in_rows, mult, mat, n_out, n_in};
     d.in = in_base + (size_t)first * in_bs;
     d.out = out_base + (size_t)first * out_bs;
     d.in_bs = in_bs;
