@@ -210,6 +210,7 @@ struct Context {
   char* export_slot[2] = {nullptr, nullptr};
   size_t export_slot_bytes = 0;
   hipEvent_t export_done[2] = {nullptr, nullptr};
+  int import_slot = 0;
   Tuning tune;                    // active for the evaluation being issued
   std::vector<TuneEntry> tune_table;
   // the table's entry for an evaluation of `batch` query groups of a plaintext or encrypted model (defaults

@@ -37,15 +37,15 @@ __global__ void residues_to_words_kernel(uint64_t* out, const double* in, int lo
 
 // The column pass with the conversion folded in, for the rings of the split transform (N = 2^13 .. 2^16): one
 // thread keeps one column (2^S1 elements, C = N >> S1 apart) in registers.
-//   forward (import): words, checked against the prime, then stages 0 .. S1 - 1; signed output for the row pass, in
-//   place
-//   inverse (export): the row pass's signed output (< 32 q), the last stages, N^-1, canonical words to `out` (pinned
-//   host memory: the stores cross the bus, so no copy follows)
+//   forward (import): words from `words`, checked against the prime, then stages 0 .. S1 - 1; signed output for the row
+//   pass to `io` (which may be the same memory)
+//   inverse (export): the row pass's signed output in `io` (< 32 q), the last stages, N^-1, canonical words to `words`
+// Where words is pinned host memory, the loads and stores cross the bus and no copy stands before or after.
 // Bound by the copy from or to the caller's memory.  A request of eight planes (42 MB) in, one evaluation, its result
 // out: 5.50 ms with the conversion loops on the host, 3.14 ms here, of which the copy in takes 1.2 and the evaluation
 // 1.4.
 template <int S1, bool kInverse>
-__global__ __launch_bounds__(64) void wire_cols_kernel(double* io, uint64_t* out, int nl,
+__global__ __launch_bounds__(64) void wire_cols_kernel(double* io, uint64_t* words, int nl,
                                                        const DevPrime* __restrict__ P, int logN, int* bad) {
   constexpr int R = 1 << S1;
   const size_t C = (size_t)1 << (logN - S1);
@@ -53,13 +53,14 @@ __global__ __launch_bounds__(64) void wire_cols_kernel(double* io, uint64_t* out
   if (col >= C) return;
   const DevPrime pr = P[blockIdx.y % nl];
   double* a = io + ((size_t)blockIdx.y << logN) + col;
+  uint64_t* w = words + ((size_t)blockIdx.y << logN) + col;
   double x[R];
   if (!kInverse) {
     const uint64_t q = (uint64_t)pr.q;
     bool ok = true;
 #pragma unroll
     for (int r = 0; r < R; ++r) {
-      const uint64_t v = reinterpret_cast<const uint64_t*>(a)[r * C];
+      const uint64_t v = w[r * C];
       ok = ok && v < q;
       x[r] = v < q ? (double)v : 0.0;
     }
@@ -92,7 +93,7 @@ __global__ __launch_bounds__(64) void wire_cols_kernel(double* io, uint64_t* out
 #pragma unroll
     for (int r = 0; r < R; ++r) {
       const double v = canon(reduce_sym(mul_lazy(x[r], pr.ninv, pr.q, pr.qinv), pr.q, pr.qinv), pr.q);
-      out[((size_t)blockIdx.y << logN) + col + r * C] = (uint64_t)v;
+      w[r * C] = (uint64_t)v;
     }
   }
 }
@@ -145,21 +146,26 @@ static void ct_words(Context& c, const Ct& a, uint64_t* out) {
 // group of eight planes (42 MB, to fresh pages) encrypted and exported 5.41 -> 4.28 ms.  A ciphertext beyond a slot goes through device memory.
 constexpr size_t kExportSlotMax = (size_t)8 << 20;
 
-void export_cts(Context& c, const std::vector<const Ct*>& cts, uint64_t* buf) {
-  size_t need = 0;
-  for (const Ct* a : cts) need = std::max(need, a->words() * 8);
+// slots of at least min(need, kExportSlotMax) bytes
+static void wire_slots(Context& c, size_t need) {
   need = std::min(need, kExportSlotMax);
   for (int k = 0; k < 2; ++k)
     if (!c.export_done[k]) COPSE_HIP(hipEventCreateWithFlags(&c.export_done[k], hipEventDisableTiming));
-  if (need > c.export_slot_bytes) {
-    for (char*& p : c.export_slot) {
-      if (p) COPSE_HIP(hipHostFree(p));
-      p = nullptr;
-    }
-    c.export_slot_bytes = 0;
-    for (char*& p : c.export_slot) COPSE_HIP(hipHostMalloc(reinterpret_cast<void**>(&p), need, hipHostMallocDefault));
-    c.export_slot_bytes = need;
+  if (need <= c.export_slot_bytes) return;
+  COPSE_HIP(hipStreamSynchronize(c.stream));   // an import may still be read
+  for (char*& p : c.export_slot) {
+    if (p) COPSE_HIP(hipHostFree(p));
+    p = nullptr;
   }
+  c.export_slot_bytes = 0;
+  for (char*& p : c.export_slot) COPSE_HIP(hipHostMalloc(reinterpret_cast<void**>(&p), need, hipHostMallocDefault));
+  c.export_slot_bytes = need;
+}
+
+void export_cts(Context& c, const std::vector<const Ct*>& cts, uint64_t* buf) {
+  size_t need = 0;
+  for (const Ct* a : cts) need = std::max(need, a->words() * 8);
+  wire_slots(c, need);
   struct Pending {
     uint64_t* to = nullptr;
     size_t bytes = 0;
@@ -196,14 +202,32 @@ void export_cts(Context& c, const std::vector<const Ct*>& cts, uint64_t* buf) {
   finish(slot ^ 1);
 }
 
+// Words through a pinned slot up to this size: a result (0.5 MB) imported and decrypted takes 131 against 138 us with a
+// copy from pageable memory, a small ring's request (eight planes of 2 MB) imported, evaluated and exported 0.80 against
+// 0.85 ms; planes of 5 MB are copied by the host more slowly than by the runtime (3.13 against 3.00 ms).
+constexpr size_t kImportSlotMax = (size_t)2 << 20;
+
 // A ciphertext from coefficient words in caller memory, enqueued; *bad (device) becomes 1 when a word is not
 // below its prime.  `words` must stay valid until the stream has been synchronized.
 CtPtr ct_from_words(Context& c, const uint64_t* words, int level, int npolys, int* bad) {
   auto ct = ct_alloc(c, level, npolys);
   const int nl = level + 1, rows = npolys * nl;
-  COPSE_HIP(hipMemcpyAsync(ct->data(), words, ct->words() * 8, hipMemcpyHostToDevice, c.stream));
+  const size_t bytes = ct->words() * 8;
+  if (bridge_supported(c, 1) && bytes <= kImportSlotMax) {
+    wire_slots(c, bytes);
+    const int slot = c.import_slot;
+    c.import_slot ^= 1;
+    COPSE_HIP(hipEventSynchronize(c.export_done[slot]));   // what last read or wrote the slot
+    std::memcpy(c.export_slot[slot], words, bytes);
+    launch_wire_cols<false>(c, ct->data(), reinterpret_cast<uint64_t*>(c.export_slot[slot]), rows, nl, bad);
+    COPSE_HIP(hipEventRecord(c.export_done[slot], c.stream));
+    launch_ntt_fwd_rows(c, ct->data(), limb_rows(c, npolys, nl), rows);
+    return ct;
+  }
+  // a larger one as it is: the runtime pins the caller's pages and copies at the bus's rate
+  COPSE_HIP(hipMemcpyAsync(ct->data(), words, bytes, hipMemcpyHostToDevice, c.stream));
   if (bridge_supported(c, 1)) {
-    launch_wire_cols<false>(c, ct->data(), nullptr, rows, nl, bad);
+    launch_wire_cols<false>(c, ct->data(), reinterpret_cast<uint64_t*>(ct->data()), rows, nl, bad);
     launch_ntt_fwd_rows(c, ct->data(), limb_rows(c, npolys, nl), rows);
     return ct;
   }

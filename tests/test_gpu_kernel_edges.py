@@ -166,3 +166,30 @@ def test_rotations_with_nine_digits(C):
                                                     (13, 3, True, 8), (13, 4, True, 33), (14, 3, True, 12)])
 def test_relinearizations_by_workgroup_count(C, log_n, alpha, enc, groups):
     evaluate_groups(C, synth.ForestShape(3, 3, 0.9, 3, 4, 3), 74, log_n, (42, 48, 48), alpha, enc, groups)
+
+
+@pytest.mark.parametrize("log_n", [11, 13])
+def test_import_of_mixed_shapes(C, log_n):
+    """A buffer of ciphertexts whose shapes change along the way (runs of one to nine of a shape), and the same with one
+    word out of range in the last."""
+    import ctypes
+
+    ctx = C.Context(log_n, 3, 1 << 48, 1 << 46, 1, 1 << 49)
+    qs = ctx.primes()
+    rng = np.random.default_rng(5)
+    want, words = [], []
+    for np_, lv, run in ((2, 2, 9), (2, 0, 1), (3, 0, 2), (1, 1, 8), (2, 1, 1)):
+        for _ in range(run):
+            polys = [np.stack([rng.integers(0, q, ctx.N, dtype=np.uint64) for q in qs[:lv + 1]]) for _ in range(np_)]
+            want.append((lv, polys))
+            words += [np.array([np_, lv, ctx.N, 0], dtype=np.uint64)] + [p.reshape(-1) for p in polys]
+    buf = np.ascontiguousarray(np.concatenate(words))
+    ptr = buf.ctypes.data_as(ctypes.POINTER(ctypes.c_uint64))
+    h = ctypes.c_void_p()
+    C.check(C.lib().copse_cts_import(ctx.ptr, ptr, buf.size, ctypes.byref(h)))
+    got = ctx.export(C.Cts(h, ctx))
+    assert len(got) == len(want)
+    for g, (lv, polys) in zip(got, want):
+        assert g["level"] == lv and all((a == b).all() for a, b in zip(g["polys"], polys))
+    buf[-1] = qs[1]
+    assert C.lib().copse_cts_import(ctx.ptr, ptr, buf.size, ctypes.byref(h)) == C.COPSE_EINVAL
