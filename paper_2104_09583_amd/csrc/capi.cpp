@@ -132,6 +132,7 @@ int copse_ctx_create(const copse_params* p, copse_ctx** out) {
     c->L = (int)p->n_data_primes - 1;
     c->pool = std::make_shared<Pool>(p->device);
     c->primes = make_chain(*p);
+    c->packed = std::all_of(c->primes.begin(), c->primes.end(), [](uint64_t q) { return q < (1ULL << 48); });
     setup_slots(*c);
     // transform tables of the chain's primes and, last, of t (slots <-> coefficients, root zeta)
     std::vector<DevPrime> dp;

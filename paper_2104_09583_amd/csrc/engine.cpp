@@ -49,7 +49,7 @@ static const int2* block_rows(Context& c, int np, int nl) {
 std::vector<SCt> b_modswitch(Context& c, const std::vector<const Ct*>& in,
                              const std::vector<const double*>* adds = nullptr, int add_np = 0) {
   std::vector<SCt> out(in.size());
-  const size_t N = c.N;
+  const size_t N = c.N, RD = c.row_doubles();
   for (const Ct* x : in)
     if (x->level == 0) fail(COPSE_ECAPACITY, "modulus chain exhausted");
   if (bridge_supported(c, 1)) {
@@ -64,7 +64,7 @@ std::vector<SCt> b_modswitch(Context& c, const std::vector<const Ct*>& in,
       size_t wrows = 0;
       for (size_t j : idx) wrows += (size_t)np * in[j]->level;
       DBuf top(&c, (size_t)J * np * N);
-      DBuf w(&c, wrows * N);
+      DBuf w(&c, wrows * RD);
       std::vector<double*> po;
       std::vector<const double*> pi, pa, pw, tabs;
       std::vector<int> lv;
@@ -81,9 +81,10 @@ std::vector<SCt> b_modswitch(Context& c, const std::vector<const Ct*>& in,
         BridgeDesc d{rows_cached(c, "msout:" + std::to_string(l), orr), rows_cached(c, "msin:" + std::to_string(l), ir),
                      T.d_ms + 1, nullptr, l, 1};
         d.in = top.get() + (size_t)j0 * np * N;
-        d.out = w.get() + woff * N;
+        d.out = w.get() + woff * RD;
         d.in_bs = N;
-        d.out_bs = (size_t)l * N;
+        d.out_bs = (size_t)l * RD;
+        d.packed = c.packed;
         d.nz = (j1 - j0) * np;
         ds.push_back(d);
         for (int j = j0; j < j1; ++j) {
@@ -91,7 +92,7 @@ std::vector<SCt> b_modswitch(Context& c, const std::vector<const Ct*>& in,
           po.push_back(outs[j - j0]->data());
           pi.push_back(in[g]->data());
           if (adds) pa.push_back((*adds)[g]);
-          pw.push_back(w.get() + woff * N);
+          pw.push_back(w.get() + woff * RD);
           tabs.push_back(T.d_ms);
           lv.push_back(l);
           out[g] = outs[j - j0];
@@ -144,7 +145,7 @@ std::vector<SCt> b_modswitch(Context& c, const std::vector<const Ct*>& in,
 // (level, k) (mode 3: the single switches' lifts one after the other), one forward row pass with the finish.
 static std::vector<SCt> b_switch_by(Context& c, const std::vector<const Ct*>& in, const std::vector<int>& kk) {
   std::vector<SCt> out(in.size());
-  const size_t N = c.N;
+  const size_t N = c.N, RD = c.row_doubles();
   std::map<int, std::vector<size_t>> by_np;
   for (size_t i = 0; i < in.size(); ++i) {
     if (kk[i] < 1 || kk[i] > 4 || kk[i] > in[i]->level) fail(COPSE_EINVAL, "internal: switch count");
@@ -166,7 +167,7 @@ static std::vector<SCt> b_switch_by(Context& c, const std::vector<const Ct*>& in
     }
     const int rpj = np * kmax;
     DBuf top(&c, (size_t)J * rpj * N);
-    DBuf w(&c, wrows * N);
+    DBuf w(&c, wrows * RD);
     std::vector<double*> po;
     std::vector<const double*> pi, pw, tabs;
     std::vector<int> glv, flv;
@@ -181,16 +182,17 @@ static std::vector<SCt> b_switch_by(Context& c, const std::vector<const Ct*>& in
       auto outs = alloc_batch(c, j1 - j0, l - k, np);
       BridgeDesc d{M.out_rows, M.in_rows, M.mult, M.mat, n_out, k};
       d.in = top.get() + (size_t)j0 * rpj * N;
-      d.out = w.get() + woff * N;
+      d.out = w.get() + woff * RD;
       d.in_bs = (size_t)kmax * N;
-      d.out_bs = (size_t)n_out * N;
+      d.out_bs = (size_t)n_out * RD;
+      d.packed = c.packed;
       d.nz = (j1 - j0) * np;
       ds.push_back(d);
       for (int j = j0; j < j1; ++j) {
         const size_t g = idx[j];
         po.push_back(outs[j - j0]->data());
         pi.push_back(in[g]->data());
-        pw.push_back(w.get() + woff * N);
+        pw.push_back(w.get() + woff * RD);
         tabs.push_back(M.tab);
         glv.push_back(l | (k << 16));
         flv.push_back(n_out | ((l + 1) << 16));
@@ -211,18 +213,18 @@ static std::vector<SCt> b_switch_by(Context& c, const std::vector<const Ct*>& in
 static std::vector<SCt> b_ptlayer_switch(Context& c, const std::vector<const double*>& x,
                                          const std::vector<const double*>& mul, const std::vector<const double*>& add,
                                          int l) {
-  const size_t N = c.N;
+  const size_t N = c.N, RD = c.row_doubles();
   const int J = (int)x.size(), np = 2;
   KSTables& T = c.kstab(l);
   auto outs = alloc_batch(c, J, l - 1, np);
   DBuf top(&c, (size_t)J * np * N);
-  DBuf w(&c, (size_t)J * np * l * N);
+  DBuf w(&c, (size_t)J * np * l * RD);
   std::vector<double*> po;
   std::vector<const double*> pw, tabs;
   std::vector<int> lv(J, l);
   for (int j = 0; j < J; ++j) {
     po.push_back(outs[j]->data());
-    pw.push_back(w.get() + (size_t)j * np * l * N);
+    pw.push_back(w.get() + (size_t)j * np * l * RD);
     tabs.push_back(T.d_ms);
   }
   std::vector<int2> ir{make_int2(0, l)}, orr;
@@ -232,7 +234,8 @@ static std::vector<SCt> b_ptlayer_switch(Context& c, const std::vector<const dou
   d.in = top.get();
   d.out = w.get();
   d.in_bs = N;
-  d.out_bs = (size_t)l * N;
+  d.out_bs = (size_t)l * RD;
+  d.packed = c.packed;
   d.nz = J * np;
   launch_ntt_inv_rows_gather(c, top.get(), x, np, 0, 0, -4, &lv, &mul, &add);
   launch_bridge_set(c, 1, nullptr, nullptr, {d}, 0, 0, 0);
@@ -352,7 +355,7 @@ struct KsReq {
 static void ks_batch(Context& c, int level, const std::vector<const double*>& inputs, const std::vector<KsReq>& reqs,
                      int add_mode, bool merge = false, const std::vector<const double*>* inputs_b = nullptr) {
   if (reqs.empty()) return;
-  const size_t N = c.N;
+  const size_t N = c.N, RD = c.row_doubles();
   const int nl = level + 1, nE = nl + c.alpha, D = c.n_digits(level);
   const int R = (int)reqs.size();
   const int Lt = c.n_primes();
@@ -369,7 +372,7 @@ static void ks_batch(Context& c, int level, const std::vector<const double*>& in
   DBuf ext = modup_batch(c, level, inputs, !no_auto, inputs_b);
   if (fused && add_mode == 2) {
     // rotations: the inner products only where their result is used (keyswitch.hip)
-    DBuf acc(&c, (size_t)R * 2 * c.alpha * N), w(&c, (size_t)R * 2 * nl * N);
+    DBuf acc(&c, (size_t)R * 2 * c.alpha * N), w(&c, (size_t)R * 2 * nl * RD);
     std::vector<KsRot> rots;
     for (const KsReq& rq : reqs)
       rots.push_back(KsRot{inputs[rq.input], ext.get() + (size_t)rq.input * D * nE * N, rq.key->b.get(),
@@ -380,7 +383,7 @@ static void ks_batch(Context& c, int level, const std::vector<const double*>& in
     for (int i = 0; i < nl; ++i) outr.push_back(make_int2(i, i));
     launch_bridge(c, 0, w.get(), rows_cached(c, "mdout:" + std::to_string(level), outr), nl, acc.get(),
                   rows_cached(c, "rotin:" + std::to_string(c.alpha), inr), c.alpha, T.d_md_mult, T.d_md_mat, 2 * R,
-                  (size_t)c.alpha * N, (size_t)nl * N);
+                  (size_t)c.alpha * N, (size_t)nl * RD, c.packed);
     launch_ks_rot_finish(c, rots, w.get(), T.d_md_pinv, D, nE, level, (size_t)Lt * N);
     return;
   }
@@ -423,10 +426,10 @@ static void ks_batch(Context& c, int level, const std::vector<const double*>& in
     for (int s2 = 0; s2 < c.alpha; ++s2) inr.push_back(make_int2(nl + s2, c.L + 1 + s2));
     inr.push_back(make_int2(l, l));
     for (int i = 0; i < l; ++i) outr.push_back(make_int2(i, i));
-    DBuf w(&c, (size_t)2 * R * l * N);
+    DBuf w(&c, (size_t)2 * R * l * RD);
     launch_bridge(c, 2, w.get(), rows_cached(c, "mdmsout:" + std::to_string(level), outr), l, acc.get(),
                   rows_cached(c, "mdmsin:" + std::to_string(level), inr), c.alpha + 1, T.d_mm_mult, T.d_mm_mat,
-                  2 * R, (size_t)nE * N, (size_t)l * N);
+                  2 * R, (size_t)nE * N, (size_t)l * RD, c.packed);
     if (inline_data) {
       std::vector<KsRelin> rj;
       for (int q = 0; q < R; ++q)
@@ -467,7 +470,7 @@ static void ks_batch(Context& c, int level, const std::vector<const double*>& in
       launch_ntt_inv(c, acc.get(), r, 2 * R * c.alpha);
     }
   }
-  DBuf zh(&c, (size_t)2 * R * nl * N);
+  DBuf zh(&c, (size_t)2 * R * nl * (fused ? RD : N));
   std::vector<int2> inr, outr;
   for (int s = 0; s < c.alpha; ++s) inr.push_back(make_int2(nl + s, c.L + 1 + s));
   for (int i = 0; i < nl; ++i) outr.push_back(make_int2(i, i));
@@ -482,7 +485,7 @@ static void ks_batch(Context& c, int level, const std::vector<const double*>& in
   if (fused) {
     launch_bridge(c, 0, zh.get(), rows_cached(c, "mdout:" + std::to_string(level), outr), nl, acc.get(),
                   rows_cached(c, "mdin:" + std::to_string(level), inr), c.alpha, T.d_md_mult, T.d_md_mat, 2 * R,
-                  (size_t)nE * N, (size_t)nl * N);
+                  (size_t)nE * N, (size_t)nl * RD, c.packed);
     if (inline_data) {
       std::vector<KsRelin> rj;
       for (int q = 0; q < R; ++q)
@@ -744,10 +747,10 @@ static std::vector<std::vector<SCt>> b_matmul_many(Context& c, const Keys& k, co
     for (int s2 = 0; s2 < c.alpha; ++s2) inr.push_back(make_int2(nl + s2, c.L + 1 + s2));
     inr.push_back(make_int2(l, l));
     for (int i = 0; i < l; ++i) outr.push_back(make_int2(i, i));
-    DBuf w(&c, (size_t)2 * R * l * N);
+    DBuf w(&c, (size_t)2 * R * l * c.row_doubles());
     launch_bridge(c, 2, w.get(), rows_cached(c, "mdmsout:" + std::to_string(level), outr), l, acc.get(),
                   rows_cached(c, "mdmsin:" + std::to_string(level), inr), c.alpha + 1, T.d_mm_mult, T.d_mm_mat,
-                  2 * R, (size_t)nE * N, (size_t)l * N);
+                  2 * R, (size_t)nE * N, (size_t)l * c.row_doubles(), c.packed);
     launch_ntt_fwd_rows_mdms_finish(c, outs, addp, acc.get(), w.get(), nE, l, T.d_mm_m1, T.d_mm_m2, T.d_mm_m3,
                                     adds ? &maskp : nullptr, add_np);
     return out;

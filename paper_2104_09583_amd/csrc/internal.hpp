@@ -221,6 +221,10 @@ struct Context {
   std::vector<std::pair<hipEvent_t, hipEvent_t>> pending[kProfKinds];
   std::vector<hipEvent_t> event_cache;
 
+  // Key switching's rows between its kernels (written by the fused column pass, read once or twice) hold six bytes per
+  // value where every prime is below 2^48; a row then takes row_doubles() doubles.
+  bool packed = false;
+  size_t row_doubles() const { return packed ? N / 4 * 3 : N; }
   int n_primes() const { return (int)primes.size(); }
   int special(int r) const { return L + 1 + r; }
   int n_digits(int level) const { return (level + 1 + alpha - 1) / alpha; }
@@ -326,6 +330,7 @@ struct BridgeDesc {
   const double* mult;
   const double* mat;
   int n_out, n_in;
+  bool packed = false;   // the output rows are packed
   // set by launch_bridge_set when left empty: the blocks and batch of this map
   const double* in = nullptr;
   double* out = nullptr;
@@ -344,7 +349,7 @@ void launch_bridge_set(Context& c, int mode, double* out_base, const double* in_
 // [alpha][n_out + 1] (the last column for the top prime), see ntt_bridge_kernel
 void launch_bridge(Context& c, int mode, double* out_base, const int2* out_rows, int n_out, const double* in_base,
                    const int2* in_rows, int n_in, const double* mult, const double* mat, int batch, size_t in_bs,
-                   size_t out_bs);
+                   size_t out_bs, bool packed = false);
 // out = a op b over rows (same row layout for out, a, b)
 void launch_add(Context& c, double* out, const double* a, const double* b, const int2* rows, int nrows);
 void launch_sub(Context& c, double* out, const double* a, const double* b, const int2* rows, int nrows);

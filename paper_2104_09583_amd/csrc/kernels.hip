@@ -340,7 +340,7 @@ __global__ __launch_bounds__(512) void ntt_rowreg4_kernel(double* __restrict__ b
   double* a = base + (size_t)row.x * N + t0;
   double x[8];
   if (!kInverse) {
-    row4_fwd_tile(a, t0, S1, pr, sh, x);
+    row4_fwd_tile(TileSrc{a - t0, t0, N, false}, S1, pr, sh, x);
 #pragma unroll
     for (int k = 0; k < 8; ++k) tile_store(a, k, canon(reduce_sym(x[k], pr.q, pr.qinv), pr.q));
   } else {
@@ -439,7 +439,8 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(6))) void n
                                                                const double* __restrict__ mul,
                                                                const double* __restrict__ tmul,
                                                                const DevPrime* __restrict__ P, int logN, int S1,
-                                                               const double* __restrict__ amul, Pack mulp) {
+                                                               const double* __restrict__ amul, Pack mulp,
+                                                               bool packed) {
   __shared__ double sh[kLdsTile4];
   const int i = blockIdx.y, z = blockIdx.z;
   constexpr bool kMd = kMode == 1 || kMode == 3;   // ModDown layout (2 polys per job, accumulator rows)
@@ -453,7 +454,7 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(6))) void n
   const size_t N = (size_t)1 << logN;
   const size_t t0 = (size_t)blockIdx.x * 4096;
   double x[8];
-  const double* wrow = kMd ? w + ((size_t)z * nl + i) * N : ws.p[j] + ((size_t)k * nl + i) * N;
+  const double* wrow = kMd ? row_at(w, (size_t)z * nl + i, N, packed) : row_at(ws.p[j], (size_t)k * nl + i, N, packed);
   const double* tab = kMd ? nullptr : tabs.p[j];
   const double m1 = kMd ? mul[i] : tab[2 + 2 * i];
   const double m2 = kMd ? tmul[i] : tab[3 + 2 * i];
@@ -462,7 +463,7 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(6))) void n
   const double* yrow = kMd ? acc + ((size_t)z * nE + i) * N : in.p[j] + ((size_t)k * nin + i) * N;
   // the epilogue's main operand is loaded during the transform, so its latency overlaps it
   double yv[8];
-  row4_fwd_tile(wrow + t0, t0, S1, pr, sh, x, yrow + t0, yv);
+  row4_fwd_tile(TileSrc{wrow, t0, N, packed}, S1, pr, sh, x, yrow + t0, yv);
   if (kMode == 4) {
     // the plaintext layer's value of this limb (the input's limb i, the plaintexts' limb i)
     const double* mp = mulp.p[j] + (size_t)i * N + t0;
@@ -792,8 +793,9 @@ __global__ __launch_bounds__(1024) void ntt_bridge_kernel(BridgeSet set, const D
     BridgeOut<S1> nxt;
     if (o + nw < n_out) nxt = bridge_out_load<S1, kMode>(d, P, o + nw);
     const double q = cur.q, qinv = cur.qinv;
-    // below 2^46 the sums (< 8 q) pass unreduced through the column stages and into the row pass
-    const bool lazy = q < kFwdLazy;
+    // below 2^46 the sums (< 8 q) pass unreduced through the column stages and into the row pass; packed rows hold
+    // 2^47, so there below 2^44 (and q / 2 above)
+    const bool lazy = q < (d.packed ? kInvLazy : kFwdLazy);
     double x[R];
 #pragma unroll
     for (int r = 0; r < R; ++r) {
@@ -828,9 +830,16 @@ __global__ __launch_bounds__(1024) void ntt_bridge_kernel(BridgeSet set, const D
 #pragma unroll
       for (int r = 0; r < R; ++r) x[r] = reduce_sym(x[r], q, qinv);
     }
-    double* a = out + (size_t)cur.row.x * N;
+    if (d.packed) {   // uniform
+      uint32_t* lo = reinterpret_cast<uint32_t*>(out + (size_t)cur.row.x * (N / 4 * 3));
+      uint16_t* hi = reinterpret_cast<uint16_t*>(lo + N);
 #pragma unroll
-    for (int r = 0; r < R; ++r) a[r * C + c] = x[r];
+      for (int r = 0; r < R; ++r) pack48(x[r], lo[r * C + c], hi[r * C + c]);
+    } else {
+      double* a = out + (size_t)cur.row.x * N;
+#pragma unroll
+      for (int r = 0; r < R; ++r) a[r * C + c] = x[r];
+    }
     cur = nxt;
   }
 }
@@ -916,11 +925,11 @@ void launch_bridge_set(Context& c, int mode, double* out_base, const double* in_
 
 void launch_bridge(Context& c, int mode, double* out_base, const int2* out_rows, int n_out, const double* in_base,
                    const int2* in_rows, int n_in, const double* mult, const double* mat, int batch, size_t in_bs,
-                   size_t out_bs) {
+                   size_t out_bs, bool packed) {
   if (n_out <= 0 || batch <= 0) return;
   // batches beyond one launch's z range run in slices
   for (int first = 0; first < batch; first += kMaxGridY) {
-    BridgeDesc d{out_rows, in_rows, mult, mat, n_out, n_in};
+    BridgeDesc d{out_rows, in_rows, mult, mat, n_out, n_in, packed};
     d.in = in_base + (size_t)first * in_bs;
     d.out = out_base + (size_t)first * out_bs;
     d.in_bs = in_bs;
@@ -1007,8 +1016,8 @@ void launch_ntt_fwd_rows_md_finish(Context& c, const std::vector<double*>& out, 
     IPack nolv{};
     hipLaunchKernelGGL(ntt_rowfwd_finish_kernel<1>, dim3((unsigned)(c.N / 4096), nl, 2 * cnt), dim3(512), 0,
                        c.stream, po, none, pa, none, none, nolv, acc + first * 2 * nE * c.N,
-                       w + first * 2 * nl * c.N, nE, nl, 2, 1, 0, pinv, tpinv, c.d_primes, (int)c.log_n,
-                       (int)c.log_n - 12, nullptr, none);
+                       w + first * 2 * nl * c.row_doubles(), nE, nl, 2, 1, 0, pinv, tpinv, c.d_primes, (int)c.log_n,
+                       (int)c.log_n - 12, nullptr, none, c.packed);
     COPSE_HIP(hipGetLastError());
     prof_end(c, 7, ev, 8.0 * nl * cnt * (double)c.N * 8.0);
   }
@@ -1039,8 +1048,8 @@ void launch_ntt_fwd_rows_mdms_finish(Context& c, const std::vector<double*>& out
     prof_begin(c, 7, &ev);
     hipLaunchKernelGGL(ntt_rowfwd_finish_kernel<3>, dim3((unsigned)(c.N / 4096), l, 2 * cnt), dim3(512), 0,
                        c.stream, po, pm, pa, none, none, nolv, acc + first * 2 * nE * c.N,
-                       w + first * 2 * l * c.N, nE, l, 2, 0, masks ? mask_np : 0, m1, m2, c.d_primes,
-                       (int)c.log_n, (int)c.log_n - 12, m3, pb);
+                       w + first * 2 * l * c.row_doubles(), nE, l, 2, 0, masks ? mask_np : 0, m1, m2, c.d_primes,
+                       (int)c.log_n, (int)c.log_n - 12, m3, pb, c.packed);
     COPSE_HIP(hipGetLastError());
     // per output row: the bridge's row, the accumulator and addend rows read (a product's addend: its two
     // ciphertexts' rows, 2 for poly 0 and 4 for poly 1), the output written (+ mask)
@@ -1081,11 +1090,11 @@ void launch_ntt_fwd_rows_ms_finish(Context& c, const std::vector<double*>& out, 
     if (mulp)   // the plaintext layer (`add` holds its addends, no post-switch add)
       hipLaunchKernelGGL(ntt_rowfwd_finish_kernel<4>, dim3((unsigned)(c.N / 4096), lmax, np * cnt), dim3(512), 0,
                          c.stream, po, pi, pa, pw, pt, lv, nullptr, nullptr, 0, 0, np, 0, 0, nullptr, nullptr,
-                         c.d_primes, (int)c.log_n, (int)c.log_n - 12, nullptr, pm);
+                         c.d_primes, (int)c.log_n, (int)c.log_n - 12, nullptr, pm, c.packed);
     else
       hipLaunchKernelGGL(ntt_rowfwd_finish_kernel<2>, dim3((unsigned)(c.N / 4096), lmax, np * cnt), dim3(512), 0,
                          c.stream, po, pi, pa, pw, pt, lv, nullptr, nullptr, 0, 0, np, 0, add ? add_np : 0,
-                         nullptr, nullptr, c.d_primes, (int)c.log_n, (int)c.log_n - 12, nullptr, pm);
+                         nullptr, nullptr, c.d_primes, (int)c.log_n, (int)c.log_n - 12, nullptr, pm, c.packed);
     COPSE_HIP(hipGetLastError());
     prof_end(c, 8, ev, bytes);
   }
@@ -1733,7 +1742,7 @@ __global__ __launch_bounds__(512, 4) void ks_inner_rows_kernel(KsPack jobs, int 
 #pragma unroll
     for (int k = 0; k < 8; ++k) a1[k] += mul_lazy(x[k], kv[k], pr.q, pr.qinv);
   };
-  auto ext = [&](int j) { return jb.ext + ((size_t)j * nE + o) * N + t0; };
+  auto ext = [&](int j) { return TileSrc{jb.ext + ((size_t)j * nE + o) * N, t0, N, false}; };
   // the first two digits to transform (not the row's own) as one pair, before any sum is live; the sums
   // are exact, so the digit order changes no bit
   int j = own == 0 ? 1 : 0, jn = D;   // jn: the first digit left after the pair
@@ -1742,7 +1751,7 @@ __global__ __launch_bounds__(512, 4) void ks_inner_rows_kernel(KsPack jobs, int 
     if (j2 == own) ++j2;
     if (j2 < D) {
       double x[8], y[8];
-      row4_fwd_tile2(ext(j), ext(j2), t0, S1, pr, sh, sh2, x, y);
+      row4_fwd_tile2(ext(j), ext(j2), S1, pr, sh, sh2, x, y);
 #pragma unroll
       for (int k = 0; k < 8; ++k) a0[k] = a1[k] = 0.0;
       mac(j, x);
@@ -1750,7 +1759,7 @@ __global__ __launch_bounds__(512, 4) void ks_inner_rows_kernel(KsPack jobs, int 
       jn = j2 + 1;
     } else {
       double x[8];
-      row4_fwd_tile(ext(j), t0, S1, pr, sh, x);
+      row4_fwd_tile(ext(j), S1, pr, sh, x);
 #pragma unroll
       for (int k = 0; k < 8; ++k) a0[k] = a1[k] = 0.0;
       mac(j, x);
@@ -1762,7 +1771,7 @@ __global__ __launch_bounds__(512, 4) void ks_inner_rows_kernel(KsPack jobs, int 
   for (int jj = jn; jj < D; ++jj) {   // any further digit one at a time (uniform per workgroup)
     if (jj == own) continue;
     double x[8];
-    row4_fwd_tile(ext(jj), t0, S1, pr, sh, x);
+    row4_fwd_tile(ext(jj), S1, pr, sh, x);
     mac(jj, x);
   }
   // the digit whose own limb this row is: its values are the input's in NTT form (a product's: formed

@@ -89,7 +89,7 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(6))) void k
 // 32 jobs (the inner products of the data rows and the finish apart: 92).
 __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(6))) void ks_rot_finish_kernel(
     RotPack jobs, int njobs, const double* __restrict__ w, const double* __restrict__ pinv, double t_mod, int D, int nE,
-    int nl, int alpha, int logN, size_t key_ds, const DevPrime* __restrict__ P) {
+    int nl, int alpha, int logN, size_t key_ds, const DevPrime* __restrict__ P, bool packed) {
   __shared__ double sh[kLdsTile4];
   const size_t N = (size_t)1 << logN;
   const KsPlace pl = ks_place(njobs);
@@ -97,7 +97,8 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(6))) void k
   const int i = pl.row;
   const DevPrime pr = P[i];
   double a[8];
-  row4_fwd_tile(w + (((size_t)pl.job * 2 + pl.poly) * nl + i) * N + pl.t0, pl.t0, logN - 12, pr, sh, a);
+  row4_fwd_tile(TileSrc{row_at(w, ((size_t)pl.job * 2 + pl.poly) * nl + i, N, packed), pl.t0, N, packed}, logN - 12, pr, sh,
+                a);
 #pragma unroll
   for (int k = 0; k < 8; ++k) a[k] = -mul_lazy(a[k], t_mod, pr.q, pr.qinv);
   const AutoTile at = auto_tile(pl.t0, jb.g, logN);
@@ -165,8 +166,8 @@ void launch_ks_rot_finish(Context& c, const std::vector<KsRot>& jobs, const doub
     hipEvent_t ev;
     prof_begin(c, 7, &ev);
     hipLaunchKernelGGL(ks_rot_finish_kernel, dim3((unsigned)(c.N / 4096), nl, 2 * cnt), dim3(512), 0, c.stream, pk,
-                       cnt, w + first * 2 * nl * c.N, pinv, (double)c.t, D, nE, nl, c.alpha, (int)c.log_n, key_ds,
-                       c.d_primes);
+                       cnt, w + first * 2 * nl * c.row_doubles(), pinv, (double)c.t, D, nE, nl, c.alpha, (int)c.log_n, key_ds,
+                       c.d_primes, c.packed);
     COPSE_HIP(hipGetLastError());
     prof_end(c, 7, ev, ((double)(D + 5) * cnt + 2.0 * D * distinct_keys(pk, cnt)) * nl * (double)c.N * 8.0);
   }
@@ -189,7 +190,8 @@ __global__ __launch_bounds__(512, 4) void ks_relin_finish_kernel(RelinPack jobs,
                                                                  const double* __restrict__ cw,
                                                                  const double* __restrict__ ca, double t_mod, int nout,
                                                                  int D, int nE, int nl, int alpha, int logN,
-                                                                 size_t key_ds, const DevPrime* __restrict__ P) {
+                                                                 size_t key_ds, const DevPrime* __restrict__ P,
+                                                                 bool packed) {
   __shared__ double sh[kLdsTile4], sh2[kLdsTile4];
   const size_t N = (size_t)1 << logN;
   const unsigned lin = blockIdx.x + gridDim.x * (blockIdx.y + gridDim.y * blockIdx.z);
@@ -201,8 +203,9 @@ __global__ __launch_bounds__(512, 4) void ks_relin_finish_kernel(RelinPack jobs,
   const int S1 = logN - 12, own = i / alpha;
   const size_t ro = (size_t)i * N + t0, ps = (size_t)nl * N;
   double a0[8], a1[8];
-  const double* w0 = w + ((size_t)job * 2 * nout + i) * N + t0;
-  row4_fwd_tile2(w0, w0 + (size_t)nout * N, t0, S1, pr, sh, sh2, a0, a1);
+  const size_t r0 = (size_t)job * 2 * nout + i;
+  row4_fwd_tile2(TileSrc{row_at(w, r0, N, packed), t0, N, packed}, TileSrc{row_at(w, r0 + nout, N, packed), t0, N, packed},
+                 S1, pr, sh, sh2, a0, a1);
   const double c1 = cw != nullptr ? cload(cw + i) : t_mod, c2 = cload(ca + i);
 #pragma unroll
   for (int k = 0; k < 8; ++k) {
@@ -271,7 +274,7 @@ __global__ __launch_bounds__(512, 4) void ks_relin_finish_kernel(RelinPack jobs,
     if (j == own) continue;
     double x[8];
     lds_barrier();   // the tile buffer's previous use is over in every wave
-    row4_fwd_tile(jb.ext + ((size_t)j * nE + i) * N + t0, t0, S1, pr, sh, x);
+    row4_fwd_tile(TileSrc{jb.ext + ((size_t)j * nE + i) * N, t0, N, false}, S1, pr, sh, x);
     mac(j, x);
   }
   // at most eight digits: |a| < 10 q, the product below 2.5 q
@@ -300,8 +303,8 @@ void launch_ks_relin_finish(Context& c, const std::vector<KsRelin>& jobs, const 
     hipEvent_t ev;
     prof_begin(c, 7, &ev);
     hipLaunchKernelGGL(ks_relin_finish_kernel, dim3((unsigned)(c.N / 4096), nout, cnt), dim3(512), 0, c.stream, pk, cnt,
-                       w + first * 2 * nout * c.N, m1, cw, ca, (double)c.t, nout, D, nE, level + 1, c.alpha,
-                       (int)c.log_n, key_ds, c.d_primes);
+                       w + first * 2 * nout * c.row_doubles(), m1, cw, ca, (double)c.t, nout, D, nE, level + 1, c.alpha,
+                       (int)c.log_n, key_ds, c.d_primes, c.packed);
     COPSE_HIP(hipGetLastError());
     prof_end(c, 7, ev, (rows + 2.0 * D) * nout * (double)c.N * 8.0);
   }

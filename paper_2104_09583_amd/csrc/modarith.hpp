@@ -78,6 +78,28 @@ __device__ __forceinline__ T* uniform(T* p) {
 __device__ __forceinline__ double gload_off(const double* p, uint32_t bytes) {
   return *(const __attribute__((address_space(1))) double*)((const char*)p + (size_t)bytes);
 }
+// Packed rows: N values of |x| < 2^47 in six bytes each, as N 32-bit words followed by N 16-bit words of x + 2^47.
+// 2^52 + 2^47 + x has the sum in its low mantissa bits, so packing is an addition and unpacking an or and a
+// subtraction.
+constexpr double kPackBias = 4503599627370496.0 + 140737488355328.0;   // 2^52 + 2^47
+__device__ __forceinline__ double unpack48(uint32_t lo, uint32_t hi) {
+  return __hiloint2double((int)(0x43300000u | hi), (int)lo) - kPackBias;
+}
+__device__ __forceinline__ void pack48(double x, uint32_t& lo, uint16_t& hi) {
+  const double d = x + kPackBias;
+  lo = (uint32_t)__double2loint(d);
+  hi = (uint16_t)__double2hiint(d);
+}
+__device__ __forceinline__ uint32_t gload32_off(const uint32_t* p, uint32_t bytes) {
+  return *(const __attribute__((address_space(1))) uint32_t*)((const char*)p + (size_t)bytes);
+}
+__device__ __forceinline__ uint32_t gload16_off(const uint16_t* p, uint32_t bytes) {
+  return *(const __attribute__((address_space(1))) uint16_t*)((const char*)p + (size_t)bytes);
+}
+// row r of a block of packed or plain rows of N values
+__device__ __forceinline__ const double* row_at(const double* base, size_t r, size_t N, bool packed) {
+  return base + r * (packed ? N / 4 * 3 : N);
+}
 // A load of a value that is uniform across the wave from a table no kernel writes (twiddles, row
 // descriptors, primes, conversion constants): read through the constant address space, so it is a scalar
 // load into scalar registers.

@@ -102,6 +102,29 @@ __device__ __forceinline__ Tw8 tw8_scalar(const double* tab, uint32_t g0, uint32
 __device__ __forceinline__ double tile_load(const double* p, int k) {
   return gload_off(uniform(p + 512 * k), 8 * threadIdx.x);
 }
+// A tile of a row that is plain or packed (see pack48): the row's start, the tile's first element, N
+struct TileSrc {
+  const double* row;
+  size_t t0, N;
+  bool packed;
+};
+__device__ __forceinline__ void tile_read(const TileSrc& s, double (&x)[8]) {
+  if (s.packed) {   // uniform
+    const uint32_t* lo = reinterpret_cast<const uint32_t*>(s.row);
+    const uint16_t* hi = reinterpret_cast<const uint16_t*>(lo + s.N);
+    uint32_t l[8], h[8];
+#pragma unroll
+    for (int k = 0; k < 8; ++k) {
+      l[k] = gload32_off(uniform(lo + s.t0 + 512 * k), 4 * threadIdx.x);
+      h[k] = gload16_off(uniform(hi + s.t0 + 512 * k), 2 * threadIdx.x);
+    }
+#pragma unroll
+    for (int k = 0; k < 8; ++k) x[k] = unpack48(l[k], h[k]);
+  } else {
+#pragma unroll
+    for (int k = 0; k < 8; ++k) x[k] = tile_load(s.row + s.t0, k);
+  }
+}
 __device__ __forceinline__ void tile_store(double* p, int k, double v) {
   auto* q = (__attribute__((address_space(1))) char*)uniform(p + 512 * k);
   *(__attribute__((address_space(1))) double*)(q + (size_t)(uint32_t)(8 * threadIdx.x)) = v;
@@ -140,17 +163,16 @@ constexpr int kLdsTile4 = 4096;
 // addresses; those of the last two rounds are loaded one round ahead, so a small launch waits on memory once.
 // With pre given, the forward tile also loads pre[t + 512 k] into y[k] during its third round (an
 // epilogue's operand, so that its latency overlaps the transform).
-__device__ __forceinline__ void row4_fwd_tile(const double* __restrict__ src, size_t gb0, int S1, const DevPrime& pr,
+__device__ __forceinline__ void row4_fwd_tile(const TileSrc& src, int S1, const DevPrime& pr,
                                               double* sh, double x[8], const double* pre = nullptr,
                                               double* y = nullptr) {
   const int t = threadIdx.x;
-  const uint32_t mA = 1u << S1, mB = mA << 3, mC = mA << 6, mD = mA << 9, tile = (uint32_t)(gb0 >> 12);
+  const uint32_t mA = 1u << S1, mB = mA << 3, mC = mA << 6, mD = mA << 9, tile = (uint32_t)(src.t0 >> 12);
   const LdsPlace lp = lds_place();
   const uint32_t wave = __builtin_amdgcn_readfirstlane(t >> 6);
   const Tw8 wa = tw8_scalar(pr.fwd, tile, mA);
   const Tw8 wb = tw8_scalar(pr.fwd, 8 * tile + wave, mB);
-#pragma unroll
-  for (int k = 0; k < 8; ++k) x[k] = tile_load(src, k);
+  tile_read(src, *reinterpret_cast<double (*)[8]>(x));
   radix8_ct_w(x, wa, pr);
   const Tw8 wc = tw8_load(pr.fwd, 64 * tile, mC, (uint32_t)t >> 3);
 #pragma unroll
@@ -230,20 +252,17 @@ __device__ __forceinline__ void row4_inv_tile(const double* __restrict__ src, si
 // independent work between them.  sh and sh2: one tile buffer each.  The forward pair reads srcA[t + 512 k]
 // and srcB[t + 512 k]; the inverse pair takes the tiles' values at t + 512 k in va and vb.  Results as for
 // one tile, in x and y.
-__device__ __forceinline__ void row4_fwd_tile2(const double* __restrict__ srcA, const double* __restrict__ srcB,
-                                               size_t gb0, int S1, const DevPrime& pr, double* sh, double* sh2,
+__device__ __forceinline__ void row4_fwd_tile2(const TileSrc& srcA, const TileSrc& srcB, int S1,
+                                               const DevPrime& pr, double* sh, double* sh2,
                                                double x[8], double y[8]) {
   const int t = threadIdx.x;
-  const uint32_t mA = 1u << S1, mB = mA << 3, mC = mA << 6, mD = mA << 9, tile = (uint32_t)(gb0 >> 12);
+  const uint32_t mA = 1u << S1, mB = mA << 3, mC = mA << 6, mD = mA << 9, tile = (uint32_t)(srcA.t0 >> 12);
   const LdsPlace lp = lds_place();
   const uint32_t wave = __builtin_amdgcn_readfirstlane(t >> 6);
   const Tw8 wa = tw8_scalar(pr.fwd, tile, mA);
   const Tw8 wb = tw8_scalar(pr.fwd, 8 * tile + wave, mB);
-#pragma unroll
-  for (int k = 0; k < 8; ++k) {
-    x[k] = tile_load(srcA, k);
-    y[k] = tile_load(srcB, k);
-  }
+  tile_read(srcA, *reinterpret_cast<double (*)[8]>(x));
+  tile_read(srcB, *reinterpret_cast<double (*)[8]>(y));
   radix8_ct_w(x, wa, pr);
   radix8_ct_w(y, wa, pr);
   const Tw8 wc = tw8_load(pr.fwd, 64 * tile, mC, (uint32_t)t >> 3);
