@@ -21,6 +21,7 @@
 // lt_k = Th_k - u_k; then S_k = prod_{j>k} eq_j by a Kogge-Stone prefix
 // product over (eq_{p-1}, ..., eq_1) and dec = lt_{p-1} + sum_k lt_k S_k.
 #include <algorithm>
+#include <cstring>
 #include <cmath>
 #include <set>
 
@@ -165,7 +166,7 @@ std::unique_ptr<Model> build_model(Context& c, const Compiled& C, const Keys* k,
     size_t ngs = 0;
     for (auto& P : M->plan_L) ngs += P.groups.size();
     const size_t nu = M->lvl_rots.size();
-    std::vector<const double*> cat(nu * ngs + kMmTabPad, nullptr);
+    std::vector<const double*> cat(nu * ngs, nullptr);
     size_t off = 0;
     for (auto& P : M->plan_L) {
       const size_t ng = P.groups.size();
@@ -173,6 +174,7 @@ std::unique_ptr<Model> build_model(Context& c, const Compiled& C, const Keys* k,
         for (size_t s = 0; s < ng; ++s) cat[u * ngs + off + s] = P.tab[u * ng + s];
       off += ng;
     }
+    cat = mm_table(cat, nu, ngs);
     M->lcat_buf = DBuf(&c, cat.size());
     COPSE_HIP(hipMemcpyAsync(M->lcat_buf.get(), cat.data(), cat.size() * sizeof(const double*), hipMemcpyHostToDevice,
                              c.stream));
@@ -184,6 +186,19 @@ std::unique_ptr<Model> build_model(Context& c, const Compiled& C, const Keys* k,
 }
 
 // ------------------------------------------------------------------ matrix-product plans
+std::vector<const double*> mm_table(const std::vector<const double*>& tab, size_t n_u, size_t n_groups) {
+  const size_t words = (size_t)mm_mask_words((int)n_groups);
+  std::vector<uint32_t> masks((n_u * words + 1) / 2 * 2, 0);
+  for (size_t u = 0; u < n_u; ++u)
+    for (size_t s = 0; s < n_groups; ++s)
+      if (tab[u * n_groups + s] != nullptr) masks[u * words + s / 32] |= 1u << (s % 32);
+  static_assert(sizeof(const double*) == 2 * sizeof(uint32_t), "two mask words per table entry");
+  std::vector<const double*> full(tab);
+  full.resize(n_u * n_groups + kMmTabPad + masks.size() / 2, nullptr);
+  if (!masks.empty()) std::memcpy(full.data() + n_u * n_groups + kMmTabPad, masks.data(), masks.size() * sizeof(uint32_t));
+  return full;
+}
+
 void build_plan(Context& c, MatPlan& P, const std::vector<Operand>& diags, uint32_t n1, bool enc,
                 const std::vector<int32_t>* shared_rots) {
   const uint32_t n = (uint32_t)diags.size();
@@ -219,8 +234,7 @@ void build_plan(Context& c, MatPlan& P, const std::vector<Operand>& diags, uint3
   tab.assign(nu * ng, nullptr);
   for (size_t s = 0; s < ng; ++s)
     for (auto& t : per_group[s]) tab[(size_t)t.first * ng + s] = t.second;
-  std::vector<const double*> padded(tab);
-  padded.resize(tab.size() + kMmTabPad, nullptr);
+  const std::vector<const double*> padded = mm_table(tab, nu, ng);
   P.tab_buf = DBuf(&c, padded.size());
   COPSE_HIP(hipMemcpyAsync(P.tab_buf.get(), padded.data(), padded.size() * sizeof(const double*),
                            hipMemcpyHostToDevice, c.stream));

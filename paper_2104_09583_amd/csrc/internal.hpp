@@ -513,7 +513,15 @@ void launch_md_finish2(Context& c, const std::vector<double*>& out, const std::v
 // MatMul inner sums.  The device table holds kMmTabPad null entries past its end (the kernel fetches
 // whole chunks of a row); tab[u * n_groups + s] is the pre-rotated diagonal that multiplies baby step u in giant
 // group s (plaintext [nl][N], or ciphertext [2][nl][N] when enc), null when that diagonal is zero.
+// After them it holds, for each baby step, which of its diagonals are nonzero: mm_mask_words 32-bit words, group s at
+// bit s % 32 of word s / 32.
 constexpr int kMmTabPad = 32;
+#if defined(__HIPCC__)
+__host__ __device__
+#endif
+inline int mm_mask_words(int n_groups) { return (n_groups + 31) / 32 + 1; }   // one more: a chunk may span two
+// the table with its padding and masks, as the device holds it
+std::vector<const double*> mm_table(const std::vector<const double*>& tab, size_t n_u, size_t n_groups);
 // u0 >= 0: baby step u0 of batch element b is read from b0[b] instead of the baby buffer
 void launch_mm_inner(Context& c, double* out, const double* baby, const double* const* tab, int n_u, int n_groups,
                      int G, int nl, size_t baby_slot, size_t baby_b, bool enc, size_t nnz, int u0 = -1,

@@ -2288,7 +2288,9 @@ __global__ __launch_bounds__(256) void mm_inner_kernel(double* __restrict__ out,
 // coefficients) is fetched once per workgroup, each wave loading every kW-th group, and staged in LDS,
 // double-buffered: the next baby step's tile and baby values are in flight while the current step's
 // products run, and one barrier per baby step hands the tile over.  Which diagonals of a step are zero
-// is a scalar bitmask.  A wave past the end of the batch still loads its share of the tiles.
+// is a scalar bitmask, read from the table (formed here from the pointers, it took more scalar instructions than
+// the products vector ones: 2114 us of MatMul for 16 groups of the 32-tree forest, 1944 with the masks read).
+// fp64 issue bounds it now.  A wave past the end of the batch still loads its share of the tiles.
 template <int GM, bool kEnc, int kW>
 __global__ __launch_bounds__(64 * kW) void mm_inner_batch_kernel(double* __restrict__ out,
                                                                  const double* __restrict__ baby,
@@ -2316,18 +2318,14 @@ __global__ __launch_bounds__(64 * kW) void mm_inner_batch_kernel(double* __restr
   const int fold = mm_fold_every(pr.q, kEnc);
   const size_t o = (size_t)l * N + i, ps = (size_t)nl * N;
   // the first baby step at or after u with a term in the chunk (n_u if none) and its bitmask of groups
+  const int mw = mm_mask_words(ng);
+  const uint32_t* masks = reinterpret_cast<const uint32_t*>(tab + (size_t)n_u * ng + kMmTabPad) + (s0 >> 5);
+  const uint32_t gmask = gm >= 32 ? ~0u : (1u << gm) - 1u;
   auto scan = [&](int u, uint32_t& mask) -> int {
     for (; u < n_u; ++u) {
-      const double* const* row = tab + (size_t)u * ng + s0;
-      // the whole row at once (the table's kMmTabPad trailing entries keep it in bounds), masked to gm
-      uint32_t mk = 0;
-#pragma unroll
-      for (int s = 0; s < GM; ++s) mk |= (cload(row + s) != nullptr ? 1u : 0u) << s;
-      mk &= gm >= 32 ? ~0u : (1u << gm) - 1u;
-      if (mk != 0) {
-        mask = mk;
-        return u;
-      }
+      const uint32_t lo = cload(masks + (size_t)u * mw), hi = cload(masks + (size_t)u * mw + 1);
+      mask = (uint32_t)(((uint64_t)hi << 32 | lo) >> (s0 & 31)) & gmask;
+      if (mask != 0) return u;
     }
     mask = 0;
     return n_u;
@@ -2468,10 +2466,12 @@ void launch_mm_inner(Context& c, double* out, const double* baby, const double* 
     fail(COPSE_EINVAL, "MatMul batch too large");
   hipEvent_t ev;
   prof_begin(c, 9, &ev);
-  // giant groups in chunks of at most 24 (12 with three accumulators each, or for one batch element, whose
-  // kernel holds a step's loads for every group: more, smaller chunks at higher occupancy measured faster),
-  // split evenly
-  const int cap = c.tune.mm_cap > 0 ? std::min(32, std::max(4, c.tune.mm_cap)) : (enc || G == 1 ? 12 : 24);
+  // giant groups in chunks of at most 12, split evenly: three workgroups of eight waves share a compute unit (76
+  // registers), against two at 24 groups, and the baby values a further chunk reads again are in the XCD's L2.  16
+  // groups' queries of the 32-tree forest: 1887 us against 1981 at 24 and 1937 at 8, three groups of the 16-tree forest
+  // 255 against 266 and 252.  (Sums of unreduced products in two doubles each, four instructions a product instead of
+  // seven, ran 2030: their registers leave two workgroups, and the steps then wait on memory.)
+  const int cap = c.tune.mm_cap > 0 ? std::min(32, std::max(4, c.tune.mm_cap)) : 12;
   const int chunks = (ng + cap - 1) / cap;
   const int per = (ng + chunks - 1) / chunks;
   auto run = [&](auto gm_tag) {

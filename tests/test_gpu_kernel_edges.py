@@ -193,3 +193,10 @@ def test_import_of_mixed_shapes(C, log_n):
         assert g["level"] == lv and all((a == b).all() for a, b in zip(g["polys"], polys))
     buf[-1] = qs[1]
     assert C.lib().copse_cts_import(ctx.ptr, ptr, buf.size, ctypes.byref(h)) == C.COPSE_EINVAL
+
+
+# more than 32 and more than 64 giant groups over the levels (one baby step each): the words of the table's masks, and
+# chunks that begin in one word and end in the next
+@pytest.mark.parametrize("trees,enc,groups", [(2, False, 2), (6, False, 8), (2, True, 3), (2, True, 8)])
+def test_matmul_masks_over_several_words(C, trees, enc, groups):
+    evaluate_groups(C, synth.ForestShape(trees, 4, 0.85, 2, 4, 3), 75, 11, (42, 48, 48), 3, enc, groups, n1=(2, 1))
