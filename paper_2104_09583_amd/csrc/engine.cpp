@@ -372,7 +372,9 @@ static void ks_batch(Context& c, int level, const std::vector<const double*>& in
   DBuf ext = modup_batch(c, level, inputs, !no_auto, inputs_b);
   if (fused && add_mode == 2) {
     // rotations: the inner products only where their result is used (keyswitch.hip)
-    DBuf acc(&c, (size_t)R * 2 * c.alpha * N), w(&c, (size_t)R * 2 * nl * RD);
+    // (in copse_evaluate_noalloc the block keeps the size of all extended rows: which models exceed the array does not
+    // depend on the route)
+    DBuf acc(&c, (size_t)R * 2 * (c.no_alloc ? nE : c.alpha) * N), w(&c, (size_t)R * 2 * nl * RD);
     std::vector<KsRot> rots;
     for (const KsReq& rq : reqs)
       rots.push_back(KsRot{inputs[rq.input], ext.get() + (size_t)rq.input * D * nE * N, rq.key->b.get(),

@@ -96,11 +96,13 @@ class ScratchPool : public Pool {
 struct NoAllocScope {
   Context& c;
   std::shared_ptr<Pool> saved;
-  bool prof;
-  NoAllocScope(Context& c_, std::shared_ptr<Pool> scratch_pool) : c(c_), saved(c_.pool), prof(c_.profiling) {
+  bool prof, packed;
+  NoAllocScope(Context& c_, std::shared_ptr<Pool> scratch_pool)
+      : c(c_), saved(c_.pool), prof(c_.profiling), packed(c_.packed) {
     c.pool = std::move(scratch_pool);
     c.profiling = false;
     c.no_alloc = true;
+    c.packed = false;   // a call's demand on the array, and so which models it refuses, is that of plain rows
   }
   ~NoAllocScope() {
     (void)hipStreamSynchronize(c.stream);
@@ -110,6 +112,7 @@ struct NoAllocScope {
     c.no_alloc = false;
     c.pool = saved;
     c.profiling = prof;
+    c.packed = packed;
   }
 };
 
