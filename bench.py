@@ -59,9 +59,11 @@ KIND_NAMES = {0: "ntt_fwd_rows", 1: "ntt_fwd_cols", 2: "ntt_inv_rows", 3: "ntt_i
 KERNEL_KINDS = (0, 1, 2, 3, 4, 5, 6, 7, 8, 9, 10, 15, 16)
 STAGE_NAMES = ("comparison", "reshuffle", "levels", "aggregation")
 # kernel of each class (for the counter runs); class 6 is a family of small kernels and is not a roofline
-# (name patterns for rocprofv3's kernel filter: class 7 is the ModDown finishes, alone and merged with the switch)
-KIND_KERNELS = {0: "ntt_rowreg4_kernel<false>", 2: "ntt_rowreg4_kernel<true>", 4: "ks_inner2",
-                5: "ntt_bridge_kernel", 7: "ntt_rowfwd_finish_kernel<[13]>", 8: "ntt_rowfwd_finish_kernel<2>",
+# (name patterns for rocprofv3's kernel filter: class 7 is the ModDown finishes, alone, merged with the switch and with
+# the data rows' inner products inside)
+KIND_KERNELS = {0: "ntt_rowreg4_kernel<false>", 2: "ntt_rowreg4_kernel<true>", 4: "ks_rot_special|ks_inner2",
+                5: "ntt_bridge_kernel", 7: "ntt_rowfwd_finish_kernel<[13]>|ks_rot_finish|ks_relin_finish",
+                8: "ntt_rowfwd_finish_kernel<[24]>",
                 9: "mm_inner", 10: "ntt_rowinv_gather_kernel", 15: "ks_inner_rows", 16: "ks_inner_gsum"}
 
 
@@ -69,16 +71,14 @@ def measured_traffic(kind: str, workload: str):
     """HBM bytes per launch of the roofline kernel from the committed counter runs
     (profiles/hbm_bytes_<kind>_<workload>.json, written by paper_2104_09583_amd.pmc_traffic);
     None when there is none or the kernels' source changed since the counters were taken."""
-    import hashlib
+    from paper_2104_09583_amd.pmc_traffic import kernel_source_sha256
     path = os.path.join(ROOT, "profiles", f"hbm_bytes_{kind}_{workload}.json")
-    src = os.path.join(ROOT, "paper_2104_09583_amd", "csrc", "kernels.hip")
     if not os.path.exists(path):
         return None
     with open(path) as f:
         doc = json.load(f)
-    with open(src, "rb") as f:
-        if hashlib.sha256(f.read()).hexdigest() != doc["kernels_hip_sha256"]:
-            return None
+    if kernel_source_sha256() != doc.get("kernel_source_sha256"):
+        return None
     return doc["bytes_per_dispatch"]
 
 

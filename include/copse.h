@@ -138,8 +138,7 @@ size_t copse_ctx_device_bytes(const copse_ctx* ctx);
  * that log_n and top_level, batch_lo <= G <= batch_hi and a matching model
  * kind (model: -1 any, 0 plaintext, 1 encrypted); a knob of 0 (or no
  * matching entry) keeps the built-in choice.  Knobs: mm_cap, giant groups per
- * register tile of the MatMul inner sums (4..32; built in: 24 for several
- * groups of a plaintext model, else 12); mm_waves, batch elements per MatMul
+ * register tile of the MatMul inner sums (4..32; built in 12); mm_waves, batch elements per MatMul
  * workgroup when G is a multiple of 8 (4 or 8; built in 8); ks_jobs,
  * key-switch inner products per launch (1..32; built in 32); bridge_wgs, the
  * workgroup count under which the fused column pass of a base change gives
@@ -404,17 +403,18 @@ int copse_poly_mul(copse_ctx* ctx, int prime, const uint64_t* a, const uint64_t*
  * operation read or written once; each distinct key's rows counted once per
  * launch; twiddle tables not counted).  kind: 0 = forward NTT row pass, 1 = forward
  * NTT column pass (unfused path), 2 = inverse NTT row pass, 3 = inverse NTT
- * column pass (unfused path), 4 = key-switch inner product, 5 = base
+ * column pass (unfused path), 4 = the rotations' key-switch inner products (on the
+ * fused path their special rows, with the inverse row pass), 5 = base
  * conversion (fused with the column passes where available), 6 = other
- * elementwise kernels, 7 = forward row pass with the ModDown finish,
+ * elementwise kernels, 7 = forward row pass with the ModDown finish (and, for
+ * rotations and large relinearizations, the data rows' inner products inside),
  * 8 = forward row pass with the modulus-switch finish, 9 = MatMul inner sums,
  * 10 = inverse row pass reading ciphertext rows in place; 11..14 = the
  * stages of an evaluation (comparison, reshuffle product, level products with
  * masks, product tree with the final switch: the breakdown of Section 8),
  * bracketed on the evaluating stream, bytes 0; 15 = relinearization inner
  * products with the ModUp's forward and the ModDown's inverse row passes
- * inside, 16 = giant-step sums of key-switch inner products (kind 4 is then
- * the rotations' inner products).  reset clears the counters. */
+ * inside, 16 = giant-step sums of key-switch inner products.  reset clears the counters. */
 int copse_profile_enable(copse_ctx* ctx, int on);
 int copse_profile_read(copse_ctx* ctx, int kind, uint64_t* launches, double* total_ms,
                        double* bytes, int reset);

@@ -367,7 +367,8 @@ static void ks_batch(Context& c, int level, const std::vector<const double*>& in
   if (inputs_b && (!merge || inputs_b->size() != inputs.size()))
     fail(COPSE_EINVAL, "internal: product inputs only for the merged relinearization");
   // relinearizations (no automorphism) fold the ModUp's forward row pass and the ModDown's inverse row
-  // pass into the inner products (two launches fewer, the extended rows never written in NTT form)
+  // pass into the inner products (two launches fewer, the extended rows never written in NTT form); fused
+  // rotations return below
   const bool no_auto = fused && add_mode == 1;
   DBuf ext = modup_batch(c, level, inputs, !no_auto, inputs_b);
   if (fused && add_mode == 2) {
@@ -409,21 +410,12 @@ static void ks_batch(Context& c, int level, const std::vector<const double*>& in
   const bool inline_data = no_auto && (size_t)(N / 4096) * back * R >= 1024;
   if (no_auto)
     launch_ks_inner_rows(c, jobs, D, nE, level, (size_t)Lt * N, merge ? T.mm_ptop : 0.0, back, inline_data ? back : 0);
-  else launch_ks_inner2(c, jobs, D, nE, level, (size_t)Lt * N, merge ? T.mm_ptop : 0.0);
+  else launch_ks_inner2(c, jobs, D, nE, level, (size_t)Lt * N);
   if (merge) {
     // ModDown by P and switch by q_l in one pass: the top data row (now y_l + P a_l) joins the special rows
     // in the inverse transform, the fused column pass lifts the switched top limb, and the finish writes
     // the result at level - 1
     const int l = level;
-    const int2* r = rows_cached(c, "mdmsrows:" + std::to_string(level) + ":" + std::to_string(2 * R), [&] {
-      std::vector<int2> h;
-      for (int k = 0; k < 2 * R; ++k) {
-        for (int s2 = 0; s2 < c.alpha; ++s2) h.push_back(make_int2(k * nE + nl + s2, c.L + 1 + s2));
-        h.push_back(make_int2(k * nE + l, l));
-      }
-      return h;
-    }());
-    if (!no_auto) launch_ntt_inv_rows(c, acc.get(), r, 2 * R * (c.alpha + 1));
     std::vector<int2> inr, outr;
     for (int s2 = 0; s2 < c.alpha; ++s2) inr.push_back(make_int2(nl + s2, c.L + 1 + s2));
     inr.push_back(make_int2(l, l));
@@ -451,26 +443,15 @@ static void ks_batch(Context& c, int level, const std::vector<const double*>& in
                                     nullptr, 0, inputs_b ? &adds_b : nullptr);
     return;
   }
-  // ModDown of all accumulators
-  {
-    std::string key = "mdspec:" + std::to_string(level) + ":" + std::to_string(2 * R);
-    auto it = c.row_tables.find(key);
-    const int2* r;
-    if (it != c.row_tables.end()) {
-      r = it->second;
-    } else {
+  // ModDown of all accumulators (the fused inner products leave the special rows transformed back)
+  if (!fused) {
+    const int2* r = rows_cached(c, "mdspec:" + std::to_string(level) + ":" + std::to_string(2 * R), [&] {
       std::vector<int2> h;
       for (int k = 0; k < 2 * R; ++k)
         for (int s = 0; s < c.alpha; ++s) h.push_back(make_int2(k * nE + nl + s, c.L + 1 + s));
-      r = c.rows(key, h);
-    }
-    if (no_auto) {
-      // done by the fused inner product
-    } else if (fused) {
-      launch_ntt_inv_rows(c, acc.get(), r, 2 * R * c.alpha);
-    } else {
-      launch_ntt_inv(c, acc.get(), r, 2 * R * c.alpha);
-    }
+      return h;
+    }());
+    launch_ntt_inv(c, acc.get(), r, 2 * R * c.alpha);
   }
   DBuf zh(&c, (size_t)2 * R * nl * (fused ? RD : N));
   std::vector<int2> inr, outr;
@@ -497,12 +478,11 @@ static void ks_batch(Context& c, int level, const std::vector<const double*>& in
     }
     launch_ntt_fwd_rows_md_finish(c, outs, adds, acc.get(), zh.get(), nE, nl, T.d_md_pinv, T.d_md_tpinv);
     return;
-  } else {
-    launch_bconv(c, zh.get(), rows_cached(c, "mdout:" + std::to_string(level), outr), nl, acc.get(),
-                 rows_cached(c, "mdin:" + std::to_string(level), inr), c.alpha, T.d_md_mult, T.d_md_mat, 2 * R,
-                 (size_t)nE * N, (size_t)nl * N);
-    launch_ntt_fwd(c, zh.get(), block_rows(c, 2 * R, nl), 2 * R * nl);
   }
+  launch_bconv(c, zh.get(), rows_cached(c, "mdout:" + std::to_string(level), outr), nl, acc.get(),
+               rows_cached(c, "mdin:" + std::to_string(level), inr), c.alpha, T.d_md_mult, T.d_md_mat, 2 * R,
+               (size_t)nE * N, (size_t)nl * N);
+  launch_ntt_fwd(c, zh.get(), block_rows(c, 2 * R, nl), 2 * R * nl);
   launch_md_finish2(c, outs, adds, gal, acc.get(), zh.get(), nE, nl, T.d_md_pinv, T.d_md_tpinv, add_mode);
 }
 

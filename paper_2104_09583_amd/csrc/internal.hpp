@@ -325,8 +325,8 @@ void launch_ntt_fwd_rows_ms_finish(Context& c, const std::vector<double*>& out, 
                                    const std::vector<const double*>* add, int add_np,
                                    const std::vector<const double*>* mulp = nullptr);
 // One coefficient map of the fused column pass: rows of the input block (index, prime), rows of the
-// output block, per-input multipliers and the [n_in][n_out] matrix (mode 0).  Several maps over the same input and output blocks (the digits of a ModUp) run as one
-// launch.
+// output block, per-input multipliers and the [n_in][n_out] matrix (mode 0).  Several maps over the same input and
+// output blocks (the digits of a ModUp) run as one launch.
 struct BridgeDesc {
   const int2* out_rows;
   const int2* in_rows;
@@ -433,9 +433,7 @@ void launch_tensor_multi(Context& c, const std::vector<double*>& d, const std::v
 void launch_ms_finish_multi(Context& c, const std::vector<double*>& out, const std::vector<const double*>& in,
                             const double* w, int np, int level, const double* tab,
                             const std::vector<const double*>* add = nullptr, int add_np = 0);
-// ptop: P mod q_level, the factor of the jobs' top addends
-void launch_ks_inner2(Context& c, const std::vector<KsJob2>& jobs, int D, int nE, int level, size_t key_ds,
-                      double ptop = 0.0);
+void launch_ks_inner2(Context& c, const std::vector<KsJob2>& jobs, int D, int nE, int level, size_t key_ds);
 // the same for jobs without automorphism (g = 1) whose ext holds the ModUp rows after the column stages
 // only: the forward row pass is done inside (relinearizations); extended rows inv_from.. nE - 1 of acc
 // are written after the inverse row pass (the rows the ModDown transforms back; nE: none), and only rows from

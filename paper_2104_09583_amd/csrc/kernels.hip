@@ -1035,14 +1035,12 @@ void launch_ntt_fwd_rows_mdms_finish(Context& c, const std::vector<double*>& out
     const int cnt = (int)std::min<size_t>(kPack, out.size() - first);
     MPack po;
     Pack pa, pm, pb{}, none{};
-    GPack pg;
     IPack nolv{};
     for (int k = 0; k < cnt; ++k) {
       po.p[k] = out[first + k];
       pa.p[k] = add[first + k];
       pm.p[k] = masks ? (*masks)[first + k] : nullptr;
       if (add_b) pb.p[k] = (*add_b)[first + k];
-      pg.g[k] = 1;
     }
     hipEvent_t ev;
     prof_begin(c, 7, &ev);
@@ -1068,7 +1066,6 @@ void launch_ntt_fwd_rows_ms_finish(Context& c, const std::vector<double*>& out, 
     const int cnt = (int)std::min<size_t>(per, out.size() - first);
     MPack po;
     Pack pi, pa, pw, pt, pm{};
-    GPack pg;
     IPack lv{};
     int lmax = 0;
     double bytes = 0;
@@ -1079,7 +1076,6 @@ void launch_ntt_fwd_rows_ms_finish(Context& c, const std::vector<double*>& out, 
       if (mulp) pm.p[k] = (*mulp)[first + k];
       pw.p[k] = w[first + k];
       pt.p[k] = tabs[first + k];
-      pg.g[k] = 1;
       lv.v[k] = levels[first + k];
       const int nl = lv.v[k] & 0xffff;
       lmax = std::max(lmax, nl);
@@ -1597,12 +1593,13 @@ __device__ __forceinline__ void ks_tensor_top(double& t0, double& t1, double b0,
   t1 = mul_lazy(a0, b1, pr.q, pr.qinv) + mul_lazy(t1, b0, pr.q, pr.qinv);
 }
 
-// key-switch inner product over jobs; digit rows come straight from the job's input poly (a product's
-// third polynomial in (.) in_b when in_b is set).  kD > 0: the digit count, known at compile time, so every
-// digit's loads are issued before the first product (kD = 0: any count, one digit at a time).
+// key-switch inner product over jobs, for the key switches of separate passes (rings outside the split transform,
+// rotations of more than eight digits); digit rows come straight from the job's input poly.  kD > 0: the digit
+// count, known at compile time, so every digit's loads are issued before the first product (kD = 0: any count, one
+// digit at a time).
 template <int kD>
 __global__ void ks_inner2_kernel(KsPack jobs, int D_, int nE, int nl, int L, int alpha, int logN, size_t key_ds,
-                                 const DevPrime* P, double ptop) {
+                                 const DevPrime* P) {
   const size_t N = (size_t)1 << logN;
   const size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (i >= N) return;
@@ -1612,11 +1609,8 @@ __global__ void ks_inner2_kernel(KsPack jobs, int D_, int nE, int nl, int L, int
   const DevPrime& pr = P[prime];
   const size_t src = jb.g == 1 ? i : auto_src((uint32_t)i, jb.g, logN);
   const int own = o < nl ? o / alpha : -1;   // digit whose own limb this row is
-  // digit j's row: the input's own limb, else the ModUp output; a product's own limb is a1 (.) b1, b1's
-  // value (ob) loaded with the others and multiplied in after the loads
+  // digit j's row: the input's own limb, else the ModUp output
   auto row = [&](int j) -> const double* { return j == own ? jb.in + (size_t)o * N : jb.ext + ((size_t)j * nE + o) * N; };
-  const bool prod = own >= 0 && jb.in_b != nullptr;   // uniform
-  const double ob = prod ? jb.in_b[(size_t)o * N + src] : 0.0;
   // lazy sums: each product is in (-0.91 q, 0.91 q); D <= 8 digits stay far below 2^52
   double a0 = 0.0, a1 = 0.0;
   if (kD > 0) {
@@ -1631,24 +1625,16 @@ __global__ void ks_inner2_kernel(KsPack jobs, int D_, int nE, int nl, int L, int
     }
 #pragma unroll
     for (int j = 0; j < kD; ++j) {
-      const double ej = prod && j == own ? mul_lazy(e[j], ob, pr.q, pr.qinv) : e[j];
-      a0 += mul_lazy(ej, kb[j], pr.q, pr.qinv);
-      a1 += mul_lazy(ej, ka[j], pr.q, pr.qinv);
+      a0 += mul_lazy(e[j], kb[j], pr.q, pr.qinv);
+      a1 += mul_lazy(e[j], ka[j], pr.q, pr.qinv);
     }
   } else {
     for (int j = 0; j < D_; ++j) {
-      double e = row(j)[src];
-      if (prod && j == own) e = mul_lazy(e, ob, pr.q, pr.qinv);
+      const double e = row(j)[src];
       const size_t ko = (size_t)j * key_ds + (size_t)prime * N + i;
       a0 += mul_lazy(e, jb.kb[ko], pr.q, pr.qinv);
       a1 += mul_lazy(e, jb.ka[ko], pr.q, pr.qinv);
     }
-  }
-  if (jb.top != nullptr && o == nl - 1) {   // uniform per workgroup
-    double t0 = jb.top[(size_t)o * N + i], t1 = jb.top[((size_t)nl + o) * N + i];
-    if (jb.top_b != nullptr) ks_tensor_top(t0, t1, jb.top_b[(size_t)o * N + i], jb.top_b[((size_t)nl + o) * N + i], pr);
-    a0 += mul_lazy(t0, ptop, pr.q, pr.qinv);
-    a1 += mul_lazy(t1, ptop, pr.q, pr.qinv);
   }
   jb.acc[(size_t)o * N + i] = canon(reduce_sym(a0, pr.q, pr.qinv), pr.q);
   jb.acc[((size_t)nE + o) * N + i] = canon(reduce_sym(a1, pr.q, pr.qinv), pr.q);
@@ -1666,8 +1652,7 @@ static double ks_pack_bytes(const Context& c, const KsPack& pk, int cnt, int D, 
   return rows * (double)c.N * 8.0;
 }
 
-void launch_ks_inner2(Context& c, const std::vector<KsJob2>& jobs, int D, int nE, int level, size_t key_ds,
-                      double ptop) {
+void launch_ks_inner2(Context& c, const std::vector<KsJob2>& jobs, int D, int nE, int level, size_t key_ds) {
   const size_t per = c.tune.ks_jobs > 0 ? (size_t)std::min(c.tune.ks_jobs, KsPack::kMax) : KsPack::kMax;
   for (size_t first = 0; first < jobs.size(); first += per) {
     int cnt = (int)std::min<size_t>(per, jobs.size() - first);
@@ -1678,7 +1663,7 @@ void launch_ks_inner2(Context& c, const std::vector<KsJob2>& jobs, int D, int nE
     const dim3 grid((unsigned)((c.N + 255) / 256), nE, cnt);
 #define COPSE_KS2(KD)                                                                                          \
   hipLaunchKernelGGL(ks_inner2_kernel<KD>, grid, dim3(256), 0, c.stream, pk, D, nE, level + 1, c.L, c.alpha, \
-                     (int)c.log_n, key_ds, c.d_primes, ptop)
+                     (int)c.log_n, key_ds, c.d_primes)
     switch (D) {
       case 1: COPSE_KS2(1); break;
       case 2: COPSE_KS2(2); break;

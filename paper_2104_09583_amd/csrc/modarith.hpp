@@ -43,8 +43,9 @@ __device__ __forceinline__ double mod_reduce(double v, double q, double qinv) {
 // In general |mul_lazy(a, b)| <= (0.5 + 3 x 2^-53 |a|) q: the quotient estimate is off by three roundings.
 // Forward, a stage adds one such product to |x|: from |x| <= q six stages reach at most 7.6 q < 2^52 for
 // q = 2^49, every value still an exact integer, so the row pass folds back once, after its second radix-8
-// round; for q < 2^46 (kFwdLazy) its twelve stages stay below 20 q even from 8 q, and it never does.  Inverse, a stage doubles the sums: 2^3 per round, folded back after every round, or for
-// q < 2^44 (kInvLazy) after every second one (64 q <= 2^50).  For q < 2^42 (kInvOpen) the inverse row pass
+// round; for q < 2^46 (kFwdLazy) its twelve stages stay below 20 q even from 8 q, and it never does.  Inverse, a
+// stage doubles the sums: 2^3 per round, folded back after every round, or for q < 2^44 (kInvLazy) after every second
+// one (64 q <= 2^50).  For q < 2^42 (kInvOpen) the inverse row pass
 // also leaves its output unreduced (32 q): three column stages that follow reach 256 q <= 2^50, where the
 // next product is still within 0.875 q (four: 512 q, within 1.25 q and folded back there).
 constexpr double kFwdLazy = 70368744177664.0;   // 2^46

@@ -143,7 +143,8 @@ static void ct_words(Context& c, const Ct& a, uint64_t* out) {
 // Two pinned slots: a ciphertext's words are written into one by the kernel that makes them while the host copies the
 // other out to the caller's buffer (the runtime's copy to pageable memory is a staging kernel and a wait of its own).
 // Against copying from device memory: 16 results exported after a batched evaluation 16.68 -> 16.39 ms together, a fresh
-// group of eight planes (42 MB, to fresh pages) encrypted and exported 5.41 -> 4.28 ms.  A ciphertext beyond a slot goes through device memory.
+// group of eight planes (42 MB, to fresh pages) encrypted and exported 5.41 -> 4.28 ms.  A ciphertext beyond a slot
+// goes through device memory.
 constexpr size_t kExportSlotMax = (size_t)8 << 20;
 
 // slots of at least min(need, kExportSlotMax) bytes

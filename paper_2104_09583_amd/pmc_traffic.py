@@ -27,6 +27,15 @@ CALIB_BYTES = 256 << 20
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 
 
+def kernel_source_sha256() -> str:
+    """Of the files the evaluation's kernels are compiled from."""
+    h = hashlib.sha256()
+    for name in ("modarith.hpp", "rowtile.hpp", "kernels.hip", "keyswitch.hip"):
+        with open(os.path.join(ROOT, "paper_2104_09583_amd", "csrc", name), "rb") as f:
+            h.update(f.read())
+    return h.hexdigest()
+
+
 def read_counter(path: str, counter: str):
     rows = []
     with open(path) as f:
@@ -53,8 +62,7 @@ def main():
     n = int(round(k["launches_per_step"] * bench["steps"]))
     out = {"workload": bench["config"]["workload"], "kind": a.kind, "kernel_regex": a.regex,
            "commands": a.command}
-    with open(os.path.join(ROOT, "paper_2104_09583_amd", "csrc", "kernels.hip"), "rb") as f:
-        out["kernels_hip_sha256"] = hashlib.sha256(f.read()).hexdigest()
+    out["kernel_source_sha256"] = kernel_source_sha256()
     per = {}
     for name, path, counter in (("fetch", a.fetch, "FETCH_SIZE"), ("write", a.write, "WRITE_SIZE")):
         rows = read_counter(path, counter)
