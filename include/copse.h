@@ -138,7 +138,8 @@ size_t copse_ctx_device_bytes(const copse_ctx* ctx);
  * that log_n and top_level, batch_lo <= G <= batch_hi and a matching model
  * kind (model: -1 any, 0 plaintext, 1 encrypted); a knob of 0 (or no
  * matching entry) keeps the built-in choice.  Knobs: mm_cap, giant groups per
- * register tile of the MatMul inner sums (4..32; built in 12); mm_waves, batch elements per MatMul
+ * register tile of the MatMul inner sums (4..32; built in 12, or 8
+ * for an encrypted model in multiples of 8 groups); mm_waves, batch elements per MatMul
  * workgroup when G is a multiple of 8 (4 or 8; built in 8); ks_jobs,
  * key-switch inner products per launch (1..32; built in 32); bridge_wgs, the
  * workgroup count under which the fused column pass of a base change gives

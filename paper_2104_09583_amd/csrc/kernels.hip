@@ -2268,6 +2268,41 @@ __global__ __launch_bounds__(256) void mm_inner_kernel(double* __restrict__ out,
   }
 }
 
+// A sum of unreduced products in two doubles, for an encrypted model's inner sums of eight batch elements: hi = m + the products rounded to
+// multiples of 2^s, lo = what the roundings left.  With m = 1.5 x 2^(52 + s) every value of hi lies in one binade, so a
+// fused multiply-add into it rounds the product to a multiple of 2^s, the difference of its two values is that multiple,
+// and a second fused multiply-add gives the rest exactly: four instructions a product instead of the seven of a reduced
+// product and its addition.  The 64-tree encrypted model's MatMul, bound by fp64 issue, took 23.3 ms a launch of 16
+// groups without and takes 20.2 so; of the 8-tree one's 1441 and 1387 us.  With four batch elements to a workgroup the
+// sums wait on memory, which the registers of the second double leave less overlap (three groups 375 and 396 us), and a
+// plaintext model's products are half as many to a diagonal (2030 us against 1887 for 16 groups of the 32-tree forest).
+// Operands are below 2^b, b one more than the bits of the prime (the middle products' operands are sums of two
+// residues).  n products keep hi in its binade for n 2^(2 b) <= 2^(51 + s) and lo within 2^52 for n 2^(s - 1) <= 2^52:
+// n = 2^(52 - b) and s = b + 1 meet both (512 products for primes below 2^42, 4 for the largest).
+struct MmSum {
+  double hi, lo;
+};
+struct MmSplit {
+  double m;
+  int fold;
+};
+__device__ __forceinline__ MmSplit mm_split(double q) {
+  const int b = __builtin_amdgcn_readfirstlane((int)((__double2hiint(q) >> 20) & 0x7ff) - 1022) + 1;
+  return {__hiloint2double((1023 + 53 + b) << 20 | 1 << 19, 0), 1 << (52 - b)};
+}
+__device__ __forceinline__ void mm_add(MmSum& a, double x, double d) {
+  const double t = __fma_rn(x, d, a.hi);
+  const double h = t - a.hi;
+  a.hi = t;
+  a.lo += __fma_rn(x, d, -h);
+}
+// the sum's residue, within q / 2: hi - m is below 2^(52 + b), its quotient below 2^54 and so estimated within four; what
+// is left is below 4.5 q, and with lo below 2^53
+__device__ __forceinline__ double mm_value(const MmSum& a, const MmSplit& sp, const DevPrime& pr) {
+  const double h = a.hi - sp.m;
+  return reduce_sym(__fma_rn(-rint(h * pr.qinv), pr.q, h) + a.lo, pr.q, pr.qinv);
+}
+
 // Several batch elements: a workgroup is 64 coefficients x kW batch elements (one per wave; kW = 4 or 8).
 // The waves need the same diagonal values, so a baby step's diagonal tile (GM groups x 1 or 2 polys x 64
 // coefficients) is fetched once per workgroup, each wave loading every kW-th group, and staged in LDS,
@@ -2277,13 +2312,15 @@ __global__ __launch_bounds__(256) void mm_inner_kernel(double* __restrict__ out,
 // the products vector ones: 2114 us of MatMul for 16 groups of the 32-tree forest, 1944 with the masks read).
 // fp64 issue bounds it now.  A wave past the end of the batch still loads its share of the tiles.
 template <int GM, bool kEnc, int kW>
-__global__ __launch_bounds__(64 * kW) void mm_inner_batch_kernel(double* __restrict__ out,
+__global__ __launch_bounds__(64 * kW, kEnc && kW == 8 && GM <= 8 ? 4 : 1) void mm_inner_batch_kernel(double* __restrict__ out,
                                                                  const double* __restrict__ baby,
                                                                  const double* const* __restrict__ tab, int n_u,
                                                                  int ng, int G, int nl, size_t baby_slot,
                                                                  size_t baby_b, const DevPrime* P, int logN, Pack b0,
                                                                  int u0) {
   constexpr int kNp = kEnc ? 3 : 2, kNd = kEnc ? 2 : 1;
+  // sums of unreduced products for an encrypted model's eight batch elements
+  constexpr bool kSplit = kEnc && kW == 8;
   constexpr int kPer = (GM + kW - 1) / kW;   // groups of a tile one wave loads
   static_assert(GM <= 32, "one bit per group");
   __shared__ double dl[2][GM][kNd][kMmLanes];
@@ -2300,7 +2337,8 @@ __global__ __launch_bounds__(64 * kW) void mm_inner_batch_kernel(double* __restr
   // the prime and the table entries as scalar loads: a vector load's wait inside the products would
   // also wait for the next tile
   const DevPrime pr = cload_prime(P + l);
-  const int fold = mm_fold_every(pr.q, kEnc);
+  const MmSplit sp = mm_split(pr.q);
+  const int fold = kSplit ? sp.fold : mm_fold_every(pr.q, kEnc);
   const size_t o = (size_t)l * N + i, ps = (size_t)nl * N;
   // the first baby step at or after u with a term in the chunk (n_u if none) and its bitmask of groups
   const int mw = mm_mask_words(ng);
@@ -2349,11 +2387,24 @@ __global__ __launch_bounds__(64 * kW) void mm_inner_batch_kernel(double* __restr
         for (int p = 0; p < kNd; ++p) dl[buf][s][p][lane] = r[k][p];
     }
   };
-  double acc[GM][kNp];
+  using Sum = typename std::conditional<kSplit, MmSum, double>::type;
+  Sum acc[GM][kNp];
+  auto clear = [&](Sum& v, double r) {
+    if constexpr (kSplit) v = MmSum{sp.m, r};
+    else v = r;
+  };
+  auto value = [&](const Sum& v) {
+    if constexpr (kSplit) return mm_value(v, sp, pr);
+    else return reduce_sym(v, pr.q, pr.qinv);
+  };
+  auto add = [&](Sum& v, double x, double d) {
+    if constexpr (kSplit) mm_add(v, x, d);
+    else v += mul_lazy(x, d, pr.q, pr.qinv);
+  };
 #pragma unroll
   for (int s = 0; s < GM; ++s)
 #pragma unroll
-    for (int p = 0; p < kNp; ++p) acc[s][p] = 0.0;
+    for (int p = 0; p < kNp; ++p) clear(acc[s][p], 0.0);
   uint32_t mask;
   int u = scan(0, mask);
   if (u < n_u) {
@@ -2375,16 +2426,16 @@ __global__ __launch_bounds__(64 * kW) void mm_inner_batch_kernel(double* __restr
         // the products (a slot without a diagonal holds 0.0 and adds exactly zero)
         if (kEnc || ((mask >> s) & 1u)) {
           const double d0 = dl[buf][s][0][lane];
-          if (kEnc) {
+          if constexpr (kEnc) {
             // three products (Karatsuba): acc[1] holds sum (x0 + x1)(d0 + d1), and a0 b1 + a1 b0 is formed
             // from it and the other two sums at the end (exact mod q)
             const double d1 = dl[buf][s][kNd - 1][lane];
-            acc[s][0] += mul_lazy(x0, d0, pr.q, pr.qinv);
-            acc[s][1] += mul_lazy(xs, d0 + d1, pr.q, pr.qinv);
-            acc[s][kNp - 1] += mul_lazy(x1, d1, pr.q, pr.qinv);
+            add(acc[s][0], x0, d0);
+            add(acc[s][1], xs, d0 + d1);
+            add(acc[s][kNp - 1], x1, d1);
           } else {
-            acc[s][0] += mul_lazy(x0, d0, pr.q, pr.qinv);
-            acc[s][1] += mul_lazy(x1, d0, pr.q, pr.qinv);
+            add(acc[s][0], x0, d0);
+            add(acc[s][1], x1, d0);
           }
         }
       }
@@ -2393,7 +2444,7 @@ __global__ __launch_bounds__(64 * kW) void mm_inner_batch_kernel(double* __restr
 #pragma unroll
         for (int s = 0; s < GM; ++s)
 #pragma unroll
-          for (int p = 0; p < kNp; ++p) acc[s][p] = reduce_sym(acc[s][p], pr.q, pr.qinv);
+          for (int p = 0; p < kNp; ++p) clear(acc[s][p], value(acc[s][p]));
       }
     }
     if (un < n_u) stage(buf ^ 1);
@@ -2410,9 +2461,12 @@ __global__ __launch_bounds__(64 * kW) void mm_inner_batch_kernel(double* __restr
   for (int s = 0; s < GM; ++s) {
     if (s < gm) {
       double* op = out + ((size_t)(s0 + s) * G + b) * kNp * ps;
-      if constexpr (kEnc) mm_karatsuba_mid(acc[s], pr.q, pr.qinv);
+      double v[kNp];
 #pragma unroll
-      for (int p = 0; p < kNp; ++p) op[(size_t)p * ps + o] = canon(reduce_sym(acc[s][p], pr.q, pr.qinv), pr.q);
+      for (int p = 0; p < kNp; ++p) v[p] = value(acc[s][p]);
+      if constexpr (kEnc) v[1] = reduce_sym(v[1] - v[0] - v[kNp - 1], pr.q, pr.qinv);
+#pragma unroll
+      for (int p = 0; p < kNp; ++p) op[(size_t)p * ps + o] = canon(v[p], pr.q);
     }
   }
 }
@@ -2454,9 +2508,10 @@ void launch_mm_inner(Context& c, double* out, const double* baby, const double* 
   // giant groups in chunks of at most 12, split evenly: three workgroups of eight waves share a compute unit (76
   // registers), against two at 24 groups, and the baby values a further chunk reads again are in the XCD's L2.  16
   // groups' queries of the 32-tree forest: 1887 us against 1981 at 24 and 1937 at 8, three groups of the 16-tree forest
-  // 255 against 266 and 252.  (Sums of unreduced products in two doubles each, four instructions a product instead of
-  // seven, ran 2030: their registers leave two workgroups, and the steps then wait on memory.)
-  const int cap = c.tune.mm_cap > 0 ? std::min(32, std::max(4, c.tune.mm_cap)) : 12;
+  // 255 against 266 and 252.  At most 8 where the sums take two doubles: two workgroups (122 registers) against one,
+  // 20.2 ms against 25.8 for the 64-tree encrypted model.
+  const bool split = enc && G % 8 == 0 && c.tune.mm_waves != 4;
+  const int cap = c.tune.mm_cap > 0 ? std::min(32, std::max(4, c.tune.mm_cap)) : split ? 8 : 12;
   const int chunks = (ng + cap - 1) / cap;
   const int per = (ng + chunks - 1) / chunks;
   auto run = [&](auto gm_tag) {

@@ -200,3 +200,11 @@ def test_import_of_mixed_shapes(C, log_n):
 @pytest.mark.parametrize("trees,enc,groups", [(2, False, 2), (6, False, 8), (2, True, 3), (2, True, 8)])
 def test_matmul_masks_over_several_words(C, trees, enc, groups):
     evaluate_groups(C, synth.ForestShape(trees, 4, 0.85, 2, 4, 3), 75, 11, (42, 48, 48), 3, enc, groups, n1=(2, 1))
+
+
+# an encrypted model's sums of unreduced products (eight batch elements to a workgroup): the fold interval goes with the
+# size of the prime, from every 4 baby steps (49 bits) to none within these products (42)
+@pytest.mark.parametrize("bits", [(42, 42, 44), (46, 47, 48), (48, 49, 49), (49, 49, 49)])
+@pytest.mark.parametrize("groups", [8, 16])
+def test_encrypted_matmul_folds_by_prime_size(C, bits, groups):
+    evaluate_groups(C, synth.ForestShape(3, 3, 0.9, 3, 4, 3), 76, 11, bits, 3, True, groups, n1=(16, 13))
