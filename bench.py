@@ -559,11 +559,14 @@ def micro_bench(args):
 
 
 # exact modular product-accumulate on the fp64 pipe: h = a b, l = fma(a, b, -h), k = rint(h / q) (a product and a
-# rounding), r = fma(-k, q, h) + l, acc += r: 7 fp64 instructions; MI355X issues 256 CUs x 4 SIMDs x 16 fp64
+# rounding), r = fma(-k, q, h) + l, acc += r: 7 fp64 instructions, or 4 where the sums hold unreduced products (batches
+# of eight groups: two fused multiply-adds, a subtraction and an addition); MI355X issues 256 CUs x 4 SIMDs x 16 fp64
 # lanes per clock at 2.4 GHz = 3.93e13 lane-instructions/s (78.6 TFLOP/s counting an fma as two flops)
 FP64_LANE_INSTR_PER_S = 256 * 4 * 16 * 2.4e9
-MODMUL_INSTR = 7
-MODMUL_PEAK_T = FP64_LANE_INSTR_PER_S / MODMUL_INSTR / 1e12
+
+
+def modmul_peak_t(groups_per_call: int) -> float:
+    return FP64_LANE_INSTR_PER_S / (4 if groups_per_call % 8 == 0 else 7) / 1e12
 
 
 def _matmul_modmuls(meta, encrypted, G, levels):
@@ -814,8 +817,9 @@ def main():
         mods = _matmul_modmuls(meta, True, n_groups, [(meta.q, nl_r), (meta.d * meta.b, nl_r - 1)])
         mods_per_launch = mods * steps / max(1, p["launches"])
         alu_t = mods_per_launch / (avg_ms / 1000.0) / 1e12
-        alu = {"bound": "alu", "achieved": round(alu_t, 3), "peak": round(MODMUL_PEAK_T, 3), "unit": "Tmodmul/s",
-               "frac": round(alu_t / MODMUL_PEAK_T, 4), "traffic": hbm["traffic"],
+        peak_t = modmul_peak_t(batch)
+        alu = {"bound": "alu", "achieved": round(alu_t, 3), "peak": round(peak_t, 3), "unit": "Tmodmul/s",
+               "frac": round(alu_t / peak_t, 4), "traffic": hbm["traffic"],
                "modmuls_per_launch": round(mods_per_launch)}
         roofline = dict(alu) if alu["frac"] >= hbm["frac"] else dict(hbm)
         roofline["hbm"] = hbm

@@ -1844,7 +1844,7 @@ void launch_ks_inner_rows(Context& c, const std::vector<KsJob2>& jobs, int D, in
       for (int k2 = 0; k2 < k; ++k2) seen |= pk.j[k2].kb == pk.j[k].kb;
       keys += !seen;
     }
-    prof_end(c, 15, ev, ks_pack_bytes(c, pk, cnt, D, nE, level + 1, keys));
+    prof_end(c, 15, ev, ks_pack_bytes(c, pk, cnt, D, nE - first_row, std::max(0, level + 1 - first_row), keys));
   }
 }
 
