@@ -501,7 +501,9 @@ int copse_decrypt_labels(copse_ctx* ctx, const copse_keys* keys, const copse_pub
     if (ct.level != 0 || ct.npolys != 2) fail(COPSE_EINVAL, "result must be at level 0");
     if ((1ULL << meta->log_n) != c.N || meta->block_w == 0 || meta->block_w > c.N / 2 || meta->m > meta->block_w)
       fail(COPSE_EINVAL, "layout made for another ring size");
-    if (n_queries > meta->queries_per_ct) fail(COPSE_EINVAL, "more queries than blocks");
+    // the layout's own count and what the ring holds: the labels' kernel reads slots by query
+    if (n_queries > meta->queries_per_ct || n_queries > c.N / 2 / meta->block_w * 2)
+      fail(COPSE_EINVAL, "more queries than blocks");
     if (cap < n_queries * meta->m) fail(COPSE_EINVAL, "bits buffer too small");
     std::vector<uint8_t> slot_bits;
     const uint64_t worst = decrypt_label_slots(c, *keys->k, *meta, ct, n_queries, slot_bits);

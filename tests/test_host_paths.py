@@ -1,0 +1,69 @@
+"""Host side of the data owner's calls, without a device (hip_host.c: kernels do nothing, memory is the host's): what
+is refused before a kernel is launched, what a call does when an allocation fails, and what it holds meanwhile.  Each
+case runs in a process of its own, in which the stand-in is loaded before the library."""
+import os
+import subprocess
+import sys
+import textwrap
+
+import pytest
+
+HERE = os.path.dirname(os.path.abspath(__file__))
+ROOT = os.path.dirname(HERE)
+
+PRELUDE = """
+import ctypes, sys
+import numpy as np
+sys.path.insert(0, {root!r})
+hip = ctypes.CDLL({stub!r}, mode=ctypes.RTLD_GLOBAL)
+for f in (hip.host_live, hip.host_peak):
+    f.restype = ctypes.c_size_t
+hip.host_set_limit.argtypes = [ctypes.c_size_t]
+from paper_2104_09583_amd import copse as C
+from paper_2104_09583_amd import synth
+LOG_N, PRECISION = 13, 8
+ctx = C.Context(LOG_N, 8, 1 << 48, 1 << 42, 3, 1 << 48)
+shape = synth.ForestShape(2, 2, 1.0, 3, PRECISION, 2)
+comp, meta = C.forest_compile(synth.gen_forest_text(shape, 5), 3, PRECISION, LOG_N)
+SEED = b"\\x21" * 32
+keys = ctx.keygen(SEED, [1])
+U64 = ctypes.POINTER(ctypes.c_uint64)
+
+def code(f, *a):
+    try:
+        f(*a)
+        return C.COPSE_OK
+    except C.CopseError as e:
+        return e.code
+"""
+
+
+@pytest.fixture(scope="module")
+def stub(tmp_path_factory):
+    out = str(tmp_path_factory.mktemp("hip") / "libhiphost.so")
+    subprocess.run(["gcc", "-O1", "-shared", "-fPIC", "-o", out, os.path.join(HERE, "hip_host.c")], check=True)
+    return out
+
+
+def run(stub, body):
+    src = PRELUDE.format(root=ROOT, stub=stub) + textwrap.dedent(body)
+    r = subprocess.run([sys.executable, "-c", src], capture_output=True, text=True, timeout=120)
+    assert r.returncode == 0, r.stdout + r.stderr
+
+
+@pytest.mark.parametrize("block_w,n", [("ctx.N // 2", 3), ("meta.block_w", "ctx.N // meta.block_w + 1")])
+def test_label_decryption_refuses_more_queries_than_the_ring_has_blocks(stub, block_w, n):
+    """A layout that states more blocks than it has: refused before anything is launched (the kernel that reads the
+    labels indexes by it)."""
+    run(stub, f"""
+        res = ctx.import_([np.zeros((1, ctx.N), dtype=np.uint64)] * 2, 0)
+        meta.block_w, n = {block_w}, {n}
+        meta.queries_per_ct = 1 << 20
+        before = hip.host_launches()
+        assert before > 0
+        assert code(ctx.decrypt_labels, keys, meta, res, n) == C.COPSE_EINVAL
+        assert hip.host_launches() == before
+        # as many as there are blocks: decrypted (all zero, as nothing ran)
+        assert code(ctx.decrypt_labels, keys, meta, res, ctx.N // meta.block_w) == C.COPSE_ENOISE
+        assert hip.host_launches() > before
+    """)
