@@ -441,6 +441,7 @@ std::unique_ptr<Keys> keygen(Context& c, const uint8_t seed[32], const std::vect
   K->pk_b = DBuf(&c, (size_t)nd * N);
   {
     std::vector<double> ha((size_t)nd * N);
+    StreamWait wait{c.stream};
     sample_uniform_limbs(seed, "pk.a", 0, 0, {c.primes.begin(), c.primes.begin() + nd}, N, ha.data());
     COPSE_HIP(hipMemcpyAsync(K->pk_a.get(), ha.data(), ha.size() * 8, hipMemcpyHostToDevice, c.stream));
     launch_ntt_fwd(c, K->pk_a.get(), drows, nd);
@@ -452,7 +453,7 @@ std::unique_ptr<Keys> keygen(Context& c, const uint8_t seed[32], const std::vect
     DBuf as(&c, (size_t)nd * N);
     launch_mul(c, as.get(), K->pk_a.get(), K->s.get(), drows, nd);
     launch_sub(c, K->pk_b.get(), te.get(), as.get(), drows, nd);
-    COPSE_HIP(hipStreamSynchronize(c.stream));
+    wait.finish();
   }
   const int D = c.n_digits(c.L);
   const int2* arows = all_rows(c, 1);
@@ -465,6 +466,8 @@ std::unique_ptr<Keys> keygen(Context& c, const uint8_t seed[32], const std::vect
     DBuf te(&c, (size_t)Lt * N), as(&c, (size_t)Lt * N);
     for (int j = 0; j < D; ++j) {
       uint64_t obj = key_id * 256 + (uint64_t)j;
+      std::vector<double> pmod(Lt, 0.0);
+      StreamWait wait{c.stream};
       sample_uniform_limbs(seed, "ksk.a", obj, 0, c.primes, N, ha.data());
       double* aj = k->a.get() + (size_t)j * Lt * N;
       double* bj = k->b.get() + (size_t)j * Lt * N;
@@ -477,7 +480,6 @@ std::unique_ptr<Keys> keygen(Context& c, const uint8_t seed[32], const std::vect
       launch_sub(c, bj, te.get(), as.get(), arows, Lt);
       // gadget: + (P mod q_i) s' on the limbs of digit j
       int first = j * c.alpha, cnt = std::min(c.alpha, c.L + 1 - first);
-      std::vector<double> pmod(Lt, 0.0);
       for (int i = first; i < first + cnt; ++i) {
         uint64_t P = 1;
         for (int r = 0; r < c.alpha; ++r) P = mulmod(P, c.primes[c.L + 1 + r] % c.primes[i], c.primes[i]);
@@ -491,7 +493,7 @@ std::unique_ptr<Keys> keygen(Context& c, const uint8_t seed[32], const std::vect
       DBuf gs(&c, (size_t)Lt * N);
       launch_mul_scalar(c, gs.get(), snew.get(), dp.get(), grow, cnt);
       launch_add(c, bj, bj, gs.get(), grow, cnt);
-      COPSE_HIP(hipStreamSynchronize(c.stream));
+      wait.finish();
     }
     K->bytes += 2 * (size_t)D * Lt * N * 8;
     return k;

@@ -45,12 +45,6 @@ static const Ct& ct_of(const Context& c, const copse_cts* x, size_t i) {
 }
 
 namespace {
-// waits for the stream when a call that copies from or to the caller's memory ends early
-struct StreamWait {
-  hipStream_t s;
-  ~StreamWait() { (void)hipStreamSynchronize(s); }
-};
-
 std::vector<uint64_t> primes_below(uint64_t bound, uint64_t modulus, int count, const std::vector<uint64_t>& taken) {
   std::vector<uint64_t> out;
   if (bound < 2) fail(COPSE_EINVAL, "prime bound too small");
@@ -633,7 +627,7 @@ int copse_cts_import(copse_ctx* ctx, const uint64_t* buf, size_t len, copse_cts*
     }
     uint64_t flag = 0;
     COPSE_HIP(hipMemcpyAsync(&flag, bad.get(), 8, hipMemcpyDeviceToHost, c.stream));
-    COPSE_HIP(hipStreamSynchronize(c.stream));
+    wait.finish();
     if (flag) fail(COPSE_EINVAL, "residue out of range in import");
     *out = r.release();
   });

@@ -40,6 +40,20 @@ struct Error {
       ::copse::fail(COPSE_EDEVICE, std::string(#x) + ": " + hipGetErrorString(e_));   \
   } while (0)
 
+// Waits for the stream when a scope that copies from or to host memory is left early, by an allocation that fails: the
+// copies may still read or write that memory.  Declared after what they read; finish() is the wait of the ordinary end.
+struct StreamWait {
+  hipStream_t s;
+  bool armed = true;
+  void finish() {
+    armed = false;
+    COPSE_HIP(hipStreamSynchronize(s));
+  }
+  ~StreamWait() {
+    if (armed) (void)hipStreamSynchronize(s);
+  }
+};
+
 // ------------------------------------------------------------------ host number theory
 uint64_t mulmod(uint64_t a, uint64_t b, uint64_t m);
 uint64_t powmod(uint64_t a, uint64_t e, uint64_t m);

@@ -269,7 +269,8 @@ static const int2* t_rows(Context& c, int count) {
   return c.rows(key, h);
 }
 
-// Coefficients in [0, t) of `count` slot vectors ([count][N] in caller memory), enqueued
+// Coefficients in [0, t) of `count` slot vectors ([count][N] in caller memory), enqueued: the caller of this keeps them
+// until the stream has been waited for
 static DBuf encode_device(Context& c, const uint64_t* slots, int count) {
   DBuf up(&c, (size_t)count * c.N), m(&c, (size_t)count * c.N);
   COPSE_HIP(hipMemcpyAsync(up.get(), slots, (size_t)count * c.N * 8, hipMemcpyHostToDevice, c.stream));
@@ -284,12 +285,13 @@ std::unique_ptr<Plain> make_plain_slots(Context& c, const uint64_t* slots, int l
   auto p = std::make_unique<Plain>();
   p->level = level;
   p->buf = DBuf(&c, (size_t)(level + 1) * c.N);
+  StreamWait wait{c.stream};   // slots is the caller's memory
   DBuf m = encode_device(c, slots, 1);
   hipLaunchKernelGGL(lift_plain_kernel, wire_grid(c, level + 1), dim3(kWireThreads), 0, c.stream, p->buf.get(), m.get(),
                      (double)c.t, c.d_primes, (int)c.log_n);
   COPSE_HIP(hipGetLastError());
   launch_ntt_fwd(c, p->buf.get(), limb_rows(c, 1, level + 1), level + 1);
-  COPSE_HIP(hipStreamSynchronize(c.stream));   // slots is the caller's memory
+  wait.finish();
   return p;
 }
 
@@ -339,6 +341,7 @@ static void encrypt_many(Context& c, const Keys& k, const DBuf& m, int n, int le
   const int nl = level + 1;
   std::vector<uint8_t> noise(n * stride);
   sample_encryption_many(seed, objs, n, N, noise.data());
+  StreamWait wait{c.stream};
   DBuf dn(&c, (noise.size() + 7) / 8);
   COPSE_HIP(hipMemcpyAsync(dn.get(), noise.data(), noise.size(), hipMemcpyHostToDevice, c.stream));
   DBuf rows(&c, (size_t)3 * n * nl * N);
@@ -355,7 +358,7 @@ static void encrypt_many(Context& c, const Keys& k, const DBuf& m, int n, int le
   hipLaunchKernelGGL(enc_combine_kernel, wire_grid(c, nl, n), dim3(kWireThreads), 0, c.stream, po, rows.get(),
                      k.pk_b.get(), k.pk_a.get(), c.d_primes, (int)c.log_n);
   COPSE_HIP(hipGetLastError());
-  COPSE_HIP(hipStreamSynchronize(c.stream));   // the noise is host memory
+  wait.finish();
 }
 
 // Plaintexts travel eight at a time: the limb rows in flight stay below 80 MB (N = 32768, twelve limbs), and eight
@@ -365,10 +368,12 @@ constexpr int kEncryptMany = 8;
 std::vector<CtPtr> encrypt_slots_many(Context& c, const Keys& k, const uint64_t* slots, int count, int level,
                                       const uint8_t seed[32], const uint64_t* objs) {
   std::vector<CtPtr> out;
+  StreamWait wait{c.stream};   // slots is the caller's memory
   for (int first = 0; first < count; first += kEncryptMany) {
     const int n = std::min(kEncryptMany, count - first);
     encrypt_many(c, k, encode_device(c, slots + (size_t)first * c.N, n), n, level, seed, objs + first, out);
   }
+  wait.finish();
   return out;
 }
 
@@ -401,6 +406,7 @@ std::vector<CtPtr> encrypt_query(Context& c, const Keys& k, const copse_public_m
   if (M.precision == 0) return out;
   const size_t words = n_queries * M.n_features;
   DBuf feats(&c, (words + 1) / 2);
+  StreamWait wait{c.stream};   // features is the caller's memory
   COPSE_HIP(hipMemcpyAsync(feats.get(), features, words * sizeof(uint32_t), hipMemcpyHostToDevice, c.stream));
   const uint32_t B = M.m + M.b + M.q - 2 + (M.server_rep ? M.n_features - 1 : 0);
   for (uint32_t first = 0; first < M.precision; first += kEncryptMany) {
@@ -415,6 +421,7 @@ std::vector<CtPtr> encrypt_query(Context& c, const Keys& k, const copse_public_m
     for (int p = 0; p < n; ++p) objs[p] = (1ULL << 56) | ((uint64_t)group << 32) | (first + (uint32_t)p);
     encrypt_many(c, k, m, n, c.L, seed, objs, out);
   }
+  wait.finish();
   return out;
 }
 

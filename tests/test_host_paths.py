@@ -67,3 +67,35 @@ def test_label_decryption_refuses_more_queries_than_the_ring_has_blocks(stub, bl
         assert code(ctx.decrypt_labels, keys, meta, res, ctx.N // meta.block_w) == C.COPSE_ENOISE
         assert hip.host_launches() > before
     """)
+
+
+@pytest.mark.parametrize("call", [
+    "ctx.query_encrypt(keys, meta, np.full((3, 3), 7), SEED)",
+    "ctx.encrypt_slots(keys, np.arange(ctx.N) % 7, ctx.L, SEED, 1)",
+    "ctx.op(None, C.OP_MUL_PLAIN, one, slots=np.arange(ctx.N) % 7)",
+    "ctx.model_encode(comp)",
+    "ctx.model_encode(comp, keys, True, SEED)",
+    "ctx.keygen(SEED, [1])",
+    "ctx.export(one)",
+    "ctx.import_(words, ctx.L)",
+])
+def test_no_copy_is_in_flight_when_an_allocation_fails(stub, call):
+    """The call with ever more device memory: each time that an allocation fails, no copy from or to the caller's
+    memory or a temporary of the call may still be outstanding when it returns."""
+    run(stub, f"""
+        words = [np.zeros((ctx.L + 1, ctx.N), dtype=np.uint64)] * 3
+        one = ctx.import_(words[:2], ctx.L)
+        failed = 0
+        for grow in range(0, 1 << 30, 96 << 10):
+            # a context of its own (of the keys' chain): what another call left in the pool would serve this one
+            hip.host_set_limit(ctypes.c_size_t(-1).value)
+            ctx = C.Context(LOG_N, 8, 1 << 48, 1 << 42, 3, 1 << 48)
+            hip.host_set_limit(hip.host_live() + grow)
+            c = code(lambda: {call})
+            if c == C.COPSE_OK:
+                break
+            assert c in (C.COPSE_ENOMEM, C.COPSE_EDEVICE), c
+            assert hip.host_pending() == 0, grow
+            failed += 1
+        assert c == C.COPSE_OK and failed > 3, failed
+    """)
