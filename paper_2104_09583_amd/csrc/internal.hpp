@@ -219,8 +219,9 @@ struct Context {
   std::map<std::string, int2*> call_rows;
   std::vector<std::vector<int2>> call_rows_host;
   std::vector<DBuf> call_row_bufs;
-  // pinned staging of copse_cts_export, allocated by the first export and kept: two slots of at most
-  // kExportSlotMax bytes
+  // pinned host memory between the caller's and the device for copse_cts_export and for small ciphertexts in
+  // copse_cts_import: two slots of at most kExportSlotMax bytes (wire.hip), allocated by the first call that uses them,
+  // kept with the context; none where the system has none left
   char* export_slot[2] = {nullptr, nullptr};
   size_t export_slot_bytes = 0;
   hipEvent_t export_done[2] = {nullptr, nullptr};

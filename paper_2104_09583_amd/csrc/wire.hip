@@ -38,9 +38,10 @@ __global__ void residues_to_words_kernel(uint64_t* out, const double* in, int lo
 // The column pass with the conversion folded in, for the rings of the split transform (N = 2^13 .. 2^16): one
 // thread keeps one column (2^S1 elements, C = N >> S1 apart) in registers.
 //   forward (import): words from `words`, checked against the prime, then stages 0 .. S1 - 1; signed output for the row
-//   pass to `io` (which may be the same memory)
+//   pass to `io`
 //   inverse (export): the row pass's signed output in `io` (< 32 q), the last stages, N^-1, canonical words to `words`
-// Where words is pinned host memory, the loads and stores cross the bus and no copy stands before or after.
+// words and io may be the same memory: a thread has read its column before it writes it.  Where words is pinned host
+// memory, the loads and stores cross the bus and no copy stands before or after.
 // Bound by the copy from or to the caller's memory.  A request of eight planes (42 MB) in, one evaluation, its result
 // out: 5.50 ms with the conversion loops on the host, 3.14 ms here, of which the copy in takes 1.2 and the evaluation
 // 1.4.
@@ -122,10 +123,9 @@ static const int2* limb_rows(Context& c, int np, int nl) {
   return c.rows(key, h);
 }
 
-// A ciphertext's coefficient words to `out` (device-visible), enqueued
-static void ct_words(Context& c, const Ct& a, uint64_t* out) {
+// A ciphertext's coefficient words to `out` (device-visible; tmp's own memory too), enqueued
+static void ct_words(Context& c, const Ct& a, DBuf& tmp, uint64_t* out) {
   const int nl = a.level + 1, rows = a.npolys * nl;
-  DBuf tmp(&c, a.words());
   if (bridge_supported(c, 1)) {
     std::vector<const double*> polys;
     for (int k = 0; k < a.npolys; ++k) polys.push_back(a.poly(k, c.N));
@@ -144,22 +144,28 @@ static void ct_words(Context& c, const Ct& a, uint64_t* out) {
 // other out to the caller's buffer (the runtime's copy to pageable memory is a staging kernel and a wait of its own).
 // Against copying from device memory: 16 results exported after a batched evaluation 16.68 -> 16.39 ms together, a fresh
 // group of eight planes (42 MB, to fresh pages) encrypted and exported 5.41 -> 4.28 ms.  A ciphertext beyond a slot
-// goes through device memory.
+// goes through device memory, in the one buffer that it needs in any case.
 constexpr size_t kExportSlotMax = (size_t)8 << 20;
 
-// slots of at least min(need, kExportSlotMax) bytes
+// slots of at least min(need, kExportSlotMax) bytes where the system has that much pinned memory left; where it has not,
+// they stay as they are, and what does not fit them goes through device memory too
 static void wire_slots(Context& c, size_t need) {
   need = std::min(need, kExportSlotMax);
   for (int k = 0; k < 2; ++k)
     if (!c.export_done[k]) COPSE_HIP(hipEventCreateWithFlags(&c.export_done[k], hipEventDisableTiming));
   if (need <= c.export_slot_bytes) return;
   COPSE_HIP(hipStreamSynchronize(c.stream));   // an import may still be read
-  for (char*& p : c.export_slot) {
-    if (p) COPSE_HIP(hipHostFree(p));
-    p = nullptr;
+  void* grown[2] = {nullptr, nullptr};
+  for (int k = 0; k < 2; ++k)
+    if (hipHostMalloc(&grown[k], need, hipHostMallocDefault) != hipSuccess) {
+      (void)hipGetLastError();
+      if (k == 1) (void)hipHostFree(grown[0]);
+      return;
+    }
+  for (int k = 0; k < 2; ++k) {
+    if (c.export_slot[k]) (void)hipHostFree(c.export_slot[k]);
+    c.export_slot[k] = static_cast<char*>(grown[k]);
   }
-  c.export_slot_bytes = 0;
-  for (char*& p : c.export_slot) COPSE_HIP(hipHostMalloc(reinterpret_cast<void**>(&p), need, hipHostMallocDefault));
   c.export_slot_bytes = need;
 }
 
@@ -184,14 +190,14 @@ void export_cts(Context& c, const std::vector<const Ct*>& cts, uint64_t* buf) {
     *buf++ = (uint64_t)c.N;
     *buf++ = 0;
     const size_t bytes = a->words() * 8;
-    if (bytes > kExportSlotMax) {
-      DBuf tmp(&c, a->words());
-      ct_words(c, *a, reinterpret_cast<uint64_t*>(tmp.get()));
+    DBuf tmp(&c, a->words());
+    if (bytes > c.export_slot_bytes) {
+      ct_words(c, *a, tmp, reinterpret_cast<uint64_t*>(tmp.get()));
       COPSE_HIP(hipMemcpyAsync(buf, tmp.get(), bytes, hipMemcpyDeviceToHost, c.stream));
       COPSE_HIP(hipStreamSynchronize(c.stream));
     } else {
       finish(slot);
-      ct_words(c, *a, reinterpret_cast<uint64_t*>(c.export_slot[slot]));
+      ct_words(c, *a, tmp, reinterpret_cast<uint64_t*>(c.export_slot[slot]));
       COPSE_HIP(hipEventRecord(c.export_done[slot], c.stream));
       pending[slot].to = buf;
       pending[slot].bytes = bytes;
@@ -214,8 +220,9 @@ CtPtr ct_from_words(Context& c, const uint64_t* words, int level, int npolys, in
   auto ct = ct_alloc(c, level, npolys);
   const int nl = level + 1, rows = npolys * nl;
   const size_t bytes = ct->words() * 8;
-  if (bridge_supported(c, 1) && bytes <= kImportSlotMax) {
-    wire_slots(c, bytes);
+  const bool through_slot = bridge_supported(c, 1) && bytes <= kImportSlotMax;
+  if (through_slot) wire_slots(c, bytes);
+  if (through_slot && bytes <= c.export_slot_bytes) {
     const int slot = c.import_slot;
     c.import_slot ^= 1;
     COPSE_HIP(hipEventSynchronize(c.export_done[slot]));   // what last read or wrote the slot

@@ -99,3 +99,22 @@ def test_no_copy_is_in_flight_when_an_allocation_fails(stub, call):
             failed += 1
         assert c == C.COPSE_OK and failed > 3, failed
     """)
+
+
+def test_wire_without_pinned_memory(stub):
+    """Import and export where the system has no pinned memory left (or none for larger slots than there are), with as
+    much device memory as one ciphertext."""
+    run(stub, """
+        small, large = [np.zeros((1, ctx.N), dtype=np.uint64)] * 2, [np.zeros((ctx.L + 1, ctx.N), dtype=np.uint64)] * 2
+        hip.host_set_no_pinned(1)
+        for first in (True, False):
+            a = ctx.import_(small, 0)
+            b = ctx.import_(large, ctx.L)
+            hip.host_set_limit(hip.host_live() + 2 * (ctx.L + 1) * ctx.N * 8 * 9 // 8 + (64 << 10))
+            assert len(ctx.export(a)) == len(ctx.export(b)) == 1
+            hip.host_set_limit(ctypes.c_size_t(-1).value)
+            if first:   # slots for the small one, none for the large one
+                hip.host_set_no_pinned(0)
+                ctx.export(a)
+                hip.host_set_no_pinned(1)
+    """)
