@@ -265,7 +265,11 @@ size_t copse_model_bytes(const copse_model* m);
  * and encrypts each plane at the top level: (pk0 u + t e0 + m,
  * pk1 u + t e1), u ternary "enc.u", e0 "enc.e0", e1 "enc.e1", object
  * (1 << 56) | (group << 32) | plane.  features: [n_queries][n_features]
- * values < 2^p; n_queries <= queries_per_ct.  Result: p ciphertexts.
+ * values < 2^p; n_queries <= queries_per_ct.  Result: p ciphertexts.  While it
+ * runs it holds, besides the result, about three rows of N words a limb for
+ * each of up to eight planes (fewer where device memory is short).  Errors:
+ * EINVAL (layout of another ring, too many queries, a value out of range, keys
+ * of another context), ENOMEM (one plane at a time does not fit either).
  */
 int copse_query_encrypt(copse_ctx* ctx, const copse_keys* keys, const copse_public_meta* meta,
                         const uint32_t* features, size_t n_queries, const uint8_t seed[32],

@@ -346,40 +346,55 @@ static void encrypt_many(Context& c, const Keys& k, const DBuf& m, int n, int le
                          const uint64_t* objs, std::vector<CtPtr>& out) {
   const size_t N = c.N, stride = encryption_noise_bytes(N);
   const int nl = level + 1;
+  DBuf rows(&c, (size_t)3 * n * nl * N), dn(&c, (n * stride + 7) / 8);
+  std::vector<CtPtr> cts;
+  MPack po;
+  for (int p = 0; p < n; ++p) {
+    cts.push_back(ct_alloc(c, level, 2));
+    po.p[p] = cts.back()->data();
+  }
   std::vector<uint8_t> noise(n * stride);
   sample_encryption_many(seed, objs, n, N, noise.data());
   StreamWait wait{c.stream};
-  DBuf dn(&c, (noise.size() + 7) / 8);
   COPSE_HIP(hipMemcpyAsync(dn.get(), noise.data(), noise.size(), hipMemcpyHostToDevice, c.stream));
-  DBuf rows(&c, (size_t)3 * n * nl * N);
   hipLaunchKernelGGL(enc_lift_kernel, wire_grid(c, nl, 3 * n), dim3(kWireThreads), 0, c.stream, rows.get(),
                      reinterpret_cast<const uint8_t*>(dn.get()), stride, m.get(), (double)c.t, c.d_primes,
                      (int)c.log_n);
   COPSE_HIP(hipGetLastError());
   launch_ntt_fwd(c, rows.get(), limb_rows(c, 3 * n, nl), 3 * n * nl);
-  MPack po;
-  for (int p = 0; p < n; ++p) {
-    out.push_back(ct_alloc(c, level, 2));
-    po.p[p] = out.back()->data();
-  }
   hipLaunchKernelGGL(enc_combine_kernel, wire_grid(c, nl, n), dim3(kWireThreads), 0, c.stream, po, rows.get(),
                      k.pk_b.get(), k.pk_a.get(), c.d_primes, (int)c.log_n);
   COPSE_HIP(hipGetLastError());
   wait.finish();
+  for (auto& ct : cts) out.push_back(std::move(ct));
 }
 
 // Plaintexts travel eight at a time: the limb rows in flight stay below 80 MB (N = 32768, twelve limbs), and eight
-// streams of randomness fill the host's vectors.
+// streams of randomness fill the host's vectors.  Where the device does not have that much left, fewer, down to one,
+// whose three rows a limb any encryption needs.
 constexpr int kEncryptMany = 8;
+template <class Encrypt>
+static void encrypt_batches(int count, Encrypt encrypt) {
+  int many = kEncryptMany;
+  for (int first = 0; first < count;) {
+    const int n = std::min(many, count - first);
+    try {
+      encrypt(first, n);
+      first += n;
+    } catch (const Error& e) {
+      if (e.code != COPSE_ENOMEM || n == 1) throw;
+      many = (n + 1) / 2;
+    }
+  }
+}
 
 std::vector<CtPtr> encrypt_slots_many(Context& c, const Keys& k, const uint64_t* slots, int count, int level,
                                       const uint8_t seed[32], const uint64_t* objs) {
   std::vector<CtPtr> out;
   StreamWait wait{c.stream};   // slots is the caller's memory
-  for (int first = 0; first < count; first += kEncryptMany) {
-    const int n = std::min(kEncryptMany, count - first);
+  encrypt_batches(count, [&](int first, int n) {
     encrypt_many(c, k, encode_device(c, slots + (size_t)first * c.N, n), n, level, seed, objs + first, out);
-  }
+  });
   wait.finish();
   return out;
 }
@@ -416,18 +431,17 @@ std::vector<CtPtr> encrypt_query(Context& c, const Keys& k, const copse_public_m
   StreamWait wait{c.stream};   // features is the caller's memory
   COPSE_HIP(hipMemcpyAsync(feats.get(), features, words * sizeof(uint32_t), hipMemcpyHostToDevice, c.stream));
   const uint32_t B = M.m + M.b + M.q - 2 + (M.server_rep ? M.n_features - 1 : 0);
-  for (uint32_t first = 0; first < M.precision; first += kEncryptMany) {
-    const int n = (int)std::min<uint32_t>(kEncryptMany, M.precision - first);
+  encrypt_batches((int)M.precision, [&](int first, int n) {
     DBuf m(&c, n * c.N);
     hipLaunchKernelGGL(query_eval_kernel, wire_grid(c, n), dim3(kWireThreads), 0, c.stream, m.get(),
                        reinterpret_cast<const uint32_t*>(feats.get()), c.d_slot_of_eval, (uint32_t)n_queries,
-                       M.n_features, B, M.q, M.K, M.block_w, first, M.server_rep ? 1 : 0, (int)c.log_n);
+                       M.n_features, B, M.q, M.K, M.block_w, (uint32_t)first, M.server_rep ? 1 : 0, (int)c.log_n);
     COPSE_HIP(hipGetLastError());
     launch_ntt_inv(c, m.get(), t_rows(c, n), n);
     uint64_t objs[kEncryptMany];
     for (int p = 0; p < n; ++p) objs[p] = (1ULL << 56) | ((uint64_t)group << 32) | (first + (uint32_t)p);
     encrypt_many(c, k, m, n, c.L, seed, objs, out);
-  }
+  });
   wait.finish();
   return out;
 }

@@ -118,3 +118,17 @@ def test_wire_without_pinned_memory(stub):
                 ctx.export(a)
                 hip.host_set_no_pinned(1)
     """)
+
+
+@pytest.mark.parametrize("precision", [1, 3, 8, 9])
+def test_query_encryption_in_little_memory(stub, precision):
+    """With device memory for the result, the rows of one encryption and a few more of one limb: every plane."""
+    run(stub, f"""
+        text = synth.gen_forest_text(synth.ForestShape(2, 2, 1.0, 3, {precision}, 2), 5)
+        meta = C.forest_compile(text, 3, {precision}, LOG_N)[1]
+        ctx = C.Context(LOG_N, 8, 1 << 48, 1 << 42, 3, 1 << 48)   # nothing in its pool
+        row, limbs = ctx.N * 8, ctx.L + 1
+        hip.host_set_limit(hip.host_live() + ({precision} * 2 * limbs + 3 * limbs + 6) * row * 9 // 8)
+        q = ctx.query_encrypt(keys, meta, np.zeros((3, 3)), SEED)
+        assert len(q) == {precision}
+    """)
