@@ -599,6 +599,7 @@ int copse_cts_export(copse_ctx* ctx, const copse_cts* cts, uint64_t* buf, size_t
       if (ct->n != c.N || ct->level > c.L) fail(COPSE_EINVAL, "ciphertext of another ring or chain");
     std::vector<const Ct*> list;
     for (auto& ct : cts->v) list.push_back(ct.get());
+    std::lock_guard<std::mutex> slots(c.wire_mu);
     StreamWait wait{c.stream};
     export_cts(c, list, buf);
   });
@@ -613,6 +614,7 @@ int copse_cts_import(copse_ctx* ctx, const uint64_t* buf, size_t len, copse_cts*
     // words copied straight from the caller's buffer, converted and checked on the device
     DBuf bad(&c, 1);
     COPSE_HIP(hipMemsetAsync(bad.get(), 0, 8, c.stream));
+    std::lock_guard<std::mutex> slots(c.wire_mu);
     StreamWait wait{c.stream};
     size_t off = 0;
     while (off < len) {

@@ -226,6 +226,7 @@ struct Context {
   size_t export_slot_bytes = 0;
   hipEvent_t export_done[2] = {nullptr, nullptr};
   int import_slot = 0;
+  std::mutex wire_mu;   // held by a call that uses them, until the device has finished with them
   Tuning tune;                    // active for the evaluation being issued
   std::vector<TuneEntry> tune_table;
   // the table's entry for an evaluation of `batch` query groups of a plaintext or encrypted model (defaults

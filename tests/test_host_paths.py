@@ -132,3 +132,30 @@ def test_query_encryption_in_little_memory(stub, precision):
         q = ctx.query_encrypt(keys, meta, np.zeros((3, 3)), SEED)
         assert len(q) == {precision}
     """)
+
+
+def test_pinned_slots_serve_one_call_at_a_time(stub):
+    """Imports and exports by several threads, as a server's clients issue them: a call has the pinned slots to itself
+    until its words are copied out.  The stand-in's wait for a slot yields to the other threads and counts them."""
+    run(stub, """
+        import threading, time
+        block = [np.zeros((1, ctx.N), dtype=np.uint64)] * 2
+        one = ctx.import_(block, 0)
+        ctx.export(one)
+        inside, worst, mu = 0, 0, threading.Lock()
+        @ctypes.CFUNCTYPE(None)
+        def wait():
+            global inside, worst
+            with mu:
+                inside += 1
+                worst = max(worst, inside)
+            time.sleep(0.01)
+            with mu:
+                inside -= 1
+        hip.host_set_event_wait(wait)
+        ts = [threading.Thread(target=lambda: [ctx.export(one) for _ in range(3)]) for _ in range(3)]
+        ts += [threading.Thread(target=lambda: [ctx.import_(block, 0) for _ in range(3)]) for _ in range(3)]
+        for t in ts: t.start()
+        for t in ts: t.join()
+        assert worst == 1, worst
+    """)
