@@ -360,8 +360,7 @@ static void ks_batch(Context& c, int level, const std::vector<const double*>& in
   const int R = (int)reqs.size();
   const int Lt = c.n_primes();
   KSTables& T = c.kstab(level);
-  // rotations with more than eight digits take the separate passes
-  const bool fused = bridge_supported(c, c.alpha) && !(add_mode == 2 && D > 8);
+  const bool fused = bridge_supported(c, c.alpha);
   if (merge && !(fused && add_mode == 1 && level >= 1 && T.mm_ok))
     fail(COPSE_EINVAL, "internal: merged switch not available here");
   if (inputs_b && (!merge || inputs_b->size() != inputs.size()))

@@ -456,7 +456,7 @@ void launch_ks_inner2(Context& c, const std::vector<KsJob2>& jobs, int D, int nE
 // first_row on are formed
 void launch_ks_inner_rows(Context& c, const std::vector<KsJob2>& jobs, int D, int nE, int level, size_t key_ds,
                           double ptop, int inv_from, int first_row = 0);
-// Hoisted rotations on the rings of the split transform (keyswitch.hip), jobs of one level and digit count D <= 8:
+// Hoisted rotations on the rings of the split transform (keyswitch.hip), jobs of one level and digit count D:
 // the special rows of the inner products with their inverse row pass, to acc [jobs][2][alpha][N], and, from the
 // converted rows w [jobs][2][nl][N], the ModDown's finish with the data rows' inner products inside.
 struct KsRot {

@@ -1593,10 +1593,9 @@ __device__ __forceinline__ void ks_tensor_top(double& t0, double& t1, double b0,
   t1 = mul_lazy(a0, b1, pr.q, pr.qinv) + mul_lazy(t1, b0, pr.q, pr.qinv);
 }
 
-// key-switch inner product over jobs, for the key switches of separate passes (rings outside the split transform,
-// rotations of more than eight digits); digit rows come straight from the job's input poly.  kD > 0: the digit
-// count, known at compile time, so every digit's loads are issued before the first product (kD = 0: any count, one
-// digit at a time).
+// key-switch inner product over jobs, for the key switches of separate passes (rings outside the split transform);
+// digit rows come straight from the job's input poly.  kD > 0: the digit count, known at compile time, so every digit's
+// loads are issued before the first product (kD = 0: any count, one digit at a time).
 template <int kD>
 __global__ void ks_inner2_kernel(KsPack jobs, int D_, int nE, int nl, int L, int alpha, int logN, size_t key_ds,
                                  const DevPrime* P) {

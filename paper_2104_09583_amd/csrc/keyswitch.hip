@@ -40,7 +40,9 @@ __device__ __forceinline__ KsPlace ks_place(int njobs) {
 }
 
 // a += sum over the digits of digit x key (key: the polynomial's half of it), on the positions t + 512 k of a tile of
-// extended row o (global prime `prime`)
+// extended row o (global prime `prime`).  Each product is within 0.69 q; from |a| < 2 q the sum is folded back after
+// every eight (below 7.5 q), so that any number of digits (48 at most, one prime each) ends below 6.1 q or, without a
+// fold, below 7.5 q.
 __device__ __forceinline__ void rot_digits(double (&a)[8], const KsRot& jb, const double* key, int D, int o, int own,
                                            int prime, int nE, const AutoTile& at, size_t t0, size_t N, size_t key_ds,
                                            const DevPrime& pr) {
@@ -55,6 +57,7 @@ __device__ __forceinline__ void rot_digits(double (&a)[8], const KsRot& jb, cons
     }
 #pragma unroll
     for (int k = 0; k < 8; ++k) a[k] += mul_lazy(e[k], kv[k], pr.q, pr.qinv);
+    if ((j & 7) == 7) red8(a, pr);   // uniform
   }
 }
 
@@ -103,7 +106,7 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(6))) void k
   for (int k = 0; k < 8; ++k) a[k] = -mul_lazy(a[k], t_mod, pr.q, pr.qinv);
   const AutoTile at = auto_tile(pl.t0, jb.g, logN);
   rot_digits(a, jb, pl.poly == 0 ? jb.kb : jb.ka, D, i, i / alpha, i, nE, at, pl.t0, N, key_ds, pr);
-  // at most eight digits: |a| < 10 q, the product below 2.5 q
+  // |a| < 7.5 q, the product below 2 q
   const double pi = pinv[i];
 #pragma unroll
   for (int k = 0; k < 8; ++k) a[k] = mul_lazy(a[k], pi, pr.q, pr.qinv);
@@ -133,14 +136,13 @@ static RotPack rot_pack(const std::vector<KsRot>& jobs, size_t first, int cnt) {
   for (int k = 0; k < cnt; ++k) pk.j[k] = jobs[first + k];
   return pk;
 }
-static void check_rot(const Context& c, int D) {
+static void check_split(const Context& c) {
   if (c.log_n < 13) fail(COPSE_EINVAL, "internal: split transform needs N >= 8192");
-  if (D < 1 || D > 8) fail(COPSE_EINVAL, "internal: too many digits for the fused rotation");
 }
 
 void launch_ks_rot_special(Context& c, const std::vector<KsRot>& jobs, double* acc, int D, int nE, int level,
                            size_t key_ds) {
-  check_rot(c, D);
+  check_split(c);
   const size_t per = rot_per_launch(c);
   for (size_t first = 0; first < jobs.size(); first += per) {
     const int cnt = (int)std::min<size_t>(per, jobs.size() - first);
@@ -157,7 +159,7 @@ void launch_ks_rot_special(Context& c, const std::vector<KsRot>& jobs, double* a
 
 void launch_ks_rot_finish(Context& c, const std::vector<KsRot>& jobs, const double* w, const double* pinv, int D,
                           int nE, int level, size_t key_ds) {
-  check_rot(c, D);
+  check_split(c);
   const int nl = level + 1;
   const size_t per = rot_per_launch(c);
   for (size_t first = 0; first < jobs.size(); first += per) {
@@ -289,7 +291,8 @@ __global__ __launch_bounds__(512, 4) void ks_relin_finish_kernel(RelinPack jobs,
 
 void launch_ks_relin_finish(Context& c, const std::vector<KsRelin>& jobs, const double* w, const double* m1,
                             const double* cw, const double* ca, int nout, int D, int nE, int level, size_t key_ds) {
-  check_rot(c, D);
+  check_split(c);
+  if (D > 8) fail(COPSE_EINVAL, "internal: too many digits for the fused inner product");
   if (nout < 1 || nout > level + 1) fail(COPSE_EINVAL, "internal: relinearization without output limbs");
   const size_t per = c.tune.ks_jobs > 0 ? (size_t)std::min(c.tune.ks_jobs, RelinPack::kMax) : RelinPack::kMax;
   for (size_t first = 0; first < jobs.size(); first += per) {
