@@ -1610,7 +1610,7 @@ __global__ void ks_inner2_kernel(KsPack jobs, int D_, int nE, int nl, int L, int
   const int own = o < nl ? o / alpha : -1;   // digit whose own limb this row is
   // digit j's row: the input's own limb, else the ModUp output
   auto row = [&](int j) -> const double* { return j == own ? jb.in + (size_t)o * N : jb.ext + ((size_t)j * nE + o) * N; };
-  // lazy sums: each product is in (-0.91 q, 0.91 q); D <= 8 digits stay far below 2^52
+  // lazy sums: each product is within 0.69 q; folded back after every eight digits, the sums stay below 6.1 q < 2^52
   double a0 = 0.0, a1 = 0.0;
   if (kD > 0) {
     // a known digit count: every digit's loads are issued before the first product
@@ -1633,6 +1633,10 @@ __global__ void ks_inner2_kernel(KsPack jobs, int D_, int nE, int nl, int L, int
       const size_t ko = (size_t)j * key_ds + (size_t)prime * N + i;
       a0 += mul_lazy(e, jb.kb[ko], pr.q, pr.qinv);
       a1 += mul_lazy(e, jb.ka[ko], pr.q, pr.qinv);
+      if ((j & 7) == 7) {   // uniform
+        a0 = reduce_sym(a0, pr.q, pr.qinv);
+        a1 = reduce_sym(a1, pr.q, pr.qinv);
+      }
     }
   }
   jb.acc[(size_t)o * N + i] = canon(reduce_sym(a0, pr.q, pr.qinv), pr.q);

@@ -66,3 +66,46 @@ def test_rotations_of_many_digits(C, n_data):
         ctx.profile_read(kind, True)
     same(ctx.export(ctx.evaluate(model, keys, query))[0], want)
     assert [ctx.profile_read(kind)["launches"] for kind in cols] == [0, 0]
+def lazy_product(a, b, q):
+    """The kernels' product a b - rint(fl(a b) fl(1 / q)) q, in whole numbers."""
+    return a * b - int(np.rint(float(a) * float(b) * (1.0 / q))) * q
+
+
+@pytest.mark.parametrize("log_n,bits", [(10, (49, 49, 49)), (13, (49, 44, 49))])
+@pytest.mark.parametrize("row", [5, 47])
+def test_key_switch_sums_of_46_digits(C, log_n, bits, row):
+    """The longest sum of digit x key that an evaluation has, 46 products modulo a 49-bit prime, made as large as it can
+    be in one slot of one row (a data row, the special row): added up without a fold it passes 2^53 and loses its last
+    bit.  The digits are constants, so that every slot of every row holds them: the query is the constant that the
+    reshuffle is to rotate, divided by what the comparison multiplies with."""
+    ctx, sc, model, omodel, pl, keys, okeys = one_branch_forest(C, log_n, 47, bits)
+    key, q, slot = okeys.rot[sc.galois(1)], sc.primes[row], 77
+    v, products = [], []
+    for j in range(46):
+        k = int(key.b_ntt[j][row][slot])
+        r = q * 47 // 100 // 2 * 2 + (j == 45)   # even, the last one odd
+        while True:
+            a = r * pow(k, -1, q) % q
+            if a < sc.primes[j] and lazy_product(a, k, q) == r:
+                break
+            r -= 2
+        v.append(a)
+        products.append(r)
+    total = np.float64(0.0)
+    for r in products:
+        total += np.float64(r)
+    assert int(total) != sum(products)   # without a fold
+    idx = sc.data_idx(sc.L)
+    factor = sc.plain_ntt(omodel.G[0], sc.L)
+    c1 = np.zeros((sc.L + 1, sc.N), dtype=np.uint64)
+    for i in idx[:-1]:   # the limb that the comparison's switch drops stays zero
+        qi = sc.primes[i]
+        top = v[i] * sc.primes[sc.L] % qi
+        c1[i] = np.array([top * pow(int(f), -1, qi) % qi for f in factor[i]], dtype=np.uint64)
+    polys = [random_poly(sc, np.random.default_rng(9)), sc.intt(c1, idx)]
+    x = B.Ciphertext(polys, sc.L)
+    dec = CI.Evaluator(sc, okeys, pl).seccomp([x], omodel)
+    assert all(dec.polys[1][i][0] == v[i] and not dec.polys[1][i][1:].any() for i in idx[:-1])
+    want = CI.Evaluator(sc, okeys, pl).run([x], omodel)["result"]
+    say("evaluate, 46 digits in the reshuffle, log_n", log_n, "row", row)
+    same(ctx.export(ctx.evaluate(model, keys, ctx.import_(polys, ctx.L)))[0], want)
