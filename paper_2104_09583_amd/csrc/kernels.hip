@@ -2281,7 +2281,8 @@ __global__ __launch_bounds__(256) void mm_inner_kernel(double* __restrict__ out,
 // plaintext model's products are half as many to a diagonal (2030 us against 1887 for 16 groups of the 32-tree forest).
 // Operands are below 2^b, b one more than the bits of the prime (the middle products' operands are sums of two
 // residues).  n products keep hi in its binade for n 2^(2 b) <= 2^(51 + s) and lo within 2^52 for n 2^(s - 1) <= 2^52:
-// n = 2^(52 - b) and s = b + 1 meet both (512 products for primes below 2^42, 4 for the largest).
+// n = 2^(52 - b) and s = b + 1 meet both (512 products for primes below 2^42, 4 for the largest; 2^30 are more than any
+// sum has).
 struct MmSum {
   double hi, lo;
 };
@@ -2291,7 +2292,7 @@ struct MmSplit {
 };
 __device__ __forceinline__ MmSplit mm_split(double q) {
   const int b = __builtin_amdgcn_readfirstlane((int)((__double2hiint(q) >> 20) & 0x7ff) - 1022) + 1;
-  return {__hiloint2double((1023 + 53 + b) << 20 | 1 << 19, 0), 1 << (52 - b)};
+  return {__hiloint2double((1023 + 53 + b) << 20 | 1 << 19, 0), 1 << min(52 - b, 30)};
 }
 __device__ __forceinline__ void mm_add(MmSum& a, double x, double d) {
   const double t = __fma_rn(x, d, a.hi);

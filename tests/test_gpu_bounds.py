@@ -109,3 +109,24 @@ def test_key_switch_sums_of_46_digits(C, log_n, bits, row):
     want = CI.Evaluator(sc, okeys, pl).run([x], omodel)["result"]
     say("evaluate, 46 digits in the reshuffle, log_n", log_n, "row", row)
     same(ctx.export(ctx.evaluate(model, keys, ctx.import_(polys, ctx.L)))[0], want)
+
+
+@pytest.mark.parametrize("bits", [20, 21, 22])
+def test_encrypted_matmul_of_small_primes(C, bits):
+    """The unreduced sums of an encrypted model's products with primes of 17 to 22 bits, on both sides of the size (20
+    bits) below which their fold interval would not fit its type."""
+    log_n, t = 6, 257
+    text, n_data, seed = "no yes\nB 1 1 L 0 L 1\n", 4, b"\x43" * 32
+    top = 1 << bits
+    ctx = C.Context(log_n, n_data, top, top, 1, top, t=t)
+    sc = B.BGV(nt.make_chain(log_n, t, n_data, top, top, 1, top))
+    comp, meta = C.forest_compile(text, 3, 1, log_n)
+    pl = CI.make_plan(OC.compile_forest(text, 3, 1), sc.N, sc.L, encrypted_model=True)
+    keys, okeys = ctx.keygen(seed, C.compiled_rotations(meta)), sc.keygen(seed, pl.rotations())
+    model, omodel = ctx.model_encode(comp, keys, True, seed), CI.encrypt_model(sc, okeys, pl, seed)
+    rng = np.random.default_rng(bits)
+    polys = [[random_poly(sc, rng) for _ in range(2)] for _ in range(8)]
+    say("evaluate an encrypted model, primes of", bits, "bits")
+    got = ctx.evaluate_batch(model, keys, [ctx.import_(p, ctx.L) for p in polys])
+    for r, p in zip(got, polys):
+        same(ctx.export(r)[0], CI.Evaluator(sc, okeys, pl).run([B.Ciphertext(p, sc.L)], omodel)["result"])
