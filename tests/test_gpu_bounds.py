@@ -9,6 +9,9 @@ from oracle import bgv as B
 from oracle import circuit as CI
 from oracle import compiler as OC
 from oracle import nt
+from paper_2104_09583_amd import synth
+
+import test_gpu_kernel_edges as edges
 
 pytestmark = pytest.mark.gpu
 T = 65537
@@ -130,3 +133,14 @@ def test_encrypted_matmul_of_small_primes(C, bits):
     got = ctx.evaluate_batch(model, keys, [ctx.import_(p, ctx.L) for p in polys])
     for r, p in zip(got, polys):
         same(ctx.export(r)[0], CI.Evaluator(sc, okeys, pl).run([B.Ciphertext(p, sc.L)], omodel)["result"])
+
+
+# jobs x limbs x tiles above the count from which a relinearization's finish forms its own inner products: plain rows (a
+# prime of 49 bits), and two to eight digits, whose tiles take turns in one buffer; merged with the switch (products) and
+# not (an encrypted model's inner sums)
+@pytest.mark.parametrize("bits,alpha,enc,groups,spare",
+                         [((48, 49, 49), 4, False, 64, 0), ((49, 49, 49), 3, True, 40, 0), ((48, 49, 49), 1, False, 56, 0),
+                          ((48, 48, 48), 1, False, 64, 1), ((49, 49, 49), 1, True, 40, 0), ((42, 44, 44), 2, False, 48, 5),
+                          ((49, 49, 49), 2, False, 32, 9)])
+def test_relinearizations_by_prime_size_and_digit_count(C, bits, alpha, enc, groups, spare):
+    edges.evaluate_groups(C, synth.ForestShape(3, 3, 0.9, 3, 4, 3), 74, 13, bits, alpha, enc, groups, spare=spare)
