@@ -458,11 +458,9 @@ static void ks_batch(Context& c, int level, const std::vector<const double*>& in
   for (int i = 0; i < nl; ++i) outr.push_back(make_int2(i, i));
   std::vector<double*> outs;
   std::vector<const double*> adds;
-  std::vector<uint64_t> gal;
   for (auto& rq : reqs) {
     outs.push_back(rq.out);
     adds.push_back(rq.add);
-    gal.push_back(rq.g);
   }
   if (fused) {
     launch_bridge(c, 0, zh.get(), rows_cached(c, "mdout:" + std::to_string(level), outr), nl, acc.get(),
@@ -482,6 +480,8 @@ static void ks_batch(Context& c, int level, const std::vector<const double*>& in
                rows_cached(c, "mdin:" + std::to_string(level), inr), c.alpha, T.d_md_mult, T.d_md_mat, 2 * R,
                (size_t)nE * N, (size_t)nl * N);
   launch_ntt_fwd(c, zh.get(), block_rows(c, 2 * R, nl), 2 * R * nl);
+  std::vector<uint64_t> gal;
+  for (auto& rq : reqs) gal.push_back(rq.g);
   launch_md_finish2(c, outs, adds, gal, acc.get(), zh.get(), nE, nl, T.d_md_pinv, T.d_md_tpinv, add_mode);
 }
 

@@ -418,7 +418,7 @@ __global__ __launch_bounds__(512) void ntt_rowinv_gather_kernel(double* __restri
 
 // Forward row pass fused with the end of a ModDown (kMode 1) or of a modulus switch (kMode 2).
 //   kMode 1: block (tile, i, z = job * 2 + k) transforms w row z * nl + i and writes
-//            out_job[k][i] = acc[z][i] P^-1 - w t P^-1  (+ add_job[k][i] when add_mode 1)
+//            out_job[k][i] = acc[z][i] P^-1 - w t P^-1 + add_job[k][i]
 //   kMode 2: block (tile, i, z = job * np + k) transforms w row z * l + i and writes
 //            out_job[k][i] = in_job[k][i] q_l^-1 - w t q_l^-1  (+ add_job[k][i] for k < add_np)
 //   kMode 4: as kMode 2 for the switch of a plaintext layer: in_job[k] stands for in_job[k] * mulp_job
@@ -435,7 +435,7 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(6))) void n
                                                                Pack tabs, IPack lvs,
                                                                const double* __restrict__ acc,
                                                                const double* __restrict__ w, int nE, int nl_,
-                                                               int np, int add_mode, int add_np,
+                                                               int np, int add_np,
                                                                const double* __restrict__ mul,
                                                                const double* __restrict__ tmul,
                                                                const DevPrime* __restrict__ P, int logN, int S1,
@@ -514,7 +514,7 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(6))) void n
     // an optional mask (the `in` pack, l limbs per poly) on the first add_np polys
     if (k < add_np && in.p[j] != nullptr) add_row(in.p[j] + orow + t0);
   } else if (kMode == 1) {
-    if (add_mode == 1) add_row(add.p[j] + orow + t0);
+    add_row(add.p[j] + orow + t0);
   } else if (kMode == 2) {
     if (k < add_np && add.p[j] != nullptr) add_row(add.p[j] + orow + t0);
   }
@@ -1016,7 +1016,7 @@ void launch_ntt_fwd_rows_md_finish(Context& c, const std::vector<double*>& out, 
     IPack nolv{};
     hipLaunchKernelGGL(ntt_rowfwd_finish_kernel<1>, dim3((unsigned)(c.N / 4096), nl, 2 * cnt), dim3(512), 0,
                        c.stream, po, none, pa, none, none, nolv, acc + first * 2 * nE * c.N,
-                       w + first * 2 * nl * c.row_doubles(), nE, nl, 2, 1, 0, pinv, tpinv, c.d_primes, (int)c.log_n,
+                       w + first * 2 * nl * c.row_doubles(), nE, nl, 2, 0, pinv, tpinv, c.d_primes, (int)c.log_n,
                        (int)c.log_n - 12, nullptr, none, c.packed);
     COPSE_HIP(hipGetLastError());
     prof_end(c, 7, ev, 8.0 * nl * cnt * (double)c.N * 8.0);
@@ -1046,7 +1046,7 @@ void launch_ntt_fwd_rows_mdms_finish(Context& c, const std::vector<double*>& out
     prof_begin(c, 7, &ev);
     hipLaunchKernelGGL(ntt_rowfwd_finish_kernel<3>, dim3((unsigned)(c.N / 4096), l, 2 * cnt), dim3(512), 0,
                        c.stream, po, pm, pa, none, none, nolv, acc + first * 2 * nE * c.N,
-                       w + first * 2 * l * c.row_doubles(), nE, l, 2, 0, masks ? mask_np : 0, m1, m2, c.d_primes,
+                       w + first * 2 * l * c.row_doubles(), nE, l, 2, masks ? mask_np : 0, m1, m2, c.d_primes,
                        (int)c.log_n, (int)c.log_n - 12, m3, pb, c.packed);
     COPSE_HIP(hipGetLastError());
     // per output row: the bridge's row, the accumulator and addend rows read (a product's addend: its two
@@ -1085,11 +1085,11 @@ void launch_ntt_fwd_rows_ms_finish(Context& c, const std::vector<double*>& out, 
     prof_begin(c, 8, &ev);
     if (mulp)   // the plaintext layer (`add` holds its addends, no post-switch add)
       hipLaunchKernelGGL(ntt_rowfwd_finish_kernel<4>, dim3((unsigned)(c.N / 4096), lmax, np * cnt), dim3(512), 0,
-                         c.stream, po, pi, pa, pw, pt, lv, nullptr, nullptr, 0, 0, np, 0, 0, nullptr, nullptr,
+                         c.stream, po, pi, pa, pw, pt, lv, nullptr, nullptr, 0, 0, np, 0, nullptr, nullptr,
                          c.d_primes, (int)c.log_n, (int)c.log_n - 12, nullptr, pm, c.packed);
     else
       hipLaunchKernelGGL(ntt_rowfwd_finish_kernel<2>, dim3((unsigned)(c.N / 4096), lmax, np * cnt), dim3(512), 0,
-                         c.stream, po, pi, pa, pw, pt, lv, nullptr, nullptr, 0, 0, np, 0, add ? add_np : 0,
+                         c.stream, po, pi, pa, pw, pt, lv, nullptr, nullptr, 0, 0, np, add ? add_np : 0,
                          nullptr, nullptr, c.d_primes, (int)c.log_n, (int)c.log_n - 12, nullptr, pm, c.packed);
     COPSE_HIP(hipGetLastError());
     prof_end(c, 8, ev, bytes);
