@@ -128,7 +128,9 @@ void* copse_ctx_stream(copse_ctx* ctx);
 int copse_ctx_set_stream(copse_ctx* ctx, void* stream);
 /* Blocks until all work enqueued on the context's stream has finished. */
 int copse_ctx_sync(copse_ctx* ctx);
-/* Device bytes currently held by the context's pool (in use + cached). */
+/* Device bytes currently held by the context's pool (in use + cached).  Not
+ * counted: pinned host memory of the context, at most 16 MiB from its first
+ * import or export on, none where the system has none left. */
 size_t copse_ctx_device_bytes(const copse_ctx* ctx);
 
 /* Launch-shape knobs of the evaluation (chosen by an autotuner; none of them

@@ -217,8 +217,8 @@ void ShakeStream::read(uint8_t* out, size_t n) {
 namespace {
 // Up to eight SHAKE-256 streams of SHAKE256(seed || domain || le64(object) || le32(limb)), squeezed together a block
 // (136 bytes of every stream) at a time.  A stream is one chain of permutations, so the eight run in the lanes of one
-// vector: with 512-bit registers a permutation of all eight takes 0.45 us, of one alone 0.43 us (eight plaintexts'
-// randomness, N = 32768: 17.6 ms one stream at a time, 1.8 ms here).
+// vector: with 512-bit registers a permutation of all eight takes 0.45 us, of one alone 0.43 us (on one host; eight
+// plaintexts' randomness, N = 32768, takes 17.6 ms there one stream at a time, 1.8 ms so).
 class ShakeStreams {
  public:
   ShakeStreams(const uint8_t seed[32], int n) : n_(n) { std::memcpy(seed_, seed, 32); }

@@ -654,8 +654,8 @@ void launch_ntt_inv(Context& c, double* base, const int2* rows, int nrows) {
 //            lifts are z_m = centered [x_m mult_m - sum_{u<m} z_u D_u D_m^-1]_{p_m} (mat[k n_out + 4 m + u]
 //            holds D_u D_m^-1 mod p_m) and out_o = sum_m z_m D_m mod q_o (mat[m n_out + o] = D_m mod q_o);
 //            the finish then computes (c - t out) D_k^-1.
-// The values handed to the forward stages are any representatives of the residues (|v| <= q/2), so the
-// transform's canonical output is the same as that of the unfused steps.
+// The values handed to the forward stages are any representatives of the residues (within q / 2, or below 8 q for
+// small primes), so the transform's canonical output is the same as that of the unfused steps.
 // grid: x over column groups of 64, y over the maps (digits), z over the batch (in_bs / out_bs apart).
 constexpr int kBridgeIn = 4;
 // A workgroup is 64 columns x W waves: wave k runs the inverse stages of input rows k, k + W, ... and leaves
@@ -736,8 +736,10 @@ __global__ __launch_bounds__(1024) void ntt_bridge_kernel(BridgeSet set, const D
     }
 #pragma unroll
     for (int r = 0; r < R; ++r) {
-      // for S1 <= 3, |x| < 4 p_k, so the lazy product lies in (-p_k, p_k) and canon gives
-      // [coef * mult_k]_{p_k}; four stages can reach 8 p_k, so the product is folded back first
+      // the stages double |x| each: after three, 4 p_k from p_k / 2, or, for primes whose row pass leaves its output
+      // unreduced (kInvOpen), 256 p_k <= 2^50 from 32 p_k.  Either way the lazy product lies in (-p_k, p_k) and canon
+      // gives [coef * mult_k]_{p_k}.  Four stages reach 8 p_k or 512 p_k <= 2^51, the product up to 2 p_k: folded back
+      // first.
       double v = mul_lazy(x[r], nm, pk.q, pk.qinv);
       if (S1 > 3) v = reduce_sym(v, pk.q, pk.qinv);
       v = canon(v, pk.q);
@@ -1691,7 +1693,7 @@ void launch_ks_inner2(Context& c, const std::vector<KsJob2>& jobs, int D, int nE
 // them after the column stages; a digit's own limbs come from the input in NTT form, a product's formed
 // from both operands) and accumulates digit x key in registers, so the extended rows are never written in
 // NTT form.  Rows o >= inv_from (the rows the ModDown transforms back) leave after the inverse row pass.
-// At most 128 registers (four waves per SIMD) and two tile buffers (68 KiB), so that two workgroups share a
+// At most 128 registers (four waves per SIMD) and two tile buffers (64 KiB), so that two workgroups share a
 // compute unit and one transforms while the other waits on memory: the first two digits to transform run
 // as one pair (row4_fwd_tile2) before any sum is live, further digits one at a time, the row's own digit
 // last; the keys are read after each transform, one polynomial at a time; the two sums' inverse row passes
@@ -2276,7 +2278,7 @@ __global__ __launch_bounds__(256) void mm_inner_kernel(double* __restrict__ out,
 // fused multiply-add into it rounds the product to a multiple of 2^s, the difference of its two values is that multiple,
 // and a second fused multiply-add gives the rest exactly: four instructions a product instead of the seven of a reduced
 // product and its addition.  The 64-tree encrypted model's MatMul, bound by fp64 issue, took 23.3 ms a launch of 16
-// groups without and takes 20.2 so; of the 8-tree one's 1441 and 1387 us.  With four batch elements to a workgroup the
+// groups without and takes 19.9 so, the 8-tree one's 1441 and 1376 us.  With four batch elements to a workgroup the
 // sums wait on memory, which the registers of the second double leave less overlap (three groups 375 and 396 us), and a
 // plaintext model's products are half as many to a diagonal (2030 us against 1887 for 16 groups of the 32-tree forest).
 // Operands are below 2^b, b one more than the bits of the prime (the middle products' operands are sums of two
@@ -2513,7 +2515,7 @@ void launch_mm_inner(Context& c, double* out, const double* baby, const double* 
   // registers), against two at 24 groups, and the baby values a further chunk reads again are in the XCD's L2.  16
   // groups' queries of the 32-tree forest: 1887 us against 1981 at 24 and 1937 at 8, three groups of the 16-tree forest
   // 255 against 266 and 252.  At most 8 where the sums take two doubles: two workgroups (122 registers) against one,
-  // 20.2 ms against 25.8 for the 64-tree encrypted model.
+  // 19.9 ms a launch against 25.8 for the 64-tree encrypted model.
   const bool split = enc && G % 8 == 0 && c.tune.mm_waves != 4;
   const int cap = c.tune.mm_cap > 0 ? std::min(32, std::max(4, c.tune.mm_cap)) : split ? 8 : 12;
   const int chunks = (ng + cap - 1) / cap;

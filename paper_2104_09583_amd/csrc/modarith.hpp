@@ -35,12 +35,13 @@ __device__ __forceinline__ double mod_reduce(double v, double q, double qinv) {
   return r;
 }
 
-// Lazy (signed) residues for the transforms.  With q < 2^49 and |a| < 4q, |b| < q:
-//   mul_lazy: k = rint(a b / q) is within 0.5 + 2^-3 of the exact quotient, so
-//   r = a b - k q = fma(-k, q, h) + l is an exact integer with |r| < 0.91 q;
+// Lazy (signed) residues for the transforms, for q < 2^49 and |b| < q:
+//   mul_lazy: k = rint(a b / q) is off by three roundings (of a b, of 1 / q, of their product), so r = a b - k q =
+//   fma(-k, q, h) + l is an exact integer with |r| <= (0.5 + 3 x 2^-53 |a|) q: 0.69 q for |a| < q, 0.875 q for
+//   |a| <= 2^50, and below q for |a| <= 4 q as well (for q > 2^48 the roundings are within 2^46 / q, 4 q^2 2^-102 and
+//   2^-3, together 0.5 at 2^49);
 //   reduce_sym: x - q rint(x / q) lies in [-q/2, q/2] for |x| < 8 q;
-//   canon: maps [-q/2, q/2] to [0, q).
-// In general |mul_lazy(a, b)| <= (0.5 + 3 x 2^-53 |a|) q: the quotient estimate is off by three roundings.
+//   canon: maps [-q/2, q/2] to [0, q), and (-q, q) too.
 // Forward, a stage adds one such product to |x|: from |x| <= q six stages reach at most 7.6 q < 2^52 for
 // q = 2^49, every value still an exact integer, so the row pass folds back once, after its second radix-8
 // round; for q < 2^46 (kFwdLazy) its twelve stages stay below 20 q even from 8 q, and it never does.  Inverse, a

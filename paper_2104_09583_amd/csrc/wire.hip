@@ -340,8 +340,8 @@ __global__ void enc_combine_kernel(MPack out, const double* rows, const double* 
 }
 
 // Fresh encryptions at `level` of n plaintexts given by their coefficients in [0, t): (pk0 u + t e0 + m, pk1 u + t e1)
-// A full group of eight planes encrypted and exported takes 4.3 ms (40.5 ms with encoding, sampling and layout on one
-// host core): 1.8 the host's SHAKE-256, 0.4 the device, the rest the 42 MB copied out to fresh pages.
+// A full group of eight planes encrypted and exported takes 4.2 ms (40.5 ms with encoding, sampling and layout on one
+// host core): 0.7 the host's SHAKE-256, 0.3 the device, the rest the 42 MB copied out to fresh pages.
 static void encrypt_many(Context& c, const Keys& k, const DBuf& m, int n, int level, const uint8_t seed[32],
                          const uint64_t* objs, std::vector<CtPtr>& out) {
   const size_t N = c.N, stride = encryption_noise_bytes(N);
